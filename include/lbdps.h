@@ -460,10 +460,10 @@ lbdps_status lbdps_kernel_times(lbdps_ctx *ctx, double *h_ms, int64_t *h_launche
 /*
  * Launch shapes that do not change results (every setting gives the same
  * numbers bit for bit), only speed:
- *   cluster_lists      candidate lists of the contact kernel taken by one
+ *   cluster_lists      with sphere_tile > 0: runs of candidate roots taken by one
  *                      workgroup of the cluster resolution, [1, 256] (default 1);
- *   cluster_groups_max most workgroups of the cluster resolution (default: no
- *                      limit);
+ *   cluster_groups_max with sphere_tile > 0: most workgroups of the cluster
+ *                      resolution (default: no limit);
  *   drag_tile          cells of the drag kernel's workgroup tile (its node fields
  *                      staged in LDS): 0 = 32 x 8 (default), 1 = 64 x 4,
  *                      2 = 128 x 2.  The beds of a batch share one.
@@ -471,8 +471,8 @@ lbdps_status lbdps_kernel_times(lbdps_ctx *ctx, double *h_ms, int64_t *h_launche
  *                      particles and the ring of cells around it are held in LDS
  *                      (contacts, clusters inside the tile resolved there, the
  *                      rest through neighbour rows): 0 = none, every particle
- *                      through the rows (default), 1 = 32 x 8, 2 = 16 x 16,
- *                      3 = 64 x 4.  A batched step takes the rows.
+ *                      through the rows, resolved patch by patch (default),
+ *                      1 = 32 x 8, 2 = 16 x 16, 3 = 64 x 4.  A batched step takes 0.
  * A context starts with the defaults.
  */
 typedef struct {
@@ -526,7 +526,7 @@ lbdps_status lbdps_batch_create(const lbdps_params *beds, int32_t nbeds, const i
 /* The context of bed `bed` (owned by the batch). */
 lbdps_status lbdps_batch_bed(lbdps_batch *batch, int32_t bed, lbdps_ctx **out);
 
-/* Enqueue nsteps steps of every bed: 7 launches per step for the whole batch.
+/* Enqueue nsteps steps of every bed: one launch per phase for the whole batch (8 to 10 per step).
  * Results equal nsteps calls of lbdps_step on each bed, bit for bit. */
 lbdps_status lbdps_batch_step(lbdps_batch *batch, int32_t nsteps);
 

@@ -8,10 +8,11 @@
 #pragma once
 
 #include "kernels.hpp"
+#include "patches.hpp"
 
 namespace lbdps {
 
-enum { PH_COLLIDE = 0, PH_DRAG, PH_SCAN, PH_SCATTER, PH_CONTACTS, PH_CLUSTERS, PH_RESOLVE, PH_COUNT };
+enum { PH_COLLIDE = 0, PH_DRAG, PH_SCAN, PH_SCATTER, PH_CONTACTS, PH_PATCH0, PH_PATCH1, PH_PATCH2, PH_FINAL, PH_COUNT };
 
 template <int P> struct BedArgs {
   using T = typename Prec<P>::T;
@@ -22,15 +23,17 @@ template <int P> struct BedArgs {
   T *px[2], *py[2], *vx[2], *vy[2];
   Fields<T> fl;
   const T *lut, *inlet;
-  int32_t *cs, *count, *stay, *rank, *slot, *flags, *deg, *done, *ticket, *chunk_busy, *need_sweep, *rcount;
-  long long *roots;
+  int32_t *cs, *count, *stay, *rank, *slot, *flags, *deg, *sweep, *left, *place_of;
+  FinalMem fin;
   Adj adj;
-  long long *pair_part, *wall0_part, *coll_part, *wall_part, *collc_part, *wallc_part;
+  long long *pair_part, *wall0_part;
+  PatchGrid pg[PATCH_PASSES];
+  int npass;  // patch passes of this bed; 0: the whole bed in the final workgroup
+  int32_t *pcoll_part[PATCH_PASSES + 1], *pwall_part[PATCH_PASSES + 1];
   TileSums ts;
   int cf;        // population buffer holding the state when the table was written
   int cp;        // particle record set holding the state when the table was written
   int cp_moves;  // 1 if the bed has particles (its records change sets every step)
-  int nlists;    // candidate-root lists of the contact kernel (its workgroups)
   __device__ Parts<T> parts(int b) const { return Parts<T>{key[b], pid[b], px[b], py[b], vx[b], vy[b]}; }
 };
 
@@ -101,24 +104,27 @@ template <int P>
 __global__ __launch_bounds__(BLOCK) LBDPS_WAVES8 void kb_contacts(const BedArgs<P> *__restrict__ tab, const int *__restrict__ off,
                                                      int nbeds, int flip) {
   LBDPS_BED_PROLOGUE(XCD_RUN_CONTACTS)
-  contacts_body<P>(bid, nbk, a.parts(1 - cp), a.cs, a.k, a.adj, a.deg, a.done, a.ticket, a.flags, a.pair_part,
-                   a.wall0_part, a.chunk_busy, a.need_sweep, a.roots, a.rcount);
+  contacts_body<P>(bid, nbk, a.parts(1 - cp), a.cs, a.k, a.adj, a.deg, a.flags, a.pair_part, a.wall0_part, a.sweep);
+}
+
+template <int P, int HELD, bool FIRST>
+__global__ __launch_bounds__(BLOCK) void kb_patches(const BedArgs<P> *__restrict__ tab, const int *__restrict__ off,
+                                                    int nbeds, int flip, int pass) {
+  LBDPS_BED_PROLOGUE(XCD_RUN_PATCHES)
+  (void)nbk;
+  patches_body<P, BLOCK, HELD, FIRST>(bid, a.parts(1 - cp), a.cs, a.k, a.adj, a.deg, a.pg[pass],
+                                                    pass + 1 == a.npass, a.left, a.place_of, a.sweep + SW_LEFT, a.pcoll_part[pass],
+                                                    a.pwall_part[pass]);
 }
 
 template <int P>
-__global__ __launch_bounds__(BLOCK) void kb_clusters(const BedArgs<P> *__restrict__ tab, const int *__restrict__ off,
-                                                     int nbeds, int flip) {
-  LBDPS_BED_PROLOGUE(XCD_RUN_CLUSTERS)
-  resolve_clusters_body<P>(bid, nbk, a.parts(1 - cp), a.adj, a.deg, a.done, a.k, a.need_sweep, a.collc_part,
-                           a.wallc_part, a.roots, a.rcount, a.nlists);
-}
-
-template <int P>
-__global__ __launch_bounds__(BLOCK) void kb_resolve(const BedArgs<P> *__restrict__ tab, const int *__restrict__ off,
-                                                    int nbeds, int flip) {
-  LBDPS_BED_PROLOGUE(XCD_RUN_RESOLVE)
-  resolve_body<P>(bid, nbk, a.parts(1 - cp), a.slot, a.adj, a.deg, a.done, a.ticket, a.k, a.flags, a.coll_part,
-                  a.wall_part, a.chunk_busy, a.need_sweep);
+__global__ __launch_bounds__(FINAL_THREADS) void kb_final(const BedArgs<P> *__restrict__ tab,
+                                                          const int *__restrict__ off, int nbeds, int flip) {
+  LBDPS_BED_PROLOGUE(-1)
+  (void)bid;
+  (void)nbk;
+  final_body<P>(a.parts(1 - cp), a.k, a.adj, a.deg, a.npass == 0, a.left, a.place_of, a.sweep + SW_LEFT, a.fin,
+                a.pcoll_part[PATCH_PASSES], a.pwall_part[PATCH_PASSES]);
 }
 
 #undef LBDPS_BED_PROLOGUE

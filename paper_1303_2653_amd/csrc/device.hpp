@@ -49,7 +49,7 @@ template <int R> __host__ __device__ constexpr int xcd_block(int bid, int gdim) 
 // batch of uneven beds, where one run per XCD left some XCDs idle.  The
 // streaming kernels keep the dispatch order.
 constexpr int XCD_RUN_COLLIDE = -1, XCD_RUN_DRAG = 8, XCD_RUN_SCAN = -1, XCD_RUN_SCATTER = -1,
-              XCD_RUN_CONTACTS = 8, XCD_RUN_CLUSTERS = 8, XCD_RUN_RESOLVE = -1;
+              XCD_RUN_CONTACTS = 8, XCD_RUN_PATCHES = 8, XCD_RUN_CLUSTERS = 8, XCD_RUN_RESOLVE = -1;
 
 enum { BC_PERIODIC = 0, BC_WALL = 1, BC_INLET = 2, BC_OUTLET = 3 };
 enum { PREC_FP64 = 0, PREC_FP32 = 1, PREC_FP16DEV = 2, PREC_BF16DEV = 3 };

@@ -275,7 +275,14 @@ template <int P> struct Pos {
 // stored densely ([N][ADJ_IN], one 32-byte run per particle); entries
 // ADJ_IN .. KMAX-1, which few particles have, in a second array
 // ([N][KMAX - ADJ_IN]).
+// The contact kernel also notes in which row of cells the partner lies, above
+// the slot (slots are below 2^29): bits 29-30 hold the row offset plus one.
 constexpr int ADJ_IN = 4;
+__device__ __forceinline__ long long adj_entry(int id, int slot, int dy) {
+  return ((long long)id << 32) | (unsigned)(slot | (dy + 1) << 29);
+}
+__device__ __forceinline__ int adj_slot(long long e) { return (int)(e & 0x1fffffffll); }
+__device__ __forceinline__ int adj_dy(long long e) { return (int)((unsigned)e >> 29 & 3u) - 1; }
 struct AdjRow {
   long long *a, *b;
   __device__ long long &operator[](int i) const { return i < ADJ_IN ? a[i] : b[i - ADJ_IN]; }
@@ -320,6 +327,9 @@ constexpr int RES_ITEMS = 8;                  // particle indices per lane and r
 // a cluster left to the sweep keeps the plain count of its finished pairs.
 constexpr int DONE_WHOLE = 1 << 30;
 constexpr int RES_CHUNK = BLOCK * RES_ITEMS;  // particle indices per chunk
+// The collision stage's counters: whether the ordered sweep has to run, the
+// tile kernel's candidate roots, the particles the patches left.
+enum { SW_NEED = 0, SW_ROOTS, SW_LEFT, SW_COUNT };
 
 // Block-wide exclusive scan of one int per thread; total = block sum.
 __device__ __forceinline__ int block_excl_scan(int v, int *sh, int &total) {
@@ -1363,20 +1373,13 @@ constexpr int CT_ALL = 0, CT_ROWS = 2;
 template <int P, int W = CONTACT_W, int MODE = CT_ALL>
 __device__ __forceinline__ void contacts_body(const int bidx, const int gdim, Parts<typename Prec<P>::T> pt,
     const int32_t *__restrict__ cs, Consts<typename Prec<P>::T> k, Adj adj, int32_t *__restrict__ deg,
-    int32_t *__restrict__ done, int32_t *ticket, int32_t *flags, long long *pair_part, long long *wall_part,
-    int32_t *__restrict__ chunk_busy, int32_t *need_sweep, long long *__restrict__ roots,
-    int32_t *__restrict__ rcount) {
+    int32_t *flags, long long *pair_part, long long *wall_part, int32_t *sweep) {
   using T = typename Prec<P>::T;
   __shared__ long long sh[BLOCK / 64];
-  __shared__ int shi[BLOCK / 64];
   const int s = bidx * BLOCK + threadIdx.x;
   long long fwd = 0, nwall = 0;
-  bool cand = false;  // has contacts, all with higher indices: a possible cluster root
   bool by_wall_pass = true;
-  if (MODE != CT_ROWS && s == 0) {
-    *ticket = 0;
-    *need_sweep = 0;
-  }
+  if (MODE != CT_ROWS && s == 0) sweep[SW_LEFT] = 0;
   if (s < k.npart) {
     const int key = pt.key[s];
     const int id = pt.pid[s];
@@ -1449,7 +1452,7 @@ __device__ __forceinline__ void contacts_body(const int bidx, const int gdim, Pa
         if (t == s) return;
         T dx, dy;
         Pos<P>::sep_nb(k, ox, oy, x, y, pt.px[t], pt.py[t], dx, dy);
-        if (dx * dx + dy * dy <= dd) hit(t, pt.pid[t]);
+        if (dx * dx + dy * dy <= dd) hit(t, pt.pid[t], oy);
       };
       if (inner_x) {
         // one flattened pass over the three rows' ranges, CONTACT_CH candidates
@@ -1481,7 +1484,7 @@ __device__ __forceinline__ void contacts_body(const int bidx, const int gdim, Pa
             if (q0 + j < tot && tt[j] != s) {
               T dx, dy;
               Pos<P>::sep_nb(k, ox[j], oy[j], x, y, xs[j], ys[j], dx, dy);
-              if (dx * dx + dy * dy <= dd) hit(tt[j], ids[j]);
+              if (dx * dx + dy * dy <= dd) hit(tt[j], ids[j], oy[j]);
             }
           }
         }
@@ -1521,7 +1524,7 @@ __device__ __forceinline__ void contacts_body(const int bidx, const int gdim, Pa
         if (t >= lo1 && t < hi1) {
           T dx, dy;
           Pos<P>::sep_nb(k, t < a1 ? -1 : (t < b1 ? 0 : 1), 0, x, y, wx[j], wy[j], dx, dy);
-          if (dx * dx + dy * dy <= dd) hit(t, wid[j]);
+          if (dx * dx + dy * dy <= dd) hit(t, wid[j], 0);
         }
       }
       const int mlo = max(lo1, s + W + 1);
@@ -1550,15 +1553,15 @@ __device__ __forceinline__ void contacts_body(const int bidx, const int gdim, Pa
           if (q0 + j < tot) {
             T dx, dy;
             Pos<P>::sep_nb(k, ox[j], oy[j], x, y, xs[j], ys[j], dx, dy);
-            if (dx * dx + dy * dy <= dd) hit(tt[j], ids[j]);
+            if (dx * dx + dy * dy <= dd) hit(tt[j], ids[j], oy[j]);
           }
         }
       }
     };
-    first_scan([&](int t, int tid) {
+    first_scan([&](int t, int tid, int dy) {
       if (tid > id) ++fwd;
       if (cnt < CONTACT_REG) {
-        const long long e = ((long long)tid << 32) | (unsigned)t;
+        const long long e = adj_entry(tid, t, dy);
         bool placed = false;
 #pragma unroll
         for (int u = CONTACT_REG - 1; u >= 0; --u)
@@ -1579,12 +1582,12 @@ __device__ __forceinline__ void contacts_body(const int bidx, const int gdim, Pa
         if (u < cnt) row[u] = r[u];
     } else {
       int m = 0;
-      scan([&](int t, int tid) {
+      scan([&](int t, int tid, int dy) {
         if (m == KMAX) {
           over = true;
           return;
         }
-        const long long e = ((long long)tid << 32) | (unsigned)t;
+        const long long e = adj_entry(tid, t, dy);
         int j = m;
         while (j > 0 && row[j - 1] > e) {
           row[j] = row[j - 1];
@@ -1601,9 +1604,6 @@ __device__ __forceinline__ void contacts_body(const int bidx, const int gdim, Pa
       by_wall_pass = false;
     } else {
       if (over) atomicOr(&flags[FLAG_CAPACITY], 1);
-      if (cnt > 0) cand = (int)((cnt <= CONTACT_REG ? r[0] : row[0]) >> 32) > id;
-      done[s] = 0;
-      if (cnt > 0) chunk_busy[id / RES_CHUNK] = 1;  // the resolution visits this chunk of indices
     }
     if (by_wall_pass && cnt == 0 && by_wall) {  // no binary collision: the wall pass can run now
       const int h = Pos<P>::walls(k, cx, cy, x, y, vx0, vy0);
@@ -1615,28 +1615,20 @@ __device__ __forceinline__ void contacts_body(const int bidx, const int gdim, Pa
     }
   }
   if constexpr (MODE == CT_ROWS) return;  // uniform
-  // candidate roots of this workgroup, compacted to the front of its segment
-  int nc;
-  const int off = block_excl_scan(cand ? 1 : 0, shi, nc);
-  if (cand) roots[(size_t)bidx * BLOCK + off] = ((long long)pt.pid[s] << 32) | (unsigned)s;
   long long t, tw;
   block_sum2(fwd, nwall, sh, t, tw);
   if (threadIdx.x == 0) {
     pair_part[bidx] = t;
     wall_part[bidx] = tw;
-    rcount[bidx] = nc;
   }
 }
 template <int P, int MODE = CT_ALL>
 __global__ __launch_bounds__(BLOCK) LBDPS_WAVES8 void k_contacts(Parts<typename Prec<P>::T> pt, const int32_t *__restrict__ cs,
                                                     Consts<typename Prec<P>::T> k, Adj adj,
-                                                    int32_t *__restrict__ deg, int32_t *__restrict__ done,
-                                                    int32_t *ticket, int32_t *flags, long long *pair_part,
-                                                    long long *wall_part, int32_t *__restrict__ chunk_busy,
-                                                    int32_t *need_sweep, long long *__restrict__ roots,
-                                                    int32_t *__restrict__ rcount) {
-  contacts_body<P, CONTACT_W, MODE>(xcd_block<XCD_RUN_CONTACTS>(blockIdx.x, gridDim.x), gridDim.x, pt, cs, k, adj, deg, done, ticket, flags, pair_part, wall_part, chunk_busy,
-      need_sweep, roots, rcount);
+                                                    int32_t *__restrict__ deg, int32_t *flags,
+                                                    long long *pair_part, long long *wall_part, int32_t *sweep) {
+  contacts_body<P, CONTACT_W, MODE>(xcd_block<XCD_RUN_CONTACTS>(blockIdx.x, gridDim.x), gridDim.x, pt, cs, k, adj, deg,
+                                    flags, pair_part, wall_part, sweep);
 }
 // Grids whose workgroups are all resident at once (CONTACTS_SMALL_MAX): a wider
 // early-loaded window at six waves per SIMD, since latency rather than the
@@ -1645,12 +1637,9 @@ constexpr int CONTACTS_SMALL_MAX = 1536;
 template <int P, int MODE = CT_ALL>
 __global__ __launch_bounds__(BLOCK) LBDPS_WAVES6 void k_contacts_small(Parts<typename Prec<P>::T> pt,
     const int32_t *__restrict__ cs, Consts<typename Prec<P>::T> k, Adj adj, int32_t *__restrict__ deg,
-    int32_t *__restrict__ done, int32_t *ticket, int32_t *flags, long long *pair_part, long long *wall_part,
-    int32_t *__restrict__ chunk_busy, int32_t *need_sweep, long long *__restrict__ roots,
-    int32_t *__restrict__ rcount) {
+    int32_t *flags, long long *pair_part, long long *wall_part, int32_t *sweep) {
   contacts_body<P, CONTACT_W_SMALL, MODE>(xcd_block<XCD_RUN_CONTACTS>(blockIdx.x, gridDim.x), gridDim.x, pt, cs, k, adj,
-                                    deg, done, ticket, flags, pair_part, wall_part, chunk_busy, need_sweep, roots,
-                                    rcount);
+                                          deg, flags, pair_part, wall_part, sweep);
 }
 
 // ------------------------------------------------------------------ A7: collision resolution (Eqs. 17-18) and walls
@@ -1723,8 +1712,8 @@ __device__ __forceinline__ int wall_pass(const Consts<typename Prec<P>::T> &k, P
 // Contact clusters (connected components of the contact graph) are independent:
 // a pair only touches its two particles, so resolving every cluster's pairs in
 // lexicographic order gives the sequential sweep's result bit for bit.  The
-// contact kernel lists, per workgroup, the particles whose neighbours all have
-// higher indices: every cluster's lowest index is among them.  A lane takes one
+// tile kernel lists the particles whose neighbours all have higher indices:
+// every cluster's lowest index is among them.  A lane takes one
 // such candidate, gathers its cluster breadth-first and gives up as soon as it
 // meets a lower index (the cluster belongs to another candidate).  Otherwise it
 // orders the members by index, applies the pairs in order, runs the wall pass
@@ -2096,8 +2085,8 @@ __device__ int resolve_group(ClusterLds<P, G> &B, int *shi, int s0, int g, const
 template <int P>
 __device__ __forceinline__ void resolve_clusters_body(const int bidx, const int gdim, Parts<typename Prec<P>::T> pt,
     Adj adj, const int32_t *__restrict__ deg, int32_t *done, Consts<typename Prec<P>::T> k, int32_t *need_sweep,
-    long long *coll_part, long long *wall_part, const long long *__restrict__ roots,
-    const int32_t *__restrict__ rcount, int nlists, const int32_t *nroots = nullptr) {
+    long long *coll_part, long long *wall_part, const long long *__restrict__ roots, int nlists,
+    const int32_t *nroots) {
   __shared__ long long sh[BLOCK / 64];
   __shared__ int shi[BLOCK / 64];
   __shared__ int pre[BLOCK + 1];
@@ -2114,7 +2103,7 @@ __device__ __forceinline__ void resolve_clusters_body(const int bidx, const int 
     nbig = 0;
     nhuge = 0;
   }
-  // candidate lists [b0, b0 + nb) of the contact kernel's workgroups
+  // candidate lists [b0, b0 + nb): list j is the j-th run of BLOCK candidates
   const int per = (nlists + gdim - 1) / gdim;  // <= BLOCK (host grid choice)
   const int b0 = bidx * per;
   const int nb = max(0, min(nlists - b0, per));
@@ -2122,12 +2111,9 @@ __device__ __forceinline__ void resolve_clusters_body(const int bidx, const int 
   // a contact row over its capacity leaves the contact graph incomplete: the
   // resolution is skipped and the step reports LBDPS_E_CAPACITY
   const bool overflow = __hip_atomic_load(&k.flags[FLAG_CAPACITY], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
-  // list j holds rcount[j] candidates, or, with one compact list of *nroots
-  // (the tile kernel's), its j-th run of BLOCK
-  // (the counts are loaded alongside the flag, not after it)
+  // (the count is loaded alongside the flag, not after it)
   int c = 0;
-  if ((int)threadIdx.x < nb)
-    c = nroots ? min(max(*nroots - (b0 + (int)threadIdx.x) * BLOCK, 0), BLOCK) : rcount[b0 + threadIdx.x];
+  if ((int)threadIdx.x < nb) c = min(max(*nroots - (b0 + (int)threadIdx.x) * BLOCK, 0), BLOCK);
   if (overflow) c = 0;
   const int o = block_excl_scan(c, shi, tot);
   if (tot == 0) {  // no candidate roots in these lists (uniform: the scan's total)
@@ -2191,11 +2177,10 @@ __global__ __launch_bounds__(BLOCK) void k_resolve_clusters(Parts<typename Prec<
                                                             const int32_t *__restrict__ deg, int32_t *done,
                                                             Consts<typename Prec<P>::T> k, int32_t *need_sweep,
                                                             long long *coll_part, long long *wall_part,
-                                                            const long long *__restrict__ roots,
-                                                            const int32_t *__restrict__ rcount, int nlists,
+                                                            const long long *__restrict__ roots, int nlists,
                                                             const int32_t *nroots) {
   resolve_clusters_body<P>(xcd_block<XCD_RUN_CLUSTERS>(blockIdx.x, gridDim.x), gridDim.x, pt, adj, deg, done, k, need_sweep, coll_part, wall_part, roots,
-      rcount, nlists, nroots);
+      nlists, nroots);
 }
 
 // Position of particle index g in the neighbour list of slot t: the number of
@@ -2273,7 +2258,7 @@ __device__ __forceinline__ void resolve_body(const int bidx, const int gdim, Par
         a = 0;
         while (a < dg && (int)(row[a] >> 32) < g) ++a;
         if (a < dg) {
-          t = (int)(row[a] & 0xffffffffll);
+          t = adj_slot(row[a]);
           b = row_position(adj, deg, t, g);
           state = 0;
         } else {
@@ -2297,7 +2282,7 @@ __device__ __forceinline__ void resolve_body(const int bidx, const int gdim, Par
           __hip_atomic_store(&done[s], a + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           ++a;
           if (a < dg) {
-            t = (int)(row[a] & 0xffffffffll);
+            t = adj_slot(row[a]);
             b = row_position(adj, deg, t, g);
           } else {
             state = 1;

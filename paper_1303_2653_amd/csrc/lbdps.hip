@@ -19,6 +19,7 @@
 #include "kernels.hpp"
 #include "lattice3d.hpp"
 #include "lbdps.h"
+#include "patches.hpp"
 #include "spheres_tile.hpp"
 
 using namespace lbdps;
@@ -79,12 +80,54 @@ int nblocks(long long n) { return (int)((n + BLOCK - 1) / BLOCK); }
 constexpr int DRAG_FLAT_MIN = 2048;
 bool drag_flat(long long tiles) { return tiles > DRAG_FLAT_MIN; }
 // Workgroups of the cluster resolution for n particles: each takes at least
-// `lists` of the contact kernel's candidate lists and at most BLOCK; at most
-// `groups_max` workgroups unless more are needed for that.
+// `lists` runs of BLOCK candidates and at most BLOCK runs; at most `groups_max`
+// workgroups unless more are needed for that.
 int cluster_blocks(long long n, int lists = RC_LISTS, int groups_max = RC_GROUPS_MAX) {
   const long long nl = std::max(1ll, (long long)nblocks(n));
   const long long want = std::min((nl + lists - 1) / lists, (long long)groups_max);
   return (int)std::max(std::max(want, 1ll), (nl + BLOCK - 1) / BLOCK);
+}
+
+// The patches of cells of resolution pass `pass`.  A patch of the first pass
+// aims at PATCH_AIM particles with contacts, under the BLOCK its workgroup holds
+// at once: with discs of diameter d at density r, a share 1 - exp(-pi d^2 r) has
+// any.  Spheres over a bottom face lie about 2.4 times as dense as their mean
+// over the lattice.  Few are left for the later passes, whose patches are two
+// and four times as wide and high, their edges a half and a quarter of the
+// first ones' off.
+constexpr double PATCH_AIM = 210.0, PATCH_DENSE = 2.4;
+constexpr int PATCH_AREA_MIN = 16, PATCH_AREA_MAX = 1024;
+double patch_density(const lbdps_params &p, long long n) {  // particles per cell where they are
+  const bool even = p.bc[2] == BC_PERIODIC || p.particles_periodic_y;
+  return std::max((double)n, 1.0) / ((double)p.nx * p.ny) * (even ? 1.0 : PATCH_DENSE);
+}
+PatchGrid patch_grid(const lbdps_params &p, long long n, int pass) {
+  const double dens = patch_density(p, n);
+  const double touch = 1.0 - std::exp(-kPi * p.d_p * p.d_p * dens);
+  const double held = std::min(PATCH_AIM / std::max(touch, 1e-3), 0.94 * PATCH_HELD0);
+  const double area = std::min(std::max(held / dens, (double)PATCH_AREA_MIN), (double)PATCH_AREA_MAX);
+  PatchGrid g{};
+  const int tw = std::max(4, std::min(p.nx, (int)std::lround(std::sqrt(2.4 * area))));
+  const int th = std::max(4, std::min({p.ny, PATCH_ROWS, (int)(area / tw)}));
+  g.tw = tw << pass;
+  g.th = std::min(th << pass, PATCH_ROWS);
+  g.ox = pass ? tw / (2 * pass) : 0;
+  g.oy = pass ? th / (2 * pass) : 0;
+  g.ntx = (p.nx + g.ox + g.tw - 1) / g.tw;
+  g.nty = (p.ny + g.oy + g.th - 1) / g.th;
+  return g;
+}
+// Patch passes of a bed of n particles: none where the final workgroup holds
+// them all, else as many as leave it about PATCH_LEFT particles.  With kappa
+// contacts per particle, about a share 0.053 kappa of the particles with
+// contacts is left after one pass and 0.002 kappa^2.8 after two (0.04 and 0.001
+// measured at kappa 0.75, 0.09 and 0.007 at 1.6).
+constexpr double PATCH_LEFT = 2500.0;
+int patch_passes(const lbdps_params &p, long long n) {
+  if (n <= FINAL_CAP) return 0;
+  const double kappa = kPi * p.d_p * p.d_p * patch_density(p, n), touch = (1.0 - std::exp(-kappa)) * (double)n;
+  if (touch * 0.053 * kappa <= PATCH_LEFT && kappa < 1.6) return 1;  // from about there on contacts may percolate
+  return touch * 0.002 * std::pow(kappa, 2.8) <= PATCH_LEFT ? 2 : 3;
 }
 
 size_t pop_bytes(int prec) { return prec == PREC_FP64 ? 8 : (prec == PREC_FP32 ? 4 : 2); }
@@ -224,6 +267,7 @@ struct lbdps_ctx {
   long long step = 0;
   bool in_batch = false;  // owned by a batch: destroyed with it
   lbdps_tuning tune{RC_LISTS, RC_GROUPS_MAX, 0, 0};
+  int passes = 0;        // patch passes of the most recent collision stage (-1: it took the tile kernel)
   int sphere_tiles = 0;  // tiles of the tile kernel in the most recent collision stage (0: not used)
   int drag_blocks = 0;  // drag workgroups of the most recent step (its partial sums)
   int cluster_groups() const { return cluster_blocks(n, tune.cluster_lists, tune.cluster_groups_max); }
@@ -244,8 +288,15 @@ struct lbdps_ctx {
   int32_t *tile_sum = nullptr, *chunk_busy = nullptr, *need_sweep = nullptr;
   int tile_shift = 11;
   long long *roots = nullptr;
-  int32_t *rcount = nullptr;
+  // slots of the particles the patches left (done then holds their places), and
+  // what the final workgroup keeps when it works in memory (rank and perm are
+  // free in the collision stage)
+  int32_t *fin_state = nullptr;
+  int32_t *left() const { return (int32_t *)roots; }
+  FinalMem final_mem() const { return FinalMem{perm, fin_state, {rank, (int32_t *)roots + nmax}}; }
   long long *collc_part = nullptr, *wallc_part = nullptr;
+  // collisions and wall hits per patch of each pass, and of the final workgroup
+  int32_t *pcoll_part[PATCH_PASSES + 1]{}, *pwall_part[PATCH_PASSES + 1]{};
   long long *tile_part = nullptr;  // the tile kernel's pairs, collisions, wall hits and particles left, per tile
   int ntiles = 0;
   double *cons_pc = nullptr, *cons_pp = nullptr, *cons_out = nullptr;
@@ -319,8 +370,15 @@ size_t carve(const lbdps_params &p, long long nmax, char *base, lbdps_ctx *x) {
   const size_t ntiles = (C + ((size_t)1 << shift) - 1) >> shift;
   int32_t *tile_sum = cv.take<int32_t>(ntiles + 1);
   long long *roots = cv.take<long long>(nbN * BLOCK);
-  int32_t *rcount = cv.take<int32_t>(nbN);
-  int32_t *chunk_busy = cv.take<int32_t>(N / RES_CHUNK + 1), *need_sweep = cv.take<int32_t>(4);
+  int32_t *pcoll[PATCH_PASSES + 1], *pwall[PATCH_PASSES + 1];
+  for (int i = 0; i <= PATCH_PASSES; ++i) {  // a patch has at least 4 x 4 cells, twice that after the first pass
+    const size_t w = i == 0 ? 4 : 8;
+    const size_t np = i < PATCH_PASSES ? ((size_t)p.nx / w + 2) * ((size_t)p.ny / w + 2) : 1;
+    pcoll[i] = cv.take<int32_t>(np);
+    pwall[i] = cv.take<int32_t>(np);
+  }
+  int32_t *chunk_busy = cv.take<int32_t>(N / RES_CHUNK + 1), *need_sweep = cv.take<int32_t>(SW_COUNT);
+  int32_t *fin_state = cv.take<int32_t>(N);
   long long *collc_part = cv.take<long long>(nbN), *wallc_part = cv.take<long long>(nbN);
   size_t nst = 1;  // tiles of the sphere tile shape with the most of them
   for (int t = 1; t < SPHERE_TILES; ++t) {
@@ -386,10 +444,14 @@ size_t carve(const lbdps_params &p, long long nmax, char *base, lbdps_ctx *x) {
     x->tile_sum = tile_sum;
     x->tile_shift = shift;
     x->roots = roots;
-    x->rcount = rcount;
     x->chunk_busy = chunk_busy;
     x->need_sweep = need_sweep;
+    x->fin_state = fin_state;
     x->collc_part = collc_part;
+    for (int i = 0; i <= PATCH_PASSES; ++i) {
+      x->pcoll_part[i] = pcoll[i];
+      x->pwall_part[i] = pwall[i];
+    }
     x->tile_part = tile_part;
     x->wallc_part = wallc_part;
     x->ntiles = (int)ntiles;
@@ -439,7 +501,7 @@ void tstop(lbdps_ctx *x, int k) {
 // recorded around a launch also counts the queue's work between them, a few
 // microseconds).  extra: a further launch of the same phase.
 template <typename F, typename... Args>
-void tlaunch(lbdps_ctx *x, int k, bool extra, F kern, dim3 grid, Args... args) {
+void tlaunch_n(lbdps_ctx *x, int k, bool extra, F kern, dim3 grid, dim3 block, Args... args) {
   hipEvent_t a = nullptr, b = nullptr;
   if (x->timed >> k & 1u) {
     if (x->nmarks == x->marks.size()) {
@@ -455,9 +517,14 @@ void tlaunch(lbdps_ctx *x, int k, bool extra, F kern, dim3 grid, Args... args) {
     }
   }
   if (a)
-    hipExtLaunchKernelGGL(kern, grid, dim3(BLOCK), 0, x->stream, a, b, 0, args...);
+    hipExtLaunchKernelGGL(kern, grid, block, 0, x->stream, a, b, 0, args...);
   else
-    hipLaunchKernelGGL(kern, grid, dim3(BLOCK), 0, x->stream, args...);
+    hipLaunchKernelGGL(kern, grid, block, 0, x->stream, args...);
+}
+
+template <typename F, typename... Args>
+void tlaunch(lbdps_ctx *x, int k, bool extra, F kern, dim3 grid, Args... args) {
+  tlaunch_n(x, k, extra, kern, grid, dim3(BLOCK), args...);
 }
 
 lbdps_status check_hip(hipError_t e, const char *what) {
@@ -610,23 +677,33 @@ template <int P> struct Impl {
     const Consts<T> k = consts(x);
     const int st = x->tune.sphere_tile;
     x->sphere_tiles = st > 0 ? sphere_tiles(x, st) : 0;
+    x->passes = st > 0 ? -1 : patch_passes(x->p, x->n);
     if (st > 0) {
       tlaunch(x, LBDPS_K_CONTACTS, extra, tile_kernel(st), dim3(x->sphere_tiles), parts(x, x->cp),
               (const int32_t *)x->cs, k, x->adj(), x->deg, x->done, x->ticket, x->need_sweep, x->chunk_busy,
               x->roots, x->tile_part);
+      tlaunch(x, LBDPS_K_RESOLVE, extra, k_resolve_clusters<P>, dim3(x->cluster_groups()), parts(x, x->cp), x->adj(),
+              (const int32_t *)x->deg, x->done, k, x->need_sweep, x->collc_part, x->wallc_part,
+              (const long long *)x->roots, nblocks(N), (const int32_t *)x->need_sweep + SW_ROOTS);
+      tlaunch(x, LBDPS_K_RESOLVE, true, k_resolve<P>, dim3(resolve_blocks(x)), parts(x, x->cp),
+              (const int32_t *)x->slot, x->adj(), (const int32_t *)x->deg, x->done, x->ticket, k, x->flags,
+              x->coll_part, x->wall_part, x->chunk_busy, x->need_sweep);
     } else {
       tlaunch(x, LBDPS_K_CONTACTS, extra, nblocks(N) <= CONTACTS_SMALL_MAX ? k_contacts_small<P> : k_contacts<P>,
-              dim3(nblocks(N)), parts(x, x->cp), (const int32_t *)x->cs, k,
-              x->adj(), x->deg, x->done, x->ticket, x->flags, x->pair_part, x->wall0_part, x->chunk_busy,
-              x->need_sweep, x->roots, x->rcount);
+              dim3(nblocks(N)), parts(x, x->cp), (const int32_t *)x->cs, k, x->adj(), x->deg, x->flags, x->pair_part,
+              x->wall0_part, x->need_sweep);
+      for (int i = 0; i < x->passes; ++i) {
+        const PatchGrid g = patch_grid(x->p, x->n, i);
+        tlaunch(x, LBDPS_K_RESOLVE, extra || i > 0,
+                i == 0 ? k_patches<P, PATCH_HELD0, true> : k_patches<P, PATCH_HELD1, false>, dim3(g.count()),
+                parts(x, x->cp), (const int32_t *)x->cs, k, x->adj(), x->deg, g, (int)(i + 1 == x->passes),
+                x->left(), x->done, x->need_sweep + SW_LEFT, x->pcoll_part[i], x->pwall_part[i]);
+      }
+      tlaunch_n(x, LBDPS_K_RESOLVE, extra || x->passes > 0, k_final<P>, dim3(1), dim3(FINAL_THREADS),
+                parts(x, x->cp), k, x->adj(), x->deg, (int)(x->passes == 0), x->left(), x->done,
+                (const int32_t *)x->need_sweep + SW_LEFT, x->final_mem(), x->pcoll_part[PATCH_PASSES],
+                x->pwall_part[PATCH_PASSES]);
     }
-    tlaunch(x, LBDPS_K_RESOLVE, extra, k_resolve_clusters<P>, dim3(x->cluster_groups()), parts(x, x->cp), x->adj(),
-            (const int32_t *)x->deg, x->done, k, x->need_sweep, x->collc_part, x->wallc_part,
-            (const long long *)x->roots, (const int32_t *)x->rcount, nblocks(N),
-            st > 0 ? (const int32_t *)x->need_sweep + 1 : nullptr);
-    tlaunch(x, LBDPS_K_RESOLVE, true, k_resolve<P>, dim3(resolve_blocks(x)), parts(x, x->cp),
-            (const int32_t *)x->slot, x->adj(), (const int32_t *)x->deg, x->done, x->ticket, k, x->flags,
-            x->coll_part, x->wall_part, x->chunk_busy, x->need_sweep);
   }
 
   static lbdps_status step(lbdps_ctx *x, int nsteps) {
@@ -700,8 +777,8 @@ template <int P> struct Impl {
     const int N = (int)x->n;
     if (!x->bins_valid) rebin(x);
     hipLaunchKernelGGL((k_contacts<P, CT_ROWS>), dim3(nblocks(N)), dim3(BLOCK), 0, x->stream, parts(x, x->cp),
-                       (const int32_t *)x->cs, consts(x), x->adj(), x->deg, x->done, x->ticket, x->flags,
-                       x->pair_part, x->wall0_part, x->chunk_busy, x->need_sweep, x->roots, x->rcount);
+                       (const int32_t *)x->cs, consts(x), x->adj(), x->deg, x->flags, x->pair_part, x->wall0_part,
+                       x->need_sweep);
   }
 
   static lbdps_status set_state(lbdps_ctx *x, const double *d_f, const double *d_pos, const double *d_vel,
@@ -908,7 +985,7 @@ lbdps_status lbdps_create(const lbdps_params *p, int64_t max_particles, void *d_
   }
   hipLaunchKernelGGL(k_fill_i32, dim3(nblocks(x->C)), dim3(BLOCK), 0, x->stream, x->count, (long long)x->C, 0);
   hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(BLOCK), 0, x->stream, x->flags, (long long)FLAG_COUNT, 0);
-  hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(BLOCK), 0, x->stream, x->need_sweep, 4ll, 0);
+  hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(BLOCK), 0, x->stream, x->need_sweep, (long long)SW_COUNT, 0);
   hipLaunchKernelGGL(k_fill_i32, dim3(nblocks(x->nmax / RES_CHUNK + 1)), dim3(BLOCK), 0, x->stream, x->chunk_busy,
                      (long long)(x->nmax / RES_CHUNK + 1), 0);
   hipLaunchKernelGGL(k_fill_i32, dim3(nblocks(x->ntiles + 1)), dim3(BLOCK), 0, x->stream, x->tile_sum,
@@ -1218,21 +1295,34 @@ lbdps_status lbdps_counters(lbdps_ctx *x, int64_t h_out[4]) {
   lbdps_status st = sync_and_check(x, "lbdps_counters");
   if (st != LBDPS_OK) return st;
   const int nbN = nblocks(x->n), nbC = x->drag_blocks;
-  std::vector<long long> buf((size_t)std::max(nbN, nbC) + 1);
   // contacts: one partial per workgroup of the contact kernel; collisions and
-  // wall hits of the resolution kernel: one per workgroup of that kernel
-  long long *src[6] = {x->pair_part, x->coll_part, x->wall_part, x->wall0_part, x->collc_part, x->wallc_part};
-  const int dst[6] = {0, 1, 2, 2, 1, 2};
-  const int nres = Impl<PREC_FP32>::resolve_blocks(x);
-  const int ncl = x->cluster_groups();
-  const int len[6] = {nbN, nres, nres, nbN, ncl, ncl};
+  // wall hits of the resolution kernels: one per workgroup of each
+  const bool tile = x->passes < 0;  // the tile kernel counts its own contacts
+  long long *src[6] = {x->pair_part, x->wall0_part, x->collc_part, x->wallc_part, x->coll_part, x->wall_part};
+  const int dst[6] = {0, 2, 1, 2, 1, 2};
+  const int nres = tile ? Impl<PREC_FP32>::resolve_blocks(x) : 0, ncl = tile ? x->cluster_groups() : 0;
+  const int nct = tile ? 0 : nbN;
+  const int len[6] = {nct, nct, ncl, ncl, nres, nres};
+  std::vector<long long> buf((size_t)std::max({nbN, nbC, ncl, nres}) + 1);
   for (int j = 0; j < 4; ++j) h_out[j] = 0;
   if (x->n > 0)
     for (int j = 0; j < 6; ++j) {
-      if (x->sphere_tiles > 0 && (j == 0 || j == 3)) continue;  // the tile kernel counts these
+      if (len[j] == 0) continue;
       st = check_hip(hipMemcpy(buf.data(), src[j], (size_t)len[j] * 8, hipMemcpyDeviceToHost), "lbdps_counters");
       if (st != LBDPS_OK) return st;
       for (int b = 0; b < len[j]; ++b) h_out[dst[j]] += buf[b];
+    }
+  if (x->n > 0 && !tile)  // the patch passes and the final workgroup
+    for (int i = 0; i <= PATCH_PASSES; ++i) {
+      if (i >= x->passes && i < PATCH_PASSES) continue;
+      const int np = i < PATCH_PASSES ? patch_grid(x->p, x->n, i).count() : 1;
+      std::vector<int32_t> pb((size_t)np);
+      for (int j = 0; j < 2; ++j) {
+        st = check_hip(hipMemcpy(pb.data(), j ? x->pwall_part[i] : x->pcoll_part[i], (size_t)np * 4,
+                                 hipMemcpyDeviceToHost), "lbdps_counters");
+        if (st != LBDPS_OK) return st;
+        for (int32_t v : pb) h_out[1 + j] += v;
+      }
     }
   // the tile kernel's pairs, collisions and wall hits of the particles it resolved
   const int nst = x->n > 0 ? x->sphere_tiles : 0;
@@ -1494,24 +1584,23 @@ template <int P> struct BatchImpl {
     a.slot = x->slot;
     a.flags = x->flags;
     a.deg = x->deg;
-    a.done = x->done;
-    a.ticket = x->ticket;
-    a.chunk_busy = x->chunk_busy;
-    a.need_sweep = x->need_sweep;
-    a.roots = x->roots;
-    a.rcount = x->rcount;
+    a.sweep = x->need_sweep;
+    a.left = x->left();
+    a.place_of = x->done;
+    a.fin = x->final_mem();
     a.adj = x->adj();
     a.pair_part = x->pair_part;
     a.wall0_part = x->wall0_part;
-    a.coll_part = x->coll_part;
-    a.wall_part = x->wall_part;
-    a.collc_part = x->collc_part;
-    a.wallc_part = x->wallc_part;
     a.ts = I::tiles(x);
     a.cf = x->cf;
     a.cp = x->cp;
     a.cp_moves = x->n > 0;
-    a.nlists = nblocks(x->n);
+    a.npass = patch_passes(x->p, x->n);
+    for (int i = 0; i <= PATCH_PASSES; ++i) {
+      if (i < PATCH_PASSES) a.pg[i] = patch_grid(x->p, x->n, i);
+      a.pcoll_part[i] = x->pcoll_part[i];
+      a.pwall_part[i] = x->pwall_part[i];
+    }
     return a;
   }
 
@@ -1525,8 +1614,9 @@ template <int P> struct BatchImpl {
     nb[PH_SCAN] = x->ntiles;
     nb[PH_SCATTER] = nblocks(x->n);
     nb[PH_CONTACTS] = nblocks(x->n);
-    nb[PH_CLUSTERS] = x->cluster_groups();
-    nb[PH_RESOLVE] = I::resolve_blocks(x);
+    const int np = patch_passes(x->p, x->n);
+    for (int i = 0; i < np; ++i) nb[PH_PATCH0 + i] = patch_grid(x->p, x->n, i).count();
+    nb[PH_FINAL] = 1;
   }
 
   // Fills table t (0 eager, 1 graph) from the beds' current state.
@@ -1575,7 +1665,7 @@ template <int P> struct BatchImpl {
       case PH_SCAN: return LBDPS_K_SCAN;
       case PH_SCATTER: return LBDPS_K_SCATTER;
       case PH_CONTACTS: return LBDPS_K_CONTACTS;
-      default: return LBDPS_K_RESOLVE;  // the cluster kernel and the ordered sweep
+      default: return LBDPS_K_RESOLVE;  // the patch passes and the final workgroup
     }
   }
   // Events for a timed launch of kernel class k in an eager batched step,
@@ -1604,15 +1694,17 @@ template <int P> struct BatchImpl {
     const bool timing = t == 0;  // never inside a captured graph
     for (int it = 0; it < nsteps; ++it) {
       const int flip = it & 1;
-#define LBDPS_LAUNCH(kern, ph)                                                                                      \
+#define LBDPS_LAUNCH_N(kern, ph, threads, extra, ...)                                                                \
   if (tot[ph] > 0) {                                                                                                \
     hipEvent_t ea = nullptr, eb = nullptr;                                                                          \
-    if (timing && bmark(B, phase_kernel(ph), ph == PH_RESOLVE, ea, eb))                                             \
-      hipExtLaunchKernelGGL(kern, dim3(tot[ph]), dim3(BLOCK), 0, B->stream, ea, eb, 0, tab, off + (ph) * nb1,       \
-                            nbeds, flip);                                                                           \
+    if (timing && bmark(B, phase_kernel(ph), extra, ea, eb))                                                        \
+      hipExtLaunchKernelGGL(kern, dim3(tot[ph]), dim3(threads), 0, B->stream, ea, eb, 0, tab, off + (ph) * nb1,     \
+                            nbeds, flip, ##__VA_ARGS__);                                                            \
     else                                                                                                            \
-      hipLaunchKernelGGL(kern, dim3(tot[ph]), dim3(BLOCK), 0, B->stream, tab, off + (ph) * nb1, nbeds, flip);       \
+      hipLaunchKernelGGL(kern, dim3(tot[ph]), dim3(threads), 0, B->stream, tab, off + (ph) * nb1, nbeds, flip,      \
+                         ##__VA_ARGS__);                                                                            \
   }
+#define LBDPS_LAUNCH(kern, ph) LBDPS_LAUNCH_N(kern, ph, BLOCK, false)
       LBDPS_LAUNCH(kb_collide<P>, PH_COLLIDE)
       const bool flat = drag_flat(tot[PH_DRAG]);
       switch (B->tile[t]) {
@@ -1628,15 +1720,20 @@ template <int P> struct BatchImpl {
       LBDPS_LAUNCH(kb_scan<P>, PH_SCAN)
       LBDPS_LAUNCH(kb_scatter<P>, PH_SCATTER)
       LBDPS_LAUNCH(kb_contacts<P>, PH_CONTACTS)
-      LBDPS_LAUNCH(kb_clusters<P>, PH_CLUSTERS)
-      LBDPS_LAUNCH(kb_resolve<P>, PH_RESOLVE)
+      // the final workgroups always run: they are the resolution launch that counts
+      LBDPS_LAUNCH_N((kb_patches<P, PATCH_HELD0, true>), PH_PATCH0, BLOCK, true, 0)
+      LBDPS_LAUNCH_N((kb_patches<P, PATCH_HELD1, false>), PH_PATCH1, BLOCK, true, 1)
+      LBDPS_LAUNCH_N((kb_patches<P, PATCH_HELD1, false>), PH_PATCH2, BLOCK, true, 2)
+      LBDPS_LAUNCH_N(kb_final<P>, PH_FINAL, FINAL_THREADS, false)
+#undef LBDPS_LAUNCH_N
 #undef LBDPS_LAUNCH
     }
   }
 
   static void advance(lbdps_batch *B, int nsteps) {
     for (auto *x : B->beds) {
-      x->sphere_tiles = 0;  // the batched collision stage is the row path
+      x->sphere_tiles = 0;  // the batched collision stage takes the patches
+      if (x->n > 0) x->passes = patch_passes(x->p, x->n);
       x->cf ^= nsteps & 1;
       if (x->n > 0) x->cp ^= nsteps & 1;
       x->step += nsteps;

@@ -1,0 +1,90 @@
+"""The collision stage's patches and final workgroup (patches.hpp) at the sizes
+where they change course, against the oracle's sequential lexicographic sweep
+and wall pass: velocities, pair counts, collisions and wall hits equal bit for
+bit, in FP64 and (float-defined stage) in FP32.  No tolerance: the order of each
+particle's pairs fixes the arithmetic."""
+import numpy as np
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+L = pytest.importorskip("paper_1303_2653_amd.lbdps")
+import oracle  # noqa: E402
+
+PER, WALLED = ("periodic",) * 4, ("wall",) * 4
+RISER, BED = ("wall", "wall", "periodic", "periodic"), ("periodic", "periodic", "inlet", "outlet")
+
+
+def grid(x0, y0, k, spacing):
+    g = np.arange(k) * spacing
+    return np.stack(np.meshgrid(x0 + g, y0 + g), axis=-1).reshape(-1, 2)
+
+
+def bed(name):
+    t = synth.tiny
+    if name == "whole-4096":  # the most the final workgroup takes alone
+        return t(nx=60, ny=61, n=4096, seed=3, bc=WALLED)
+    if name == "patches-4097":  # one more: patches
+        return t(nx=61, ny=60, n=4097, seed=4, bc=RISER)
+    if name == "one-pass":
+        return t(nx=101, ny=97, n=9000, seed=5, bc=PER)
+    if name == "two-passes":
+        return t(nx=317, ny=203, n=70_000, seed=6, bc=BED, band=150)
+    if name == "three-passes":
+        return t(nx=640, ny=509, n=500_000, seed=7, bc=PER)
+    if name == "narrow":  # patches as wide as the lattice: pairs across the periodic seam
+        return t(nx=5, ny=3000, n=9000, seed=8, bc=PER)
+    if name == "flat":
+        return t(nx=2500, ny=4, n=9001, seed=9, bc=RISER)
+    if name == "percolating":  # more left than the final workgroup holds in LDS
+        return t(nx=50, ny=60, n=14_000, seed=10, bc=BED, band=60)
+    if name == "crowded-rows":  # one row of a patch holds more than its workgroup takes
+        cfg = t(nx=64, ny=64, n=5000, seed=11, bc=WALLED, d=0.05)
+        u = synth.uniform(12, 2 * 6000).reshape(-1, 2)
+        cfg["pos"] = np.concatenate([cfg["pos"], np.stack([20.0 + 4.0 * u[:, 0], 30.0 + 2.0 * u[:, 1]], 1)])
+        return cfg
+    if name == "many-partners":  # up to 14 partners each, over patch edges
+        cfg = t(nx=64, ny=64, n=5000, seed=13, bc=RISER)
+        extra = np.concatenate([grid(x, y, 4, 0.21) for x in (6.1, 20.3, 35.7, 47.9) for y in (5.2, 17.4, 38.9, 62.1)])
+        keep = np.min(np.hypot(*(cfg["pos"][:, None, :] - extra[None]).transpose(2, 0, 1)), axis=1) > 0.5
+        cfg["pos"] = np.concatenate([cfg["pos"][keep], extra])
+        return cfg
+    raise KeyError(name)
+
+
+BEDS = ("whole-4096", "patches-4097", "one-pass", "two-passes", "three-passes", "narrow", "flat", "percolating",
+        "crowded-rows", "many-partners")
+
+
+@pytest.mark.parametrize("name", BEDS)
+def test_collision_stage(name):
+    cfg = bed(name)
+    n = len(cfg["pos"])
+    print("bed", name, "particles", n, flush=True)
+    rng = np.random.default_rng(31)
+    cell = np.floor(cfg["pos"]).astype(np.int32)
+    off = np.minimum((cfg["pos"] - cell).astype(np.float32), np.float32(0.99999994))
+    pos = cell.astype(np.float64) + off  # held exactly in FP32 as well
+    vel = ((rng.random((n, 2)) - 0.5) * 2e-2).astype(np.float32).astype(np.float64)
+    cfg = dict(cfg, pos=pos, vel=vel)
+    p = oracle.make_params(cfg)
+
+    pairs = oracle.contacts(p, pos)
+    v64, nc = oracle.resolve(p, pos, vel, pairs)
+    v64, nw = oracle.walls(p, pos, v64)
+    pairs32, v32, nc32, nw32 = oracle.collide_f32(p, cell, off, vel.astype(np.float32))
+    for prec, ref, want in (("fp64", v64, (len(pairs), nc, nw)), ("fp32", v32, (len(pairs32), nc32, nw32))):
+        gpu = L.Sim(cfg, precision=prec)
+        for again in range(2):  # the second time on the state as it was: nothing is left over from the first
+            gpu.set_state(None, pos, vel)
+            gpu.collide_particles()
+            got = gpu.particles()["vel"]
+            c = gpu.counters()
+            assert (c["pairs"], c["collisions"], c["walls"]) == want, (name, prec, again, c, want)
+            assert np.array_equal(got, ref.astype(np.float64)), (name, prec, again)
+        gpu.close()
