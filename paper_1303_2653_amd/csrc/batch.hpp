@@ -104,7 +104,8 @@ template <int P>
 __global__ __launch_bounds__(BLOCK) LBDPS_WAVES8 void kb_contacts(const BedArgs<P> *__restrict__ tab, const int *__restrict__ off,
                                                      int nbeds, int flip) {
   LBDPS_BED_PROLOGUE(XCD_RUN_CONTACTS)
-  contacts_body<P>(bid, nbk, a.parts(1 - cp), a.cs, a.k, a.adj, a.deg, a.flags, a.pair_part, a.wall0_part, a.sweep);
+  (void)nbk;
+  contacts_body<P>(bid, a.parts(1 - cp), a.cs, a.k, a.adj, a.deg, a.flags, a.pair_part, a.wall0_part, a.sweep);
 }
 
 template <int P, int HELD, bool FIRST>

@@ -319,8 +319,6 @@ constexpr int RANK_MOVED = 1 << 30;           // rank flag: the particle arrived
 constexpr int SEG_REG = 4;                    // cell segments up to this length stay in registers
 constexpr int CONTACT_REG = 4;                // contacts per particle collected in registers first
 constexpr int CONTACT_CH = 4;                 // candidate positions loaded together
-constexpr int CONTACT_W = 2;                  // slots each side of a particle loaded before its cell starts
-constexpr int CONTACT_W_SMALL = 3;            // the same for grids that fit on the chip at six waves per SIMD
 constexpr int RES_ITEMS = 8;                  // particle indices per lane and resolution chunk
 // done[] of a particle whose whole cluster the cluster kernel resolved (its
 // pairs and its wall pass): the ordered sweep leaves it alone.  A particle of
@@ -1360,257 +1358,187 @@ __global__ __launch_bounds__(BLOCK) void k_scatter(Parts<T> src, Parts<T> dst, c
 // One thread per particle slot.  Candidates come from the 3x3 cells around the
 // particle (d < 1 cell), narrowed to the columns and rows that come within d
 // of it; a contact is a centre distance <= d (Sec. 2.2), with the periodic
-// minimum image.  Away from a periodic seam the cells of a neighbour row are
-// one contiguous slot range, and a candidate's column offset follows from the
-// cell starts.  Each particle keeps its full neighbour list
-// sorted by particle index, as 64-bit entries (index << 32 | slot).  A particle
-// without contacts gets its wall collision here; the others get it after their
-// binary collisions.
+// minimum image.  The cells of one row are one slot range, and a candidate's
+// column offset follows from the cell starts; a cell across the periodic seam
+// is a range of its own.  Each particle keeps its full neighbour list sorted by
+// particle index.  A particle without contacts gets its wall collision here;
+// the others get it after their binary collisions.
+//
+// The kernel is bound by instruction issue (a particle has 4 candidates on
+// average, its wavefront's busiest lane 10), so a candidate costs its two
+// coordinate loads, the test and one bit of a mask; the few set bits are
+// turned into slots afterwards, and the indices of up to CONTACT_REG contacts
+// are loaded together and ordered by a sorting network.  A 2 M-sphere riser in
+// FP32: 50 us, against 60 us with the index loaded and an ordered insertion
+// made per candidate.
 // MODE: CT_ALL, the collision stage's contacts; CT_ROWS, the rows and degrees
-// of every particle and nothing else (no wall pass, marks, counters or flags),
-// for the pair listing.
+// of every particle and nothing else (no wall pass, counters or flags), for
+// the pair listing.
 constexpr int CT_ALL = 0, CT_ROWS = 2;
-template <int P, int W = CONTACT_W, int MODE = CT_ALL>
-__device__ __forceinline__ void contacts_body(const int bidx, const int gdim, Parts<typename Prec<P>::T> pt,
-    const int32_t *__restrict__ cs, Consts<typename Prec<P>::T> k, Adj adj, int32_t *__restrict__ deg,
+template <int P, int MODE = CT_ALL>
+__device__ __forceinline__ void contacts_body(const int bidx, Parts<typename Prec<P>::T> pt,
+    const int32_t *__restrict__ cs, const Consts<typename Prec<P>::T> &k, Adj adj, int32_t *__restrict__ deg,
     int32_t *flags, long long *pair_part, long long *wall_part, int32_t *sweep) {
   using T = typename Prec<P>::T;
   __shared__ long long sh[BLOCK / 64];
   const int s = bidx * BLOCK + threadIdx.x;
-  long long fwd = 0, nwall = 0;
-  bool by_wall_pass = true;
+  long long nwall = 0;
+  int fwd = 0;
   if (MODE != CT_ROWS && s == 0) sweep[SW_LEFT] = 0;
   if (s < k.npart) {
-    const int key = pt.key[s];
-    const int id = pt.pid[s];
-    const T x = pt.px[s], y = pt.py[s];
+    const int key = ldu(pt.key, s);
+    const int id = ldu(pt.pid, s);
+    const T x = ldu(pt.px, s), y = ldu(pt.py, s);
     int cx, cy;
     cell_xy(k, key, cx, cy);
-    // velocity for the wall pass of a contact-free particle: only a particle in a
-    // cell next to a wall can need it
-    const bool by_wall = (!k.per_x && (cx == 0 || cx == k.nx - 1)) || (!k.per_y && (cy == 0 || cy == k.ny - 1));
-    T vx0 = (T)0, vy0 = (T)0;
-    if (by_wall) {
-      vx0 = pt.vx[s];
-      vy0 = pt.vy[s];
-    }
-    const T dd = k.d * k.d;
-    const AdjRow row = adj.row(s);
-    // The particle's own row of cells (its cell and the cells left and right of
-    // it) is one slot range around s, so the W slots on each side are
-    // loaded now, before the cell starts arrive; the ones inside the row's
-    // range are tested from registers.
-    T wx[2 * W], wy[2 * W];
-    int wid[2 * W];
-#pragma unroll
-    for (int j = 0; j < 2 * W; ++j) {
-      const int t = min(max(j < W ? s - W + j : s + 1 + (j - W), 0), k.npart - 1);
-      wx[j] = ldu(pt.px, t);
-      wy[j] = ldu(pt.py, t);
-      wid[j] = ldu(pt.pid, t);
-    }
-    // Pass 1 keeps the first CONTACT_REG contacts sorted in registers (no
-    // stores while scanning, so candidate loads overlap); a particle with more
-    // contacts is scanned again and its list built in memory.
-    long long r[CONTACT_REG];
-    int cnt = 0;
-    bool over = false;
-    // candidate ranges: the three cells of each neighbour row are one slot
-    // range away from a periodic seam; the column offset of a candidate follows
-    // from the cell starts.  All starts are loaded first.
-    const bool inner_x = cx >= 1 && cx + 1 < k.nx;
     // A partner lies within d of the particle, so only the columns and rows of
     // cells that come within d of its position can hold one: with d <= 1/2
     // two of the three in each direction.  The margin keeps every candidate
     // whose rounded distance test could pass (rounding of a separation is
     // below 1e-6 at any lattice size the library accepts).
     const T fx = Pos<P>::G ? x - (T)cx : x, fy = Pos<P>::G ? y - (T)cy : y;  // position in the cell
-    const T margin = (T)1e-5;
+    const T margin = (T)1e-5, dd = k.d * k.d;
     const bool use_l = fx < k.d + margin, use_r = fx > (T)1 - k.d - margin;
-    const bool use_b = fy < k.d + margin, use_t = fy > (T)1 - k.d - margin;
-    int rlo[3], rm1[3], rm2[3], rhi[3];
+    const bool use_b = fy < k.d + margin && (cy > 0 || k.per_y), use_t = fy > (T)1 - k.d - margin && (cy + 1 < k.ny || k.per_y);
+    const int left = use_l && cx > 0, right = use_r && cx + 1 < k.nx;
+    const int row0 = key - cx;
+    const int row_b = cy > 0 ? row0 - k.nx : row0 + (k.ny - 1) * k.nx;
+    const int row_t = cy + 1 < k.ny ? row0 + k.nx : row0 - (k.ny - 1) * k.nx;
+    // The slot ranges of the own row, and of the row below or above, with the
+    // ends of the column left of the particle's (m1) and of its own (m2).
+    struct Range {
+      int lo, m1, m2, hi;
+    };
+    auto range = [&](int row) {
+      Range r;
+      r.m1 = ldu(cs, row + cx);
+      r.m2 = ldu(cs, row + cx + 1);
+      r.lo = left ? ldu(cs, row + cx - 1) : r.m1;
+      r.hi = right ? ldu(cs, row + cx + 2) : r.m2;
+      return r;
+    };
+    const bool other = use_b || use_t, seam = k.per_x && ((use_l && cx == 0) || (use_r && cx + 1 == k.nx));
+    const int dy1 = use_b ? -1 : 1;
+    const Range r0 = range(row0), r1 = other ? range(use_b ? row_b : row_t) : Range{0, 0, 0, 0};
+    // Calls f(range, dy) for each range of candidates.
+    auto ranges = [&](auto &&f) {
+      f(r0, 0);
+      if (other) f(r1, dy1);
+      if (use_b && use_t) f(range(row_t), 1);  // d near 1/2 and above
+      if (seam) {
+        const int c = cx == 0 ? k.nx - 1 : 0;
+        for (int dy = -1; dy <= 1; ++dy) {
+          if ((dy < 0 && !use_b) || (dy > 0 && !use_t)) continue;
+          const int row = dy < 0 ? row_b : (dy > 0 ? row_t : row0);
+          const int lo = ldu(cs, row + c), hi = ldu(cs, row + c + 1);
+          f(cx == 0 ? Range{lo, hi, hi, hi} : Range{lo, lo, lo, hi}, dy);
+        }
+      }
+    };
+    auto touches = [&](int t, const Range &r, int dy, T xb, T yb) {
+      T dx, dyy;
+      if constexpr (Pos<P>::G) {
+        Pos<P>::sep(k, 0, x, y, 0, xb, yb, dx, dyy);
+      } else {  // the cell difference, then the offsets
+        dx = (t < r.m1 ? (T)1 : (t < r.m2 ? (T)0 : (T)-1)) + (x - xb);
+        dyy = (T)-dy + (y - yb);
+      }
+      return dx * dx + dyy * dyy <= dd;
+    };
+    // First look: the contacts' slots, with their row offsets, in registers.
+    int e[CONTACT_REG], cnt = 0;
 #pragma unroll
-    for (int rw = 0; rw < 3; ++rw) {
-      int yy = cy + rw - 1;
-      bool ok = rw == 0 ? use_b : (rw == 2 ? use_t : true);
-      if (yy < 0 || yy >= k.ny) {
-        ok = ok && k.per_y != 0;
-        yy = wrap_i(yy, k.ny);
-      }
-      const int c0 = yy * k.nx + cx - 1;
-      if (ok && inner_x) {
-        rm1[rw] = ldu(cs, c0 + 1);
-        rm2[rw] = ldu(cs, c0 + 2);
-        rlo[rw] = use_l ? ldu(cs, c0) : rm1[rw];
-        rhi[rw] = use_r ? ldu(cs, c0 + 3) : rm2[rw];
-      } else {  // a row not needed or beyond a wall (empty), or a seam column walked cell by cell below
-        rlo[rw] = rm1[rw] = rm2[rw] = rhi[rw] = 0;
-      }
-    }
-    auto scan = [&](auto &&hit) {
-      auto test = [&](int t, int ox, int oy) {
-        if (t == s) return;
-        T dx, dy;
-        Pos<P>::sep_nb(k, ox, oy, x, y, pt.px[t], pt.py[t], dx, dy);
-        if (dx * dx + dy * dy <= dd) hit(t, pt.pid[t], oy);
-      };
-      if (inner_x) {
-        // one flattened pass over the three rows' ranges, CONTACT_CH candidates
-        // at a time: their positions and indices are all loaded before any is
-        // tested.  Candidate q of the flattened range is slot q + sh_r in row r.
-        const int n0 = rhi[0] - rlo[0], n01 = n0 + rhi[1] - rlo[1];
-        const int tot = n01 + rhi[2] - rlo[2];  // >= 1: the particle's own cell
-        const int sh0 = rlo[0], sh1 = rlo[1] - n0, sh2 = rlo[2] - n01;
-        // column boundaries as plain values (selected per candidate, not indexed)
-        const int a0 = rm1[0], a1 = rm1[1], a2 = rm1[2], b0 = rm2[0], b1 = rm2[1], b2 = rm2[2];
-        for (int q0 = 0; q0 < tot; q0 += CONTACT_CH) {
-          int tt[CONTACT_CH], ox[CONTACT_CH], oy[CONTACT_CH], ids[CONTACT_CH];
+    for (int u = 0; u < CONTACT_REG; ++u) e[u] = 0;
+    ranges([&](const Range &r, int dy) {
+      for (int b = r.lo; b < r.hi; b += 32) {
+        const int n = min(r.hi - b, 32);
+        unsigned hits = 0;
+        for (int q0 = 0; q0 < n; q0 += CONTACT_CH) {
           T xs[CONTACT_CH], ys[CONTACT_CH];
 #pragma unroll
           for (int j = 0; j < CONTACT_CH; ++j) {
-            const int q = min(q0 + j, tot - 1);  // past the end: repeat the last candidate
-            const bool r0 = q < n0, r1 = q < n01;
-            const int t = q + (r0 ? sh0 : (r1 ? sh1 : sh2));
-            const int m1 = r0 ? a0 : (r1 ? a1 : a2), m2 = r0 ? b0 : (r1 ? b1 : b2);
-            tt[j] = t;
-            ox[j] = t < m1 ? -1 : (t < m2 ? 0 : 1);
-            oy[j] = r0 ? -1 : (r1 ? 0 : 1);
+            const int t = b + min(q0 + j, n - 1);
             xs[j] = ldu(pt.px, t);
             ys[j] = ldu(pt.py, t);
-            ids[j] = ldu(pt.pid, t);
           }
 #pragma unroll
-          for (int j = 0; j < CONTACT_CH; ++j) {
-            if (q0 + j < tot && tt[j] != s) {
-              T dx, dy;
-              Pos<P>::sep_nb(k, ox[j], oy[j], x, y, xs[j], ys[j], dx, dy);
-              if (dx * dx + dy * dy <= dd) hit(tt[j], ids[j], oy[j]);
-            }
-          }
+          for (int j = 0; j < CONTACT_CH; ++j)
+            if (touches(b + q0 + j, r, dy, xs[j], ys[j]) && q0 + j < n) hits |= 1u << (q0 + j);
         }
-      } else {
-        for (int oy = -1; oy <= 1; ++oy) {
-          int yy = cy + oy;
-          if (yy < 0 || yy >= k.ny) {
-            if (!k.per_y) continue;
-            yy = wrap_i(yy, k.ny);
-          }
-          const int rb = yy * k.nx;
-          for (int ox = -1; ox <= 1; ++ox) {
-            int xx = cx + ox;
-            if (xx < 0 || xx >= k.nx) {
-              if (!k.per_x) continue;
-              xx = wrap_i(xx, k.nx);
-            }
-            const int c = rb + xx;
-            for (int t = cs[c]; t < cs[c + 1]; ++t) test(t, ox, oy);
-          }
-        }
-      }
-    };
-    // Pass 1 over a row of cells away from a periodic seam: the window slots
-    // inside the own row's range from registers, then the rest of the three
-    // ranges (row below, own row left and right of the window, row above),
-    // CONTACT_CH candidates at a time.
-    auto first_scan = [&](auto &&hit) {
-      if (!inner_x) {
-        scan(hit);
-        return;
-      }
-      const int lo1 = rlo[1], hi1 = rhi[1], a1 = rm1[1], b1 = rm2[1];
+        if (dy == 0 && s >= b && s < b + n) hits &= ~(1u << (s - b));
+        for (; hits; hits &= hits - 1) {
 #pragma unroll
-      for (int j = 0; j < 2 * W; ++j) {
-        const int t = j < W ? s - W + j : s + 1 + (j - W);
-        if (t >= lo1 && t < hi1) {
-          T dx, dy;
-          Pos<P>::sep_nb(k, t < a1 ? -1 : (t < b1 ? 0 : 1), 0, x, y, wx[j], wy[j], dx, dy);
-          if (dx * dx + dy * dy <= dd) hit(t, wid[j], 0);
+          for (int u = CONTACT_REG - 1; u > 0; --u) e[u] = e[u - 1];
+          e[0] = (b + __builtin_ctz(hits)) | (dy + 1) << 29;
+          ++cnt;
         }
       }
-      const int mlo = max(lo1, s + W + 1);
-      const int n0 = rhi[0] - rlo[0], n1 = n0 + max(0, min(hi1, s - W) - lo1);
-      const int n2 = n1 + max(0, hi1 - mlo), tot = n2 + rhi[2] - rlo[2];
-      const int sh0 = rlo[0], sh1 = lo1 - n0, sh2 = mlo - n1, sh3 = rlo[2] - n2;
-      const int a0 = rm1[0], a2 = rm1[2], b0 = rm2[0], b2 = rm2[2];
-      for (int q0 = 0; q0 < tot; q0 += CONTACT_CH) {
-        int tt[CONTACT_CH], ox[CONTACT_CH], oy[CONTACT_CH], ids[CONTACT_CH];
-        T xs[CONTACT_CH], ys[CONTACT_CH];
-#pragma unroll
-        for (int j = 0; j < CONTACT_CH; ++j) {
-          const int q = min(q0 + j, tot - 1);  // past the end: repeat the last candidate
-          const bool r0 = q < n0, r1 = q < n1, r2 = q < n2;
-          const int t = q + (r0 ? sh0 : (r1 ? sh1 : (r2 ? sh2 : sh3)));
-          const int m1 = r0 ? a0 : (r2 ? a1 : a2), m2 = r0 ? b0 : (r2 ? b1 : b2);
-          tt[j] = t;
-          ox[j] = t < m1 ? -1 : (t < m2 ? 0 : 1);
-          oy[j] = r0 ? -1 : (r2 ? 0 : 1);
-          xs[j] = ldu(pt.px, t);
-          ys[j] = ldu(pt.py, t);
-          ids[j] = ldu(pt.pid, t);
-        }
-#pragma unroll
-        for (int j = 0; j < CONTACT_CH; ++j) {
-          if (q0 + j < tot) {
-            T dx, dy;
-            Pos<P>::sep_nb(k, ox[j], oy[j], x, y, xs[j], ys[j], dx, dy);
-            if (dx * dx + dy * dy <= dd) hit(tt[j], ids[j], oy[j]);
-          }
-        }
-      }
-    };
-    first_scan([&](int t, int tid, int dy) {
-      if (tid > id) ++fwd;
-      if (cnt < CONTACT_REG) {
-        const long long e = adj_entry(tid, t, dy);
-        bool placed = false;
-#pragma unroll
-        for (int u = CONTACT_REG - 1; u >= 0; --u)
-          if (!placed && u <= cnt) {
-            if (u > 0 && r[u - 1] > e) {
-              r[u] = r[u - 1];
-            } else {
-              r[u] = e;
-              placed = true;
-            }
-          }
-      }
-      ++cnt;
     });
+    const AdjRow row = adj.row(s);
+    bool over = false;
     if (cnt <= CONTACT_REG) {
+      static_assert(CONTACT_REG == 4, "the network orders four");
+      int ids[CONTACT_REG];
+#pragma unroll
+      for (int u = 0; u < CONTACT_REG; ++u) {
+        ids[u] = u < cnt ? ldu(pt.pid, e[u] & 0x1fffffff) : 0x7fffffff;
+        fwd += u < cnt && ids[u] > id;
+      }
+      auto order = [&](int a, int c) {
+        if (ids[a] > ids[c]) {
+          const int t = ids[a], v = e[a];
+          ids[a] = ids[c];
+          e[a] = e[c];
+          ids[c] = t;
+          e[c] = v;
+        }
+      };
+      if (cnt > 1) {
+        order(0, 1);
+        order(2, 3);
+        order(0, 2);
+        order(1, 3);
+        order(1, 2);
+      }
 #pragma unroll
       for (int u = 0; u < CONTACT_REG; ++u)
-        if (u < cnt) row[u] = r[u];
-    } else {
+        if (u < cnt) row[u] = ((long long)ids[u] << 32) | (unsigned)e[u];
+    } else {  // more: the list is built in memory
       int m = 0;
-      scan([&](int t, int tid, int dy) {
-        if (m == KMAX) {
-          over = true;
-          return;
+      ranges([&](const Range &r, int dy) {
+        for (int t = r.lo; t < r.hi; ++t) {
+          if (t == s || !touches(t, r, dy, ldu(pt.px, t), ldu(pt.py, t))) continue;
+          const int tid = ldu(pt.pid, t);
+          fwd += tid > id;
+          if (m == KMAX) {
+            over = true;
+            continue;
+          }
+          const long long v = adj_entry(tid, t, dy);
+          int j = m;
+          while (j > 0 && row[j - 1] > v) {
+            row[j] = row[j - 1];
+            --j;
+          }
+          row[j] = v;
+          ++m;
         }
-        const long long e = adj_entry(tid, t, dy);
-        int j = m;
-        while (j > 0 && row[j - 1] > e) {
-          row[j] = row[j - 1];
-          --j;
-        }
-        row[j] = e;
-        ++m;
       });
       cnt = m;
     }
     deg[s] = cnt;
-    if constexpr (MODE == CT_ROWS) {
-      fwd = 0;
-      by_wall_pass = false;
-    } else {
+    if constexpr (MODE != CT_ROWS) {
       if (over) atomicOr(&flags[FLAG_CAPACITY], 1);
-    }
-    if (by_wall_pass && cnt == 0 && by_wall) {  // no binary collision: the wall pass can run now
-      const int h = Pos<P>::walls(k, cx, cy, x, y, vx0, vy0);
-      if (h) {
-        pt.vx[s] = vx0;
-        pt.vy[s] = vy0;
-        nwall += h;
+      // only a particle in a cell next to a wall can meet it
+      const bool by_wall = (!k.per_x && (cx == 0 || cx == k.nx - 1)) || (!k.per_y && (cy == 0 || cy == k.ny - 1));
+      if (cnt == 0 && by_wall) {  // no binary collision: the wall pass can run now
+        T vx = ldu(pt.vx, s), vy = ldu(pt.vy, s);
+        const int h = Pos<P>::walls(k, cx, cy, x, y, vx, vy);
+        if (h) {
+          pt.vx[s] = vx;
+          pt.vy[s] = vy;
+          nwall += h;
+        }
       }
     }
   }
@@ -1627,19 +1555,8 @@ __global__ __launch_bounds__(BLOCK) LBDPS_WAVES8 void k_contacts(Parts<typename 
                                                     Consts<typename Prec<P>::T> k, Adj adj,
                                                     int32_t *__restrict__ deg, int32_t *flags,
                                                     long long *pair_part, long long *wall_part, int32_t *sweep) {
-  contacts_body<P, CONTACT_W, MODE>(xcd_block<XCD_RUN_CONTACTS>(blockIdx.x, gridDim.x), gridDim.x, pt, cs, k, adj, deg,
-                                    flags, pair_part, wall_part, sweep);
-}
-// Grids whose workgroups are all resident at once (CONTACTS_SMALL_MAX): a wider
-// early-loaded window at six waves per SIMD, since latency rather than the
-// number of waves in flight bounds such a launch.
-constexpr int CONTACTS_SMALL_MAX = 1536;
-template <int P, int MODE = CT_ALL>
-__global__ __launch_bounds__(BLOCK) LBDPS_WAVES6 void k_contacts_small(Parts<typename Prec<P>::T> pt,
-    const int32_t *__restrict__ cs, Consts<typename Prec<P>::T> k, Adj adj, int32_t *__restrict__ deg,
-    int32_t *flags, long long *pair_part, long long *wall_part, int32_t *sweep) {
-  contacts_body<P, CONTACT_W_SMALL, MODE>(xcd_block<XCD_RUN_CONTACTS>(blockIdx.x, gridDim.x), gridDim.x, pt, cs, k, adj,
-                                          deg, flags, pair_part, wall_part, sweep);
+  contacts_body<P, MODE>(xcd_block<XCD_RUN_CONTACTS>(blockIdx.x, gridDim.x), pt, cs, k, adj, deg, flags, pair_part,
+                         wall_part, sweep);
 }
 
 // ------------------------------------------------------------------ A7: collision resolution (Eqs. 17-18) and walls

@@ -689,8 +689,7 @@ template <int P> struct Impl {
               (const int32_t *)x->slot, x->adj(), (const int32_t *)x->deg, x->done, x->ticket, k, x->flags,
               x->coll_part, x->wall_part, x->chunk_busy, x->need_sweep);
     } else {
-      tlaunch(x, LBDPS_K_CONTACTS, extra, nblocks(N) <= CONTACTS_SMALL_MAX ? k_contacts_small<P> : k_contacts<P>,
-              dim3(nblocks(N)), parts(x, x->cp), (const int32_t *)x->cs, k, x->adj(), x->deg, x->flags, x->pair_part,
+      tlaunch(x, LBDPS_K_CONTACTS, extra, k_contacts<P>, dim3(nblocks(N)), parts(x, x->cp), (const int32_t *)x->cs, k, x->adj(), x->deg, x->flags, x->pair_part,
               x->wall0_part, x->need_sweep);
       for (int i = 0; i < x->passes; ++i) {
         const PatchGrid g = patch_grid(x->p, x->n, i);
