@@ -526,7 +526,7 @@ lbdps_status lbdps_batch_create(const lbdps_params *beds, int32_t nbeds, const i
 /* The context of bed `bed` (owned by the batch). */
 lbdps_status lbdps_batch_bed(lbdps_batch *batch, int32_t bed, lbdps_ctx **out);
 
-/* Enqueue nsteps steps of every bed: one launch per phase for the whole batch (8 to 10 per step).
+/* Enqueue nsteps steps of every bed: one launch per phase for the whole batch (6 to 8 per step).
  * Results equal nsteps calls of lbdps_step on each bed, bit for bit. */
 lbdps_status lbdps_batch_step(lbdps_batch *batch, int32_t nsteps);
 

@@ -12,7 +12,7 @@
 
 namespace lbdps {
 
-enum { PH_COLLIDE = 0, PH_DRAG, PH_SCAN, PH_SCATTER, PH_CONTACTS, PH_PATCH0, PH_PATCH1, PH_PATCH2, PH_FINAL, PH_COUNT };
+enum { PH_COLLIDE = 0, PH_DRAG, PH_SCAN, PH_SCATTER, PH_CONTACTS, PH_PATCH0, PH_PATCH1, PH_REST, PH_COUNT };
 
 template <int P> struct BedArgs {
   using T = typename Prec<P>::T;
@@ -23,12 +23,12 @@ template <int P> struct BedArgs {
   T *px[2], *py[2], *vx[2], *vy[2];
   Fields<T> fl;
   const T *lut, *inlet;
-  int32_t *cs, *count, *stay, *rank, *slot, *flags, *deg, *sweep, *left, *place_of;
-  FinalMem fin;
+  int32_t *cs, *count, *stay, *rank, *slot, *flags, *deg;
+  RestBuffers rest;
   Adj adj;
   long long *pair_part, *wall0_part;
   PatchGrid pg[PATCH_PASSES];
-  int npass;  // patch passes of this bed; 0: the whole bed in the final workgroup
+  int npass;  // patch passes of this bed before the rest; 0: the whole bed in the final workgroup
   int32_t *pcoll_part[PATCH_PASSES + 1], *pwall_part[PATCH_PASSES + 1];
   TileSums ts;
   int cf;        // population buffer holding the state when the table was written
@@ -38,15 +38,17 @@ template <int P> struct BedArgs {
 };
 
 // Largest b in [0, nbeds) with off[b] <= blk (off[0] = 0; empty beds have
-// off[b] = off[b+1] and are skipped).
+// off[b] = off[b+1] and are skipped): a wavefront looks at 64 beds at a time, so
+// that up to 64 beds cost one load before the workgroup's own first one.
 __device__ __forceinline__ int bed_of(const int *__restrict__ off, int nbeds, int blk) {
-  int lo = 0, hi = nbeds;
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (off[mid] <= blk) lo = mid;
-    else hi = mid;
+  const int lane = (int)threadIdx.x & 63;
+  int b = -1;
+  for (int b0 = 0; b0 < nbeds; b0 += 64) {
+    const int below = __popcll(__ballot(b0 + lane < nbeds && off[min(b0 + lane, nbeds - 1)] <= blk));
+    b += below;
+    if (below < 64) break;
   }
-  return lo;
+  return __builtin_amdgcn_readfirstlane(b);
 }
 
 // flip = parity of the step within the batched sequence: the population
@@ -105,27 +107,28 @@ __global__ __launch_bounds__(BLOCK) LBDPS_WAVES8 void kb_contacts(const BedArgs<
                                                      int nbeds, int flip) {
   LBDPS_BED_PROLOGUE(XCD_RUN_CONTACTS)
   (void)nbk;
-  contacts_body<P>(bid, a.parts(1 - cp), a.cs, a.k, a.adj, a.deg, a.flags, a.pair_part, a.wall0_part, a.sweep);
+  contacts_body<P>(bid, a.parts(1 - cp), a.cs, a.k, a.adj, a.deg, a.flags, a.pair_part, a.wall0_part,
+                   a.rest.sweep);
 }
 
 template <int P, int HELD, bool FIRST>
 __global__ __launch_bounds__(BLOCK) void kb_patches(const BedArgs<P> *__restrict__ tab, const int *__restrict__ off,
-                                                    int nbeds, int flip, int pass) {
+                                                 int nbeds, int flip, int pass) {
   LBDPS_BED_PROLOGUE(XCD_RUN_PATCHES)
+  __shared__ PatchLds<typename Prec<P>::T, BLOCK, HELD> S;
   (void)nbk;
-  patches_body<P, BLOCK, HELD, FIRST>(bid, a.parts(1 - cp), a.cs, a.k, a.adj, a.deg, a.pg[pass],
-                                                    pass + 1 == a.npass, a.left, a.place_of, a.sweep + SW_LEFT, a.pcoll_part[pass],
-                                                    a.pwall_part[pass]);
+  patches_body<P, BLOCK, HELD, FIRST>(S, bid, a.parts(1 - cp), a.cs, a.k, a.adj, a.deg, a.pg[pass], pass + 1 == a.npass,
+                                   a.rest.left, a.rest.place_of, a.rest.sweep + SW_LEFT, a.pcoll_part[pass],
+                                   a.pwall_part[pass]);
 }
 
 template <int P>
-__global__ __launch_bounds__(FINAL_THREADS) void kb_final(const BedArgs<P> *__restrict__ tab,
-                                                          const int *__restrict__ off, int nbeds, int flip) {
+__global__ __launch_bounds__(FINAL_THREADS) void kb_rest(const BedArgs<P> *__restrict__ tab,
+                                                         const int *__restrict__ off, int nbeds, int flip) {
   LBDPS_BED_PROLOGUE(-1)
-  (void)bid;
-  (void)nbk;
-  final_body<P>(a.parts(1 - cp), a.k, a.adj, a.deg, a.npass == 0, a.left, a.place_of, a.sweep + SW_LEFT, a.fin,
-                a.pcoll_part[PATCH_PASSES], a.pwall_part[PATCH_PASSES]);
+  const int np = a.npass;
+  rest_body<P>(bid, nbk, a.parts(1 - cp), a.cs, a.k, a.adj, a.deg, np == 0, a.pg[np], a.rest, a.pcoll_part[np],
+               a.pwall_part[np], a.pcoll_part[PATCH_PASSES], a.pwall_part[PATCH_PASSES]);
 }
 
 #undef LBDPS_BED_PROLOGUE

@@ -326,8 +326,9 @@ constexpr int RES_ITEMS = 8;                  // particle indices per lane and r
 constexpr int DONE_WHOLE = 1 << 30;
 constexpr int RES_CHUNK = BLOCK * RES_ITEMS;  // particle indices per chunk
 // The collision stage's counters: whether the ordered sweep has to run, the
-// tile kernel's candidate roots, the particles the patches left.
-enum { SW_NEED = 0, SW_ROOTS, SW_LEFT, SW_COUNT };
+// tile kernel's candidate roots, the particles the patches left before and in
+// the last pass, and that pass's workgroups that have ended.
+enum { SW_NEED = 0, SW_ROOTS, SW_LEFT, SW_LEFT2, SW_ENDED, SW_COUNT };
 
 // Block-wide exclusive scan of one int per thread; total = block sum.
 __device__ __forceinline__ int block_excl_scan(int v, int *sh, int &total) {
@@ -1384,7 +1385,7 @@ __device__ __forceinline__ void contacts_body(const int bidx, Parts<typename Pre
   const int s = bidx * BLOCK + threadIdx.x;
   long long nwall = 0;
   int fwd = 0;
-  if (MODE != CT_ROWS && s == 0) sweep[SW_LEFT] = 0;
+  if (MODE != CT_ROWS && s < SW_COUNT - SW_LEFT) sweep[SW_LEFT + s] = 0;
   if (s < k.npart) {
     const int key = ldu(pt.key, s);
     const int id = ldu(pt.pid, s);

@@ -91,20 +91,31 @@ int cluster_blocks(long long n, int lists = RC_LISTS, int groups_max = RC_GROUPS
 // The patches of cells of resolution pass `pass`.  A patch of the first pass
 // aims at PATCH_AIM particles with contacts, under the BLOCK its workgroup holds
 // at once: with discs of diameter d at density r, a share 1 - exp(-pi d^2 r) has
-// any.  Spheres over a bottom face lie about 2.4 times as dense as their mean
-// over the lattice.  Few are left for the later passes, whose patches are two
-// and four times as wide and high, their edges a half and a quarter of the
-// first ones' off.
-constexpr double PATCH_AIM = 210.0, PATCH_DENSE = 2.4;
+// any.  Few are left for the later passes, whose patches are two and four times
+// as wide and high, their edges a half and a quarter of the first ones' off.
+//
+// Spheres over a bottom face lie about 2.4 times as dense as their mean over the
+// lattice if the bed fills it, and denser in a lattice much taller than the bed;
+// hence the floor under a single bed's density, as a 2-D solid fraction.  A
+// patch denser than assumed goes in bands of rows, one after the other, and
+// leaves more: a bed of fraction 0.4 in 486 x 2072 cells, 276 000 spheres, takes
+// 145 us with no floor, 84 with 0.4 (and 1 300 where the final workgroup got
+// what two passes had left).  A patch sparser than assumed costs its fixed part:
+// the first pass over 64 beds of 0.05 to 0.4, 4.2 M spheres, takes 174 us with no
+// floor and 235 with 0.4.  In a batch the workgroups of other beds hide the
+// bands, so its beds go by the mean, and aim higher (1 % of a step).
+constexpr double PATCH_AIM = 210.0, PATCH_AIM_BATCH = 235.0, PATCH_DENSE = 2.4;
+constexpr double PATCH_FRACTION0 = 0.35, PATCH_FRACTION = 0.4;  // floors of the first pass and of the later ones
 constexpr int PATCH_AREA_MIN = 16, PATCH_AREA_MAX = 1024;
-double patch_density(const lbdps_params &p, long long n) {  // particles per cell where they are
+double patch_density(const lbdps_params &p, long long n, double fraction) {  // particles per cell where they are
   const bool even = p.bc[2] == BC_PERIODIC || p.particles_periodic_y;
-  return std::max((double)n, 1.0) / ((double)p.nx * p.ny) * (even ? 1.0 : PATCH_DENSE);
+  const double mean = std::max((double)n, 1.0) / ((double)p.nx * p.ny);
+  return even ? mean : std::max(PATCH_DENSE * mean, fraction / (kPi * p.d_p * p.d_p / 4.0));
 }
-PatchGrid patch_grid(const lbdps_params &p, long long n, int pass) {
-  const double dens = patch_density(p, n);
+PatchGrid patch_grid(const lbdps_params &p, long long n, int pass, int beds = 1) {
+  const double dens = patch_density(p, n, beds > 1 ? 0.0 : (pass ? PATCH_FRACTION : PATCH_FRACTION0));
   const double touch = 1.0 - std::exp(-kPi * p.d_p * p.d_p * dens);
-  const double held = std::min(PATCH_AIM / std::max(touch, 1e-3), 0.94 * PATCH_HELD0);
+  const double held = std::min((beds > 1 ? PATCH_AIM_BATCH : PATCH_AIM) / std::max(touch, 1e-3), 0.94 * PATCH_HELD0);
   const double area = std::min(std::max(held / dens, (double)PATCH_AREA_MIN), (double)PATCH_AREA_MAX);
   PatchGrid g{};
   const int tw = std::max(4, std::min(p.nx, (int)std::lround(std::sqrt(2.4 * area))));
@@ -117,17 +128,22 @@ PatchGrid patch_grid(const lbdps_params &p, long long n, int pass) {
   g.nty = (p.ny + g.oy + g.th - 1) / g.th;
   return g;
 }
-// Patch passes of a bed of n particles: none where the final workgroup holds
-// them all, else as many as leave it about PATCH_LEFT particles.  With kappa
-// contacts per particle, about a share 0.053 kappa of the particles with
-// contacts is left after one pass and 0.002 kappa^2.8 after two (0.04 and 0.001
-// measured at kappa 0.75, 0.09 and 0.007 at 1.6).
+// Patch passes of a bed of n particles before the rest: none where the final
+// workgroup alone is as fast (2 048 particles: 21 us, against 13 + 15), else as
+// many as leave it about PATCH_LEFT particles.  With kappa contacts per particle,
+// about a share 0.053 kappa of the particles with contacts is left after one
+// pass (0.04 measured at kappa 0.75, 0.09 at 1.6), 0.001 and 0.007 after two;
+// from about kappa 1.75 on contacts may percolate.  A batch makes the second
+// pass for some bed anyway, so all of its beds take both.
 constexpr double PATCH_LEFT = 2500.0;
-int patch_passes(const lbdps_params &p, long long n) {
-  if (n <= FINAL_CAP) return 0;
-  const double kappa = kPi * p.d_p * p.d_p * patch_density(p, n), touch = (1.0 - std::exp(-kappa)) * (double)n;
-  if (touch * 0.053 * kappa <= PATCH_LEFT && kappa < 1.6) return 1;  // from about there on contacts may percolate
-  return touch * 0.002 * std::pow(kappa, 2.8) <= PATCH_LEFT ? 2 : 3;
+constexpr int PATCH_WHOLE = 2048;
+int patch_passes(const lbdps_params &p, long long n, int beds = 1) {
+  if (n <= PATCH_WHOLE) return 0;
+  const double kappa = kPi * p.d_p * p.d_p * patch_density(p, n, PATCH_FRACTION);
+  return beds == 1 && (1.0 - std::exp(-kappa)) * (double)n * 0.053 * kappa <= PATCH_LEFT && kappa < 1.75 ? 1 : 2;
+}
+int rest_blocks(const lbdps_params &p, long long n, int passes, int beds = 1) {  // of one bed of `beds`
+  return passes > 0 ? std::max(1, std::min(patch_grid(p, n, passes, beds).count(), REST_BLOCKS / beds)) : 1;
 }
 
 size_t pop_bytes(int prec) { return prec == PREC_FP64 ? 8 : (prec == PREC_FP32 ? 4 : 2); }
@@ -268,6 +284,7 @@ struct lbdps_ctx {
   bool in_batch = false;  // owned by a batch: destroyed with it
   lbdps_tuning tune{RC_LISTS, RC_GROUPS_MAX, 0, 0};
   int passes = 0;        // patch passes of the most recent collision stage (-1: it took the tile kernel)
+  int stage_beds = 1;    // and beds its launches were for
   int sphere_tiles = 0;  // tiles of the tile kernel in the most recent collision stage (0: not used)
   int drag_blocks = 0;  // drag workgroups of the most recent step (its partial sums)
   int cluster_groups() const { return cluster_blocks(n, tune.cluster_lists, tune.cluster_groups_max); }
@@ -293,7 +310,10 @@ struct lbdps_ctx {
   // free in the collision stage)
   int32_t *fin_state = nullptr;
   int32_t *left() const { return (int32_t *)roots; }
-  FinalMem final_mem() const { return FinalMem{perm, fin_state, {rank, (int32_t *)roots + nmax}}; }
+  int32_t *left2 = nullptr;
+  RestBuffers rest() const {
+    return RestBuffers{left(), left2, done, need_sweep, FinalMem{perm, fin_state, {rank, (int32_t *)roots + nmax}}};
+  }
   long long *collc_part = nullptr, *wallc_part = nullptr;
   // collisions and wall hits per patch of each pass, and of the final workgroup
   int32_t *pcoll_part[PATCH_PASSES + 1]{}, *pwall_part[PATCH_PASSES + 1]{};
@@ -378,7 +398,7 @@ size_t carve(const lbdps_params &p, long long nmax, char *base, lbdps_ctx *x) {
     pwall[i] = cv.take<int32_t>(np);
   }
   int32_t *chunk_busy = cv.take<int32_t>(N / RES_CHUNK + 1), *need_sweep = cv.take<int32_t>(SW_COUNT);
-  int32_t *fin_state = cv.take<int32_t>(N);
+  int32_t *fin_state = cv.take<int32_t>(N), *left2 = cv.take<int32_t>(N);
   long long *collc_part = cv.take<long long>(nbN), *wallc_part = cv.take<long long>(nbN);
   size_t nst = 1;  // tiles of the sphere tile shape with the most of them
   for (int t = 1; t < SPHERE_TILES; ++t) {
@@ -447,6 +467,7 @@ size_t carve(const lbdps_params &p, long long nmax, char *base, lbdps_ctx *x) {
     x->chunk_busy = chunk_busy;
     x->need_sweep = need_sweep;
     x->fin_state = fin_state;
+    x->left2 = left2;
     x->collc_part = collc_part;
     for (int i = 0; i <= PATCH_PASSES; ++i) {
       x->pcoll_part[i] = pcoll[i];
@@ -678,6 +699,7 @@ template <int P> struct Impl {
     const int st = x->tune.sphere_tile;
     x->sphere_tiles = st > 0 ? sphere_tiles(x, st) : 0;
     x->passes = st > 0 ? -1 : patch_passes(x->p, x->n);
+    x->stage_beds = 1;
     if (st > 0) {
       tlaunch(x, LBDPS_K_CONTACTS, extra, tile_kernel(st), dim3(x->sphere_tiles), parts(x, x->cp),
               (const int32_t *)x->cs, k, x->adj(), x->deg, x->done, x->ticket, x->need_sweep, x->chunk_busy,
@@ -691,17 +713,19 @@ template <int P> struct Impl {
     } else {
       tlaunch(x, LBDPS_K_CONTACTS, extra, k_contacts<P>, dim3(nblocks(N)), parts(x, x->cp), (const int32_t *)x->cs, k, x->adj(), x->deg, x->flags, x->pair_part,
               x->wall0_part, x->need_sweep);
-      for (int i = 0; i < x->passes; ++i) {
+      const int np = x->passes;
+      for (int i = 0; i < np; ++i) {
         const PatchGrid g = patch_grid(x->p, x->n, i);
-        tlaunch(x, LBDPS_K_RESOLVE, extra || i > 0,
-                i == 0 ? k_patches<P, PATCH_HELD0, true> : k_patches<P, PATCH_HELD1, false>, dim3(g.count()),
-                parts(x, x->cp), (const int32_t *)x->cs, k, x->adj(), x->deg, g, (int)(i + 1 == x->passes),
-                x->left(), x->done, x->need_sweep + SW_LEFT, x->pcoll_part[i], x->pwall_part[i]);
+        tlaunch_n(x, LBDPS_K_RESOLVE, extra || i > 0,
+                  i == 0 ? k_patches<P, PATCH_HELD0, true> : k_patches<P, PATCH_HELD1, false>,
+                  dim3(g.count()), dim3(BLOCK), parts(x, x->cp), (const int32_t *)x->cs, k,
+                  x->adj(), x->deg, g, (int)(i + 1 == np), x->left(), x->done, x->need_sweep + SW_LEFT,
+                  x->pcoll_part[i], x->pwall_part[i]);
       }
-      tlaunch_n(x, LBDPS_K_RESOLVE, extra || x->passes > 0, k_final<P>, dim3(1), dim3(FINAL_THREADS),
-                parts(x, x->cp), k, x->adj(), x->deg, (int)(x->passes == 0), x->left(), x->done,
-                (const int32_t *)x->need_sweep + SW_LEFT, x->final_mem(), x->pcoll_part[PATCH_PASSES],
-                x->pwall_part[PATCH_PASSES]);
+      const PatchGrid g = patch_grid(x->p, x->n, np);
+      tlaunch_n(x, LBDPS_K_RESOLVE, extra || np > 0, np > 0 ? k_rest<P, true> : k_rest<P, false>, dim3(rest_blocks(x->p, x->n, np)), dim3(FINAL_THREADS),
+                parts(x, x->cp), (const int32_t *)x->cs, k, x->adj(), x->deg, g, x->rest(),
+                x->pcoll_part[np], x->pwall_part[np], x->pcoll_part[PATCH_PASSES], x->pwall_part[PATCH_PASSES]);
     }
   }
 
@@ -1313,8 +1337,8 @@ lbdps_status lbdps_counters(lbdps_ctx *x, int64_t h_out[4]) {
     }
   if (x->n > 0 && !tile)  // the patch passes and the final workgroup
     for (int i = 0; i <= PATCH_PASSES; ++i) {
-      if (i >= x->passes && i < PATCH_PASSES) continue;
-      const int np = i < PATCH_PASSES ? patch_grid(x->p, x->n, i).count() : 1;
+      if (i < PATCH_PASSES && (i > x->passes || x->passes == 0)) continue;  // the rest's pass comes after the passes
+      const int np = i < PATCH_PASSES ? patch_grid(x->p, x->n, i, x->stage_beds).count() : 1;
       std::vector<int32_t> pb((size_t)np);
       for (int j = 0; j < 2; ++j) {
         st = check_hip(hipMemcpy(pb.data(), j ? x->pwall_part[i] : x->pcoll_part[i], (size_t)np * 4,
@@ -1561,7 +1585,7 @@ template <int P> struct BatchImpl {
   static size_t args_bytes(int nbeds) { return align256((size_t)nbeds * sizeof(BedArgs<P>)); }
   static size_t table_bytes(int nbeds) { return args_bytes(nbeds) + align256((size_t)PH_COUNT * (nbeds + 1) * 4); }
 
-  static BedArgs<P> args(const lbdps_ctx *x) {
+  static BedArgs<P> args(const lbdps_ctx *x, int nbeds) {
     BedArgs<P> a{};
     a.k = I::consts(x);
     for (int b = 0; b < 2; ++b) {
@@ -1583,10 +1607,7 @@ template <int P> struct BatchImpl {
     a.slot = x->slot;
     a.flags = x->flags;
     a.deg = x->deg;
-    a.sweep = x->need_sweep;
-    a.left = x->left();
-    a.place_of = x->done;
-    a.fin = x->final_mem();
+    a.rest = x->rest();
     a.adj = x->adj();
     a.pair_part = x->pair_part;
     a.wall0_part = x->wall0_part;
@@ -1594,9 +1615,9 @@ template <int P> struct BatchImpl {
     a.cf = x->cf;
     a.cp = x->cp;
     a.cp_moves = x->n > 0;
-    a.npass = patch_passes(x->p, x->n);
+    a.npass = patch_passes(x->p, x->n, nbeds);
     for (int i = 0; i <= PATCH_PASSES; ++i) {
-      if (i < PATCH_PASSES) a.pg[i] = patch_grid(x->p, x->n, i);
+      if (i < PATCH_PASSES) a.pg[i] = patch_grid(x->p, x->n, i, nbeds);
       a.pcoll_part[i] = x->pcoll_part[i];
       a.pwall_part[i] = x->pwall_part[i];
     }
@@ -1604,8 +1625,8 @@ template <int P> struct BatchImpl {
   }
 
   // Workgroups of each phase for one bed, as the single-bed step launches
-  // them; the drag under the batch's tile shape `tile`.
-  static void blocks(const lbdps_ctx *x, int tile, int nb[PH_COUNT]) {
+  // them, in a batch of nbeds; the drag under the batch's tile shape `tile`.
+  static void blocks(const lbdps_ctx *x, int nbeds, int tile, int nb[PH_COUNT]) {
     for (int i = 0; i < PH_COUNT; ++i) nb[i] = 0;
     nb[PH_COLLIDE] = nblocks(x->C);
     if (x->n == 0) return;
@@ -1613,9 +1634,9 @@ template <int P> struct BatchImpl {
     nb[PH_SCAN] = x->ntiles;
     nb[PH_SCATTER] = nblocks(x->n);
     nb[PH_CONTACTS] = nblocks(x->n);
-    const int np = patch_passes(x->p, x->n);
-    for (int i = 0; i < np; ++i) nb[PH_PATCH0 + i] = patch_grid(x->p, x->n, i).count();
-    nb[PH_FINAL] = 1;
+    const int np = patch_passes(x->p, x->n, nbeds);
+    for (int i = 0; i < np; ++i) nb[PH_PATCH0 + i] = patch_grid(x->p, x->n, i, nbeds).count();
+    nb[PH_REST] = rest_blocks(x->p, x->n, np, nbeds);
   }
 
   // Fills table t (0 eager, 1 graph) from the beds' current state.
@@ -1638,9 +1659,9 @@ template <int P> struct BatchImpl {
     B->tile[t] = tile;
     for (int b = 0; b < B->nbeds; ++b) {
       const lbdps_ctx *x = B->beds[b];
-      a[b] = args(x);
+      a[b] = args(x, B->nbeds);
       int nb[PH_COUNT];
-      blocks(x, tile, nb);
+      blocks(x, B->nbeds, tile, nb);
       for (int ph = 0; ph < PH_COUNT; ++ph) {
         const long long v = (long long)off[ph * nb1 + b] + nb[ph];
         if (v > 0x7fffffffll) return fail(LBDPS_E_SHAPE, "batch too large for one launch per phase");
@@ -1719,11 +1740,10 @@ template <int P> struct BatchImpl {
       LBDPS_LAUNCH(kb_scan<P>, PH_SCAN)
       LBDPS_LAUNCH(kb_scatter<P>, PH_SCATTER)
       LBDPS_LAUNCH(kb_contacts<P>, PH_CONTACTS)
-      // the final workgroups always run: they are the resolution launch that counts
+      // the rest always runs: it is the resolution launch that counts
       LBDPS_LAUNCH_N((kb_patches<P, PATCH_HELD0, true>), PH_PATCH0, BLOCK, true, 0)
       LBDPS_LAUNCH_N((kb_patches<P, PATCH_HELD1, false>), PH_PATCH1, BLOCK, true, 1)
-      LBDPS_LAUNCH_N((kb_patches<P, PATCH_HELD1, false>), PH_PATCH2, BLOCK, true, 2)
-      LBDPS_LAUNCH_N(kb_final<P>, PH_FINAL, FINAL_THREADS, false)
+      LBDPS_LAUNCH_N(kb_rest<P>, PH_REST, FINAL_THREADS, false)
 #undef LBDPS_LAUNCH_N
 #undef LBDPS_LAUNCH
     }
@@ -1732,7 +1752,8 @@ template <int P> struct BatchImpl {
   static void advance(lbdps_batch *B, int nsteps) {
     for (auto *x : B->beds) {
       x->sphere_tiles = 0;  // the batched collision stage takes the patches
-      if (x->n > 0) x->passes = patch_passes(x->p, x->n);
+      if (x->n > 0) x->passes = patch_passes(x->p, x->n, B->nbeds);
+      x->stage_beds = B->nbeds;
       x->cf ^= nsteps & 1;
       if (x->n > 0) x->cp ^= nsteps & 1;
       x->step += nsteps;

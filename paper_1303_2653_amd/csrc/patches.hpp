@@ -20,17 +20,19 @@
 // Passes with larger patches, moved against the ones before, leave the few
 // clusters that cross an edge in every pass (of the particles with contacts on
 // a 512 x 4096 riser 4 % after one pass, 0.1 % after two); one workgroup takes
-// those of the whole bed at once.
+// those of the whole bed at once.  Where it could not hold them, because the
+// clusters span many patches or the patches were too full, there is a pass of
+// wide workgroups before it (k_rest).
 //
-// The first pass is bound by instruction issue: on the 2 M-sphere riser about
-// 3 000 wavefront instructions per patch of 400 particles, eight patches per CU.
-// Hence the single range check per row entry (the entry carries the partner's
+// The first pass is bound by its chain of dependent loads, barriers and rounds:
+// on the 2 M-sphere riser it issues for 17 of its 46 us, eight patches of 400
+// particles per CU.  Hence the single range check per row entry (the entry carries the partner's
 // row of cells), and the rounds of one wavefront once at most 64 particles have
 // partners left, while the others wait at the barrier.  Measured there, FP32:
-// 47 us for the first pass, 16 us for the second, 18 us for the final workgroup,
+// 47 us for the first pass, 16 us for the second, 19 us for the final workgroup,
 // against 145 us (88 us in its best launch shape) and 5 us for one lane per
 // cluster and the ordered sweep; 310 + 129 + 30 against 1 034 us at 16 M spheres.
-// The later kernels are chains of dependent loads.  A counter all patches add to
+// The later kernels are such chains too.  A counter all patches add to
 // costs 7 ns each, one after the other, so only the last pass lists what it
 // leaves (34 us more for the first pass where it did).
 #pragma once
@@ -46,15 +48,18 @@ struct PatchGrid {
   __host__ __device__ int count() const { return ntx * nty; }
 };
 
-constexpr int PATCH_PASSES = 3;      // most passes
+constexpr int PATCH_PASSES = 3;      // most passes, the last one with the final workgroup
 constexpr int PATCH_ROWS = 64;       // most rows of cells in a patch
 constexpr int PATCH_NB = 8;          // partners' places kept in registers
 constexpr int PATCH_NONE = 0xffff;   // no partner, or one outside
-// Particles a patch's workgroup looks at together: of the first pass, where
-// about half of them have contacts, and of the later ones, where few are left.
+// Particles a patch's workgroup of BLOCK threads looks at together: of the first
+// pass, where about half of them have contacts, and of the second, where few are
+// left.  The pass before the final workgroup has PATCH_WIDE threads: it runs
+// where the bed is much denser in places than patch_grid assumes.
 constexpr int PATCH_HELD0 = 2 * BLOCK, PATCH_HELD1 = 8 * BLOCK;
-// The last workgroup: threads, and particles it holds.
-constexpr int FINAL_THREADS = 1024, FINAL_PT = 4, FINAL_CAP = FINAL_THREADS * FINAL_PT;
+constexpr int PATCH_WIDE = 1024, PATCH_HELD2 = 2 * PATCH_WIDE;
+// The final workgroup: threads, and particles it holds.
+constexpr int FINAL_THREADS = PATCH_WIDE, FINAL_PT = 4, FINAL_CAP = FINAL_THREADS * FINAL_PT;
 // Cell of a particle relative to the patch, for the separation in the cell +
 // offset modes: partners are at most one cell apart after the periodic wrap.
 template <int P>
@@ -102,12 +107,11 @@ template <class T, int NT, int HELD> struct PatchLds {
 };
 
 template <int P, int NT, int HELD, bool FIRST>
-__device__ __forceinline__ void patches_body(const int bidx, Parts<typename Prec<P>::T> pt,
+__device__ __forceinline__ void patches_body(PatchLds<typename Prec<P>::T, NT, HELD> &S, const int bidx, Parts<typename Prec<P>::T> pt,
     const int32_t *__restrict__ cs, const Consts<typename Prec<P>::T> &k, Adj adj, int32_t *__restrict__ deg,
     const PatchGrid g, const bool last, int32_t *__restrict__ left, int32_t *__restrict__ place_of,
     int32_t *__restrict__ nleft, int32_t *__restrict__ coll_part, int32_t *__restrict__ wall_part) {
   using T = typename Prec<P>::T;
-  __shared__ PatchLds<T, NT, HELD> S;
   const int tid = (int)threadIdx.x, lane = tid & 63;
   const int bx = bidx % g.ntx, by = bidx / g.ntx;
   const int x0 = max(bx * g.tw - g.ox, 0), x1 = min((bx + 1) * g.tw - g.ox, k.nx);
@@ -213,10 +217,9 @@ __device__ __forceinline__ void patches_body(const int bidx, Parts<typename Prec
     const int n = S.np;
     if (n == 0) continue;
     if (n > NT) {
-      // Too many with contacts: in the first pass, fewer rows at a time.  Later
-      // passes meet few particles unless a cluster spans many patches, which no
-      // patch resolves.
-      if (FIRST && r1 > r0 + 1) {
+      // Too many with contacts: fewer rows at a time.  Many too many after the
+      // first pass are of clusters that span many patches, which no patch resolves.
+      if ((FIRST || n <= 2 * NT) && r1 > r0 + 1) {
         want = (r1 - r0) / 2;
         r1 = r0;
       } else {
@@ -393,12 +396,13 @@ __device__ __forceinline__ void patches_body(const int bidx, Parts<typename Prec
 
 template <int P, int HELD, bool FIRST>
 __global__ __launch_bounds__(BLOCK) void k_patches(Parts<typename Prec<P>::T> pt, const int32_t *__restrict__ cs,
-                                                Consts<typename Prec<P>::T> k, Adj adj, int32_t *__restrict__ deg,
+                                                   Consts<typename Prec<P>::T> k, Adj adj, int32_t *__restrict__ deg,
                                                 PatchGrid g, int last, int32_t *__restrict__ left,
-                                                int32_t *__restrict__ place_of, int32_t *__restrict__ nleft, int32_t *__restrict__ coll_part,
-                                                int32_t *__restrict__ wall_part) {
-  patches_body<P, BLOCK, HELD, FIRST>(xcd_block<XCD_RUN_PATCHES>(blockIdx.x, gridDim.x), pt, cs, k, adj, deg, g,
-                                      last != 0, left, place_of, nleft, coll_part, wall_part);
+                                                int32_t *__restrict__ place_of, int32_t *__restrict__ nleft,
+                                                int32_t *__restrict__ coll_part, int32_t *__restrict__ wall_part) {
+  __shared__ PatchLds<typename Prec<P>::T, BLOCK, HELD> S;
+  patches_body<P, BLOCK, HELD, FIRST>(S, xcd_block<XCD_RUN_PATCHES>(blockIdx.x, gridDim.x), pt, cs, k, adj, deg, g,
+                                   last != 0, left, place_of, nleft, coll_part, wall_part);
 }
 
 // The clusters that are left, of the whole bed in one workgroup, by the same
@@ -628,14 +632,13 @@ __device__ __forceinline__ void final_mem(const FinalMem M, Parts<typename Prec<
 }
 
 template <int P>
-__device__ __forceinline__ void final_body(Parts<typename Prec<P>::T> pt, const Consts<typename Prec<P>::T> &k,
-    Adj adj, int32_t *deg, const bool whole, int32_t *left, int32_t *place_of,
-    const int32_t *__restrict__ nleft, const FinalMem M, int32_t *__restrict__ coll_part, int32_t *__restrict__ wall_part) {
-  __shared__ FinalLds<P> S;
+__device__ __forceinline__ void final_body(FinalLds<P> &S, Parts<typename Prec<P>::T> pt,
+    const Consts<typename Prec<P>::T> &k, Adj adj, int32_t *deg, const bool whole, int32_t *left, int32_t *place_of,
+    const int nleft, const FinalMem M, int32_t *__restrict__ coll_part, int32_t *__restrict__ wall_part) {
   __shared__ int cnt[3], tot[2], np;
   const int tid = (int)threadIdx.x, lane = tid & 63;
   const bool overflow = __hip_atomic_load(&k.flags[FLAG_CAPACITY], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
-  int n = whole ? 0 : *nleft;
+  int n = nleft;
   if (tid < 2) tot[tid] = 0;
   if (tid == 0) np = 0;
   __syncthreads();
@@ -669,13 +672,64 @@ __device__ __forceinline__ void final_body(Parts<typename Prec<P>::T> pt, const 
     wall_part[0] = tot[1];
   }
 }
+
+// What the passes before left: the final workgroup, if it can hold it; else
+// another pass of patches first, after which the workgroup that ends last is
+// the final one.  The others end at once where the pass is not needed; it keeps
+// the final workgroup's share small where a bed is denser in places than the
+// patches were laid out for.  At most one workgroup per CU, since each has the
+// LDS of the final one.
+constexpr int REST_BLOCKS = 256;
+struct RestBuffers {
+  int32_t *left, *left2, *place_of;
+  int32_t *sweep;  // SW_LEFT, SW_LEFT2, SW_ENDED
+  FinalMem mem;
+};
 template <int P>
-__global__ __launch_bounds__(FINAL_THREADS) void k_final(Parts<typename Prec<P>::T> pt, Consts<typename Prec<P>::T> k,
-                                                         Adj adj, int32_t *__restrict__ deg, int whole, int32_t *left,
-                                                         int32_t *place_of, const int32_t *__restrict__ nleft, FinalMem M,
-                                                         int32_t *__restrict__ coll_part,
-                                                         int32_t *__restrict__ wall_part) {
-  final_body<P>(pt, k, adj, deg, whole != 0, left, place_of, nleft, M, coll_part, wall_part);
+__device__ __forceinline__ void rest_body(const int bidx, const int gdim, Parts<typename Prec<P>::T> pt,
+    const int32_t *__restrict__ cs, const Consts<typename Prec<P>::T> &k, Adj adj, int32_t *deg, const bool whole,
+    const PatchGrid g, const RestBuffers R, int32_t *__restrict__ pass_coll, int32_t *__restrict__ pass_wall,
+    int32_t *__restrict__ coll_part, int32_t *__restrict__ wall_part) {
+  __shared__ union {
+    PatchLds<typename Prec<P>::T, PATCH_WIDE, PATCH_HELD2> patch;
+    FinalLds<P> fin;
+  } U;
+  __shared__ int ended;
+  int n = 0;
+  int32_t *left = R.left;
+  if (!whole) {
+    n = R.sweep[SW_LEFT];
+    if (n <= FINAL_CAP) {  // uniform over the launch
+      for (int i = bidx * FINAL_THREADS + (int)threadIdx.x; i < g.count(); i += gdim * FINAL_THREADS)
+        pass_coll[i] = pass_wall[i] = 0;
+      if (bidx != 0) return;
+    } else {
+      for (int i = bidx; i < g.count(); i += gdim) {
+        patches_body<P, PATCH_WIDE, PATCH_HELD2, false>(U.patch, i, pt, cs, k, adj, deg, g, true, R.left2,
+                                                        R.place_of, R.sweep + SW_LEFT2, pass_coll, pass_wall);
+        __syncthreads();
+      }
+      __threadfence();
+      __syncthreads();
+      if (threadIdx.x == 0) ended = atomicAdd(&R.sweep[SW_ENDED], 1);
+      __syncthreads();
+      if (ended != gdim - 1) return;  // uniform
+      __threadfence();
+      n = __hip_atomic_load(&R.sweep[SW_LEFT2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      left = R.left2;
+    }
+  }
+  final_body<P>(U.fin, pt, k, adj, deg, whole, left, R.place_of, n, R.mem, coll_part, wall_part);
+}
+template <int P, bool PASSES>
+__global__ __launch_bounds__(FINAL_THREADS) void k_rest(Parts<typename Prec<P>::T> pt, const int32_t *__restrict__ cs,
+                                                        Consts<typename Prec<P>::T> k, Adj adj, int32_t *deg,
+                                                        PatchGrid g, RestBuffers R, int32_t *__restrict__ pass_coll,
+                                                        int32_t *__restrict__ pass_wall,
+                                                        int32_t *__restrict__ coll_part,
+                                                        int32_t *__restrict__ wall_part) {
+  rest_body<P>(blockIdx.x, gridDim.x, pt, cs, k, adj, deg, !PASSES, g, R, pass_coll, pass_wall, coll_part,
+               wall_part);
 }
 
 }  // namespace lbdps

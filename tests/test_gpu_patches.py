@@ -27,10 +27,12 @@ def grid(x0, y0, k, spacing):
 
 def bed(name):
     t = synth.tiny
-    if name == "whole-4096":  # the most the final workgroup takes alone
-        return t(nx=60, ny=61, n=4096, seed=3, bc=WALLED)
-    if name == "patches-4097":  # one more: patches
-        return t(nx=61, ny=60, n=4097, seed=4, bc=RISER)
+    if name == "whole-2048":  # the most the final workgroup takes alone
+        return t(nx=42, ny=43, n=2048, seed=3, bc=WALLED)
+    if name == "patches-2049":  # one more: patches
+        return t(nx=43, ny=42, n=2049, seed=4, bc=RISER)
+    if name == "thin":  # a crowded bed at the bottom of a tall lattice: patches too full, in bands of rows
+        return t(nx=160, ny=1300, n=42_000, seed=14, bc=BED, band=80)
     if name == "one-pass":
         return t(nx=101, ny=97, n=9000, seed=5, bc=PER)
     if name == "two-passes":
@@ -57,7 +59,7 @@ def bed(name):
     raise KeyError(name)
 
 
-BEDS = ("whole-4096", "patches-4097", "one-pass", "two-passes", "three-passes", "narrow", "flat", "percolating",
+BEDS = ("whole-2048", "patches-2049", "thin", "one-pass", "two-passes", "three-passes", "narrow", "flat", "percolating",
         "crowded-rows", "many-partners")
 
 
