@@ -36,11 +36,11 @@ enum { L3_ES = 0, L3_RELAX, L3_OMG, L3_EG, L3_DILUTE, L3_A, L3_BRE, L3_H, L3_OM,
 
 // XCD run lengths of the 3-D kernels that read neighbouring rows and planes.
 // The gradient reads the rows above and below, which runs of 8 tiles keep on
-// one XCD; the contact search (27 cells) takes one contiguous run of tiles per
-// XCD.  On the 256 x 256 x 1024 riser each is 3-4 % faster than in dispatch
-// order; the drag, whose node reads are spread over whole planes, gains
-// nothing from either and keeps the dispatch order.
-constexpr int XCD_RUN_3D_CONTACTS = 0, XCD_RUN_3D_GRADP = 8;
+// one XCD; the contact search (27 cells) and the drag (8 nodes) take one
+// contiguous run of tiles per XCD.  On the 256 x 256 x 1024 riser the first and
+// the second are 3-4 % faster than in dispatch order; on 128 x 128 x 512 cells the
+// drag is 8 % faster.
+constexpr int XCD_RUN_3D_CONTACTS = 0, XCD_RUN_3D_GRADP = 8, XCD_RUN_3D_DRAG = 0;
 
 template <class T> struct Parts3 {
   int32_t *key, *pid;  // cell (z ny + y) nx + x; particle index
@@ -48,18 +48,34 @@ template <class T> struct Parts3 {
   T *vx, *vy, *vz;
 };
 
-// node: per cell the eight values the particle interpolation reads, packed
-// (u_gas x, y, z, solid fraction, beta, grad p x, y, z) so that a node is one
-// contiguous 8-value load.
+// The eight values per cell that the particle interpolation reads, in two
+// records: u_gas and the solid fraction, which the collide kernel writes, and
+// beta and grad p.  (With one record of eight, the gradient kernel copied the
+// first five into it and took 93 us on 128 x 128 x 512 cells; now it takes 37.
+// Halves of one record written by two kernels cost both 30 us each.)
+template <class T> struct alignas(4 * sizeof(T)) Node4 {
+  T v[4];
+};
 template <class T> struct Fields3 {
-  T *rho, *ugx, *ugy, *ugz, *beta, *es, *fpx, *fpy, *fpz, *node;
+  T *rho, *beta, *fpx, *fpy, *fpz;
+  Node4<T> *gas, *grad;  // (u_gas x, y, z, solid fraction), (beta, grad p x, y, z)
 };
-template <class T> struct alignas(8 * sizeof(T)) Node8 {
-  T v[8];
+
+// i / n for 0 <= i < 2^31 as (2 i m) >> 32 >> s, m = ceil(2^(31 + s) / n), 2^s >= n.
+struct Divisor {
+  unsigned m;
+  int s;
+  __device__ __forceinline__ int of(int i) const { return (int)(__umulhi(2u * (unsigned)i, m) >> s); }
 };
+inline Divisor divisor(int n) {
+  int l = 0;
+  while ((1ll << l) < n) ++l;
+  return Divisor{(unsigned)(((1ull << (31 + l)) + (unsigned long long)n - 1) / (unsigned long long)n), l};
+}
 
 template <class T> struct Consts3 {
   int nx, ny, nz, C, npart, nlut;
+  Divisor div_nx, div_ny;
   T tau, d, dd, mu, vp, m, msum, one_e, fp;
   T geff[3], halfG[3], src[Q3];
   int32_t *flags;
@@ -67,10 +83,10 @@ template <class T> struct Consts3 {
 };
 
 template <class T> __device__ __forceinline__ void cell3_xyz(const Consts3<T> &k, int key, int &x, int &y, int &z) {
-  x = key % k.nx;
-  const int yz = key / k.nx;
-  y = yz % k.ny;
-  z = yz / k.ny;
+  const int yz = k.div_nx.of(key);
+  x = key - yz * k.nx;
+  z = k.div_ny.of(yz);
+  y = yz - z * k.ny;
 }
 __device__ __forceinline__ int wrap_p(int i, int n) { return i < 0 ? i + n : (i >= n ? i - n : i); }
 
@@ -217,17 +233,37 @@ __global__ __launch_bounds__(BLOCK) void k3c_scatter(Parts3<T> src, Parts3<T> ds
   slot[id] = d;
 }
 
-// f^eq of Eq. 4 on D3Q19 (FP64, the oracle's operations in its order).
-__device__ __forceinline__ double feq3_d(int i, double rho, double ux, double uy, double uz) {
-  const double cu = (double)c3(i, 0) * ux + (double)c3(i, 1) * uy + (double)c3(i, 2) * uz;
-  const double uu = ux * ux + uy * uy + uz * uz;
-  return w3<double>(i) * rho * (1.0 + 3.0 * cu + 4.5 * cu * cu - 1.5 * uu);
+// c_i . u without the products by zero.
+template <class T> __device__ __forceinline__ T dot3(int i, const T *u) {
+  T s = (T)0;
+  bool first = true;
+#pragma unroll
+  for (int q = 0; q < 3; ++q)
+    if (c3(i, q) != 0) {
+      const T t = c3(i, q) > 0 ? u[q] : -u[q];
+      s = first ? t : s + t;
+      first = false;
+    }
+  return s;
 }
-// Its deviation from w_i with FP32 arithmetic: w ((rho - 1) + rho (3 c.u + 4.5 (c.u)^2 - 1.5 u.u)).
-__device__ __forceinline__ float geq3_f(int i, float rho, float r1, float ux, float uy, float uz) {
-  const float cu = (float)c3(i, 0) * ux + (float)c3(i, 1) * uy + (float)c3(i, 2) * uz;
-  const float uu = ux * ux + uy * uy + uz * uz;
-  return w3<float>(i) * (r1 + rho * (3.0f * cu + 4.5f * cu * cu - 1.5f * uu));
+// f^eq of Eq. 4 on D3Q19 in the directions i and opp_i, from cu = c_i . u and
+// uu = 1.5 u.u: the oracle's operations in its order in FP64, the deviation from
+// w_i, w ((rho - 1) + rho (3 c.u + 4.5 (c.u)^2 - 1.5 u.u)), with FP32 arithmetic.
+// The opposite one has the same square and the negated product.
+template <int P, class T> __device__ __forceinline__ void eq3_pair(int i, T rho, T r1, T cu, T uu, T &e, T &eo) {
+  const T t = (T)3 * cu, a = (T)4.5 * cu * cu;
+  if constexpr (P == PREC_FP64) {
+    const T wr = w3<T>(i) * rho;
+    e = wr * ((T)1 + t + a - uu);
+    eo = wr * ((T)1 - t + a - uu);
+  } else {
+    e = w3<T>(i) * (r1 + rho * (t + a - uu));
+    eo = w3<T>(i) * (r1 + rho * (a - t - uu));
+  }
+}
+template <int P, class T> __device__ __forceinline__ T eq3_rest(T rho, T r1, T uu) {
+  if constexpr (P == PREC_FP64) return w3<T>(0) * rho * ((T)1 - uu);
+  else return w3<T>(0) * (r1 + rho * ((T)0 - uu));
 }
 
 // ---------------------------------------------------------------- deposition + collision + streaming
@@ -236,6 +272,13 @@ __device__ __forceinline__ float geq3_f(int i, float rho, float r1, float ux, fl
 // arrival order), n and the velocity sum are taken in that order (Eq. 8),
 // then the collision of Eq. 23, the force of Eq. 25, the velocities of Eq. 24
 // and beta at the node, and the push to x + c_i.
+//
+// With a 16-bit storage it moves 112 bytes a cell (190 us at 128 x 128 x 512
+// cells at a large copy's rate) and issued for 234 of its 241 us there: hence the
+// pairs of directions, sums without the products by zero, one 32-bit offset per
+// access and the divisions by multiplication, which leave 168 us of issue and
+// 230 in all.  Six or eight wavefronts per SIMD instead of five are slower (234,
+// 492 us).
 template <int P>
 __global__ __launch_bounds__(BLOCK) void k3c_collide(const typename Prec<P>::S *__restrict__ fsrc,
                                                      typename Prec<P>::S *__restrict__ fdst,
@@ -249,8 +292,8 @@ __global__ __launch_bounds__(BLOCK) void k3c_collide(const typename Prec<P>::S *
   const size_t C = (size_t)k.C;
   T f[Q3];
 #pragma unroll
-  for (int i = 0; i < Q3; ++i) f[i] = load_v<P>(fsrc, (size_t)i * C + c);
-  const int a0 = cs[c], a1 = cs[c + 1], n = a1 - a0;
+  for (int i = 0; i < Q3; ++i) f[i] = from_store<P>(ldu(fsrc + (size_t)i * C, c));
+  const int a0 = ldu(cs, c), a1 = ldu(cs, c + 1), n = a1 - a0;
   for (int i = a0 + 1; i < a1; ++i) {  // insertion sort by particle index
     const int kv = pt.pid[i];
     if (pt.pid[i - 1] <= kv) continue;
@@ -288,49 +331,49 @@ __global__ __launch_bounds__(BLOCK) void k3c_collide(const typename Prec<P>::S *
     for (int q = 0; q < 3; ++q) vs[q] = vs[q] / (T)n;
   const T *L = lut + (size_t)min(n, k.nlut - 1) * L3_W;
   const T relax = L[L3_RELAX], omg = L[L3_OMG], eg = L[L3_EG];
-  T fs[Q3], F[3] = {(T)0, (T)0, (T)0}, j[3] = {(T)0, (T)0, (T)0}, rho_store;
-  T rho;
+  T F[3] = {(T)0, (T)0, (T)0}, j[3] = {(T)0, (T)0, (T)0}, r1 = (T)0, u[3];
+  // FP32 arithmetic holds deviations: rho - 1 = sum g, j = sum c g, and in Eq. 7
+  // the weights of f_opp(i) and f_i cancel
+#pragma unroll
+  for (int i = 0; i < Q3; ++i) {
+    r1 += f[i];
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+      if (c3(i, q) != 0) j[q] += c3(i, q) > 0 ? f[i] : -f[i];
+  }
+  const T rho = P == PREC_FP64 ? r1 : (T)1 + r1, rho_store = r1;
   if constexpr (P == PREC_FP64) {
-    T r = 0.0;
 #pragma unroll
-    for (int i = 0; i < Q3; ++i) {
-      r += f[i];
-#pragma unroll
-      for (int q = 0; q < 3; ++q) j[q] += (T)c3(i, q) * f[i];
-    }
-    const T u[3] = {j[0] / r, j[1] / r, j[2] / r};
-#pragma unroll
-    for (int i = 0; i < Q3; ++i) {
-      const int o = opp3(i);
-      const T om = f[o] - f[i] + feq3_d(i, r, vs[0], vs[1], vs[2]) - feq3_d(o, r, u[0], u[1], u[2]);
-      fs[i] = f[i] - relax * (f[i] - feq3_d(i, r, u[0], u[1], u[2])) + omg * om + k.src[i];
-#pragma unroll
-      for (int q = 0; q < 3; ++q) F[q] += (T)c3(i, q) * om;
-    }
-    rho = r;
-    rho_store = r;
+    for (int q = 0; q < 3; ++q) u[q] = j[q] / rho;
   } else {
-    // deviations: rho - 1 = sum g, j = sum c g, and in Eq. 7 the weights of
-    // f_opp(i) and f_i cancel
-    T r1 = (T)0;
-#pragma unroll
-    for (int i = 0; i < Q3; ++i) {
-      r1 += f[i];
-#pragma unroll
-      for (int q = 0; q < 3; ++q) j[q] += (T)c3(i, q) * f[i];
-    }
-    rho = (T)1 + r1;
     const T ir = dv<P>((T)1, rho);
-    const T u[3] = {j[0] * ir, j[1] * ir, j[2] * ir};
 #pragma unroll
-    for (int i = 0; i < Q3; ++i) {
-      const int o = opp3(i);
-      const T om = f[o] - f[i] + geq3_f(i, rho, r1, vs[0], vs[1], vs[2]) - geq3_f(o, rho, r1, u[0], u[1], u[2]);
-      fs[i] = f[i] - relax * (f[i] - geq3_f(i, rho, r1, u[0], u[1], u[2])) + omg * om + k.src[i];
+    for (int q = 0; q < 3; ++q) u[q] = j[q] * ir;
+  }
+  const T uu = (T)1.5 * (u[0] * u[0] + u[1] * u[1] + u[2] * u[2]);
+  const T ww = (T)1.5 * (vs[0] * vs[0] + vs[1] * vs[1] + vs[2] * vs[2]);
+  {
+    const T ge = eq3_rest<P>(rho, r1, uu);
+    const T om = f[0] - f[0] + eq3_rest<P>(rho, r1, ww) - ge;
+    f[0] = f[0] - relax * (f[0] - ge) + omg * om + k.src[0];
+  }
 #pragma unroll
-      for (int q = 0; q < 3; ++q) F[q] += (T)c3(i, q) * om;
-    }
-    rho_store = r1;
+  for (int i = 1; i < Q3; i += 2) {
+    static_assert(opp3(1) == 2 && opp3(17) == 18, "directions come in opposite pairs");
+    const int o = i + 1;
+    T gi, go, si, so;
+    eq3_pair<P>(i, rho, r1, dot3(i, u), uu, gi, go);
+    eq3_pair<P>(i, rho, r1, dot3(i, vs), ww, si, so);
+    const T fi = f[i], fo = f[o];
+    const T om = fo - fi + si - go, omo = fi - fo + so - gi;
+    f[i] = fi - relax * (fi - gi) + omg * om + k.src[i];
+    f[o] = fo - relax * (fo - go) + omg * omo + k.src[o];
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+      if (c3(i, q) != 0) F[q] += c3(i, q) > 0 ? om : -om;
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+      if (c3(o, q) != 0) F[q] += c3(o, q) > 0 ? omo : -omo;
   }
   T ug[3], sl2 = (T)0;
 #pragma unroll
@@ -352,27 +395,25 @@ __global__ __launch_bounds__(BLOCK) void k3c_collide(const typename Prec<P>::S *
   } else {
     beta = L[L3_D1] + dv<P>(L[L3_D2] * slip, k.d);
   }
-  fl.rho[c] = rho_store;
-  fl.ugx[c] = ug[0];
-  fl.ugy[c] = ug[1];
-  fl.ugz[c] = ug[2];
-  fl.fpx[c] = F[0];
-  fl.fpy[c] = F[1];
-  fl.fpz[c] = F[2];
-  fl.beta[c] = beta;
-  fl.es[c] = L[L3_ES];
+  stu(fl.rho, c, rho_store);
+  fl.gas[c] = Node4<T>{{ug[0], ug[1], ug[2], L[L3_ES]}};
+  stu(fl.fpx, c, F[0]);
+  stu(fl.fpy, c, F[1]);
+  stu(fl.fpz, c, F[2]);
+  stu(fl.beta, c, beta);
   if (dg_n) dg_n[c] = n;
   int x, y, z;
   cell3_xyz(k, c, x, y, z);
+  const int tx[3] = {wrap_p(x - 1, k.nx), x, wrap_p(x + 1, k.nx)};
+  const int ty[3] = {wrap_p(y - 1, k.ny), y, wrap_p(y + 1, k.ny)};
+  const int tz[3] = {wrap_p(z - 1, k.nz), z, wrap_p(z + 1, k.nz)};
 #pragma unroll
-  for (int i = 0; i < Q3; ++i) {
-    const int tx = wrap_p(x + c3(i, 0), k.nx), ty = wrap_p(y + c3(i, 1), k.ny), tz = wrap_p(z + c3(i, 2), k.nz);
-    store_v<P>(fdst, (size_t)i * C + ((size_t)tz * k.ny + ty) * k.nx + tx, fs[i]);
-  }
+  for (int i = 0; i < Q3; ++i)
+    stu(fdst + (size_t)i * C, (tz[1 + c3(i, 2)] * k.ny + ty[1 + c3(i, 1)]) * k.nx + tx[1 + c3(i, 0)], to_store<P>(f[i]));
 }
 
-// Node pressure gradient (central differences of p = rho / 3, periodic),
-// packed with the node's u_gas, solid fraction and beta for the interpolation.
+// Node pressure gradient (central differences of p = rho / 3, periodic), with
+// beta in the record for the interpolation.
 template <int P>
 __global__ __launch_bounds__(BLOCK) void k3c_gradp(Fields3<typename Prec<P>::T> fl, Consts3<typename Prec<P>::T> k) {
   using T = typename Prec<P>::T;
@@ -384,16 +425,26 @@ __global__ __launch_bounds__(BLOCK) void k3c_gradp(Fields3<typename Prec<P>::T> 
   const int xp = z * nxy + y * k.nx + wrap_p(x + 1, k.nx), xm = z * nxy + y * k.nx + wrap_p(x - 1, k.nx);
   const int yp = z * nxy + wrap_p(y + 1, k.ny) * k.nx + x, ym = z * nxy + wrap_p(y - 1, k.ny) * k.nx + x;
   const int zp = wrap_p(z + 1, k.nz) * nxy + y * k.nx + x, zm = wrap_p(z - 1, k.nz) * nxy + y * k.nx + x;
-  Node8<T> nd;
-  nd.v[0] = fl.ugx[c];
-  nd.v[1] = fl.ugy[c];
-  nd.v[2] = fl.ugz[c];
-  nd.v[3] = fl.es[c];
-  nd.v[4] = fl.beta[c];
-  nd.v[5] = (dv<P>(fl.rho[xp], (T)3.0) - dv<P>(fl.rho[xm], (T)3.0)) * (T)0.5;
-  nd.v[6] = (dv<P>(fl.rho[yp], (T)3.0) - dv<P>(fl.rho[ym], (T)3.0)) * (T)0.5;
-  nd.v[7] = (dv<P>(fl.rho[zp], (T)3.0) - dv<P>(fl.rho[zm], (T)3.0)) * (T)0.5;
-  reinterpret_cast<Node8<T> *>(fl.node)[c] = nd;
+  Node4<T> nd;
+  nd.v[0] = ldu(fl.beta, c);
+  nd.v[1] = (dv<P>(ldu(fl.rho, xp), (T)3.0) - dv<P>(ldu(fl.rho, xm), (T)3.0)) * (T)0.5;
+  nd.v[2] = (dv<P>(ldu(fl.rho, yp), (T)3.0) - dv<P>(ldu(fl.rho, ym), (T)3.0)) * (T)0.5;
+  nd.v[3] = (dv<P>(ldu(fl.rho, zp), (T)3.0) - dv<P>(ldu(fl.rho, zm), (T)3.0)) * (T)0.5;
+  fl.grad[c] = nd;
+}
+
+// The value of a lane of the quad, by DPP control: 0x4e is the one two lanes on.
+template <int CTRL, class T> __device__ __forceinline__ T quad(T v) {
+  if constexpr (sizeof(T) == 4) {
+    return __builtin_bit_cast(T, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
+  } else {
+    struct Two {
+      int a, b;
+    } w = __builtin_bit_cast(Two, v);
+    w.a = __builtin_amdgcn_mov_dpp(w.a, CTRL, 0xf, 0xf, true);
+    w.b = __builtin_amdgcn_mov_dpp(w.b, CTRL, 0xf, 0xf, true);
+    return __builtin_bit_cast(T, w);
+  }
 }
 
 // Gas quantities at one particle: trilinear interpolation of u_gas, the solid
@@ -402,30 +453,82 @@ __global__ __launch_bounds__(BLOCK) void k3c_gradp(Fields3<typename Prec<P>::T> 
 template <int P> struct Interp3 {
   using T = typename Prec<P>::T;
   T u[3], es, beta, gp[3];
-  __device__ void at(const Consts3<T> &k, const Fields3<T> &fl, const int *cc, const T *o) {
-    int i0[3];
-    T t[3];
+  __device__ void stencil(const Consts3<T> &k, const int *cc, const T *o, int *i0, T *t) {
     const int nn[3] = {k.nx, k.ny, k.nz};
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
       Pos3<P>::axis_stencil(cc[q], o[q], i0[q], t[q]);
       i0[q] = min(max(i0[q], -1), nn[q] - 1);  // a position in the box needs no clamp; a NaN stays in bounds
     }
+  }
+  // The particles of the wavefront, all lanes active, sixteen neighbours in cell
+  // order at a time: four lanes read the two records of two nodes next to each
+  // other in x, a record per lane, and lane 0 of the four ends up with the sums
+  // of the gas record, lane 1 with the other's.  A load of the wavefront then
+  // touches the lines of about 100 consecutive cells, not those of 64 particles
+  // in one place each: the kernel is bound by its requests for lines (159 us on
+  // 128 x 128 x 512 cells and 1.25 M spheres, 200 with a particle per lane, 167
+  // with the four particles of four lanes in turn).
+  template <int L> __device__ __forceinline__ void sixteen(const Consts3<T> &k, const Fields3<T> &fl, const int *i0,
+                                                           const T *t) {
+    const int lane = (int)threadIdx.x & 63, j = lane & 3, ox = j >> 1, src = 16 * L + (lane >> 2);
+    const int x = __shfl(i0[0], src, 64), y = __shfl(i0[1], src, 64), z = __shfl(i0[2], src, 64);
+    const T tx = __shfl(t[0], src, 64), ty = __shfl(t[1], src, 64), tz = __shfl(t[2], src, 64);
+    const int xs = wrap_p(x + ox, k.nx), ys[2] = {wrap_p(y, k.ny), wrap_p(y + 1, k.ny)};
+    const int zs[2] = {wrap_p(z, k.nz) * k.ny, wrap_p(z + 1, k.nz) * k.ny};
+    const Node4<T> *rec = j & 1 ? fl.grad : fl.gas;
+    Node4<T> h[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) h[r] = rec[(zs[r >> 1] + ys[r & 1]) * k.nx + xs];
+    const T wx = ox ? tx : (T)1.0 - tx;
+    T a[4] = {(T)0, (T)0, (T)0, (T)0};
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const T w = wx * (r & 1 ? ty : (T)1.0 - ty) * (r >> 1 ? tz : (T)1.0 - tz);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const T p = w * h[r].v[c];
+        a[c] += p;
+        a[c] += quad<0x4e>(p);
+      }
+    }
+    const int from = (lane & 15) * 4;
+    T lo[4], hi[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) lo[c] = __shfl(a[c], from, 64), hi[c] = __shfl(a[c], from + 1, 64);
+    if (lane >> 4 == L) {
+      u[0] = lo[0], u[1] = lo[1], u[2] = lo[2], es = lo[3];
+      beta = hi[0], gp[0] = hi[1], gp[1] = hi[2], gp[2] = hi[3];
+    }
+  }
+  __device__ void at_wave(const Consts3<T> &k, const Fields3<T> &fl, const int *cc, const T *o) {
+    int i0[3];
+    T t[3];
+    stencil(k, cc, o, i0, t);
+    sixteen<0>(k, fl, i0, t);
+    sixteen<1>(k, fl, i0, t);
+    sixteen<2>(k, fl, i0, t);
+    sixteen<3>(k, fl, i0, t);
+  }
+  __device__ void at(const Consts3<T> &k, const Fields3<T> &fl, const int *cc, const T *o) {
+    int i0[3];
+    T t[3];
+    stencil(k, cc, o, i0, t);
     u[0] = u[1] = u[2] = es = beta = gp[0] = gp[1] = gp[2] = (T)0;
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
       const int ox = q & 1, oy = (q >> 1) & 1, oz = q >> 2;
       const int id = (wrap_p(i0[2] + oz, k.nz) * k.ny + wrap_p(i0[1] + oy, k.ny)) * k.nx + wrap_p(i0[0] + ox, k.nx);
       const T w = (ox ? t[0] : (T)1.0 - t[0]) * (oy ? t[1] : (T)1.0 - t[1]) * (oz ? t[2] : (T)1.0 - t[2]);
-      const Node8<T> nd = reinterpret_cast<const Node8<T> *>(fl.node)[id];
-      u[0] += w * nd.v[0];
-      u[1] += w * nd.v[1];
-      u[2] += w * nd.v[2];
-      es += w * nd.v[3];
-      beta += w * nd.v[4];
-      gp[0] += w * nd.v[5];
-      gp[1] += w * nd.v[6];
-      gp[2] += w * nd.v[7];
+      const Node4<T> g = fl.gas[id], p = fl.grad[id];
+      u[0] += w * g.v[0];
+      u[1] += w * g.v[1];
+      u[2] += w * g.v[2];
+      es += w * g.v[3];
+      beta += w * p.v[0];
+      gp[0] += w * p.v[1];
+      gp[1] += w * p.v[2];
+      gp[2] += w * p.v[3];
     }
   }
 };
@@ -441,17 +544,19 @@ template <int P> struct Interp3 {
 // Eq. 16, moves the particle with the periodic wrap and counts it into its
 // new cell.  The moved record goes to the same slot of the other record set
 // (out), so the records every workgroup reads stay as they were.  Six waves
-// per SIMD (68 VGPRs in FP32) rather than the five the registers allow
+// per SIMD (70 VGPRs in FP32) rather than the five the registers allow
 // unbounded: 1.5 % faster; eight were 6.5 % slower.
 template <int P> struct PreDrag3 {
   using T = typename Prec<P>::T;
   T pd[3];  // cf (u_gas - v), Eq. 26 before the per-cell correction
   Interp3<P> I;
+  template <bool TOGETHER>
   __device__ void at(const Parts3<T> &pt, const Fields3<T> &fl, const Consts3<T> &k, int t) {
     int cc[3];
-    cell3_xyz(k, pt.key[t], cc[0], cc[1], cc[2]);
-    const T o[3] = {pt.px[t], pt.py[t], pt.pz[t]}, v[3] = {pt.vx[t], pt.vy[t], pt.vz[t]};
-    I.at(k, fl, cc, o);
+    cell3_xyz(k, ldu(pt.key, t), cc[0], cc[1], cc[2]);
+    const T o[3] = {ldu(pt.px, t), ldu(pt.py, t), ldu(pt.pz, t)}, v[3] = {ldu(pt.vx, t), ldu(pt.vy, t), ldu(pt.vz, t)};
+    if constexpr (TOGETHER) I.at_wave(k, fl, cc, o);
+    else I.at(k, fl, cc, o);
     const T cf = dv<P>(k.vp * I.beta, I.es);
 #pragma unroll
     for (int q = 0; q < 3; ++q) pd[q] = cf * (I.u[q] - v[q]);
@@ -466,13 +571,12 @@ __global__ __launch_bounds__(BLOCK) LBDPS_WAVES6 void k3c_drag(Parts3<typename P
                                                   typename Prec<P>::T *dg_acc) {
   using T = typename Prec<P>::T;
   __shared__ T spd[3][BLOCK];
-  const int s0 = blockIdx.x * BLOCK, s = s0 + threadIdx.x, s1 = min(s0 + BLOCK, k.npart);
+  const int s0 = xcd_block<XCD_RUN_3D_DRAG>(blockIdx.x, gridDim.x) * BLOCK, s = s0 + threadIdx.x;
+  const int s1 = min(s0 + BLOCK, k.npart);
   PreDrag3<P> me;
-  if (s < k.npart) {
-    me.at(pt, fl, k, s);
+  me.template at<true>(pt, fl, k, min(s, k.npart - 1));  // all lanes: those past the end repeat the last particle
 #pragma unroll
-    for (int q = 0; q < 3; ++q) spd[q][threadIdx.x] = me.pd[q];
-  }
+  for (int q = 0; q < 3; ++q) spd[q][threadIdx.x] = me.pd[q];
   __syncthreads();
   if (s >= k.npart) return;
   const int c = pt.key[s];
@@ -485,7 +589,7 @@ __global__ __launch_bounds__(BLOCK) LBDPS_WAVES6 void k3c_drag(Parts3<typename P
       for (int q = 0; q < 3; ++q) pd[q] = spd[q][t - s0];
     } else {  // a member held by the neighbouring workgroup
       PreDrag3<P> o;
-      o.at(pt, fl, k, t);
+      o.template at<false>(pt, fl, k, t);
 #pragma unroll
       for (int q = 0; q < 3; ++q) pd[q] = o.pd[q];
     }
@@ -536,6 +640,10 @@ __global__ __launch_bounds__(BLOCK) LBDPS_WAVES6 void k3c_drag(Parts3<typename P
 // cells that come within d of the particle along each axis can hold one (two
 // of the three per axis for d <= 1/2, with a rounding margin).  Contacts are
 // kept as a row sorted by particle index (index << 32 | slot), as in 2-D.
+// The search was bound by instruction issue (64 of 75 us on 128 x 128 x 512 cells,
+// 1.25 M spheres), mostly divisions for the candidates' cells: a candidate's
+// offset is that of the range it is in, and at most four ranges are looked at:
+// 40 of 50 us.
 // Eight waves per SIMD (58 VGPRs in FP32, no spill) instead of seven: the
 // search is a chain of dependent loads, and the extra wave makes it 10 %
 // faster on the 256 x 256 x 1024 riser.
@@ -576,13 +684,22 @@ __global__ __launch_bounds__(BLOCK) LBDPS_WAVES8 void k3c_contacts(Parts3<typena
     const AdjRow row = adj.row(s);
     int cnt = 0;
     bool over = false;
-    auto test = [&](int t) {
+    // candidate t in the cell at offset oy, oz, whose row of cells starts at `base`
+    auto test = [&](int t, int base, int oy, int oz) {
       if (t == s) return;
-      const T b[3] = {pt.px[t], pt.py[t], pt.pz[t]};
+      const T b[3] = {ldu(pt.px, t), ldu(pt.py, t), ldu(pt.pz, t)};
       T d[3];
-      Pos3<P>::sep(k, key, a, pt.key[t], b, d);
+      if constexpr (Prec<P>::global_pos) {
+        Pos3<P>::sep(k, 0, a, 0, b, d);
+      } else {  // cells next to each other: no division, and the minimum image by one comparison
+        int dc = cc[0] - (ldu(pt.key, t) - base);
+        dc = dc > 1 ? -1 : (dc < -1 ? 1 : dc);
+        d[0] = (T)dc + (a[0] - b[0]);
+        d[1] = (T)-oy + (a[1] - b[1]);
+        d[2] = (T)-oz + (a[2] - b[2]);
+      }
       if (!(d[0] * d[0] + d[1] * d[1] + d[2] * d[2] <= k.dd)) return;
-      const int tid = pt.pid[t];
+      const int tid = ldu(pt.pid, t);
       if (tid > id) ++fwd;
       if (cnt == KMAX) {
         over = true;
@@ -597,35 +714,46 @@ __global__ __launch_bounds__(BLOCK) LBDPS_WAVES8 void k3c_contacts(Parts3<typena
       row[j] = e;
       ++cnt;
     };
-    // The cells of one (y, z) row next to each other in x are one slot range:
-    // away from the x seam, the bounds of all (at most nine) ranges are read
-    // together, then their candidates tested.
+    auto base_of = [&](int oy, int oz) {
+      return (wrap_p(cc[2] + oz, nn[2]) * k.ny + wrap_p(cc[1] + oy, nn[1])) * k.nx;
+    };
+    // The cells of one (y, z) row next to each other in x are one slot range
+    // away from the x seam.  With d <= 1/2 at most one side per axis is near, so
+    // there are at most four ranges: their bounds are read together, then their
+    // candidates tested.
     const bool xin = (!use[0][0] || cc[0] >= 1) && (!use[0][2] || cc[0] <= k.nx - 2);
-    if (xin) {
-      int lo[9], hi[9];
+    const bool four = xin && !(use[1][0] && use[1][2]) && !(use[2][0] && use[2][2]);
+    if (four) {
+      const int sy = use[1][0] ? -1 : 1, sz = use[2][0] ? -1 : 1;
+      const bool ny2 = use[1][0] || use[1][2], nz2 = use[2][0] || use[2][2];
+      const int xl = cc[0] - (use[0][0] ? 1 : 0), xh = cc[0] + 1 + (use[0][2] ? 1 : 0);
+      int lo[4], hi[4], base[4];
 #pragma unroll
-      for (int r = 0; r < 9; ++r) {
-        const int oz = r / 3 - 1, oy = r % 3 - 1;
+      for (int r = 0; r < 4; ++r) {
         lo[r] = hi[r] = 0;
-        if (use[2][oz + 1] && use[1][oy + 1]) {
-          const int base = (wrap_p(cc[2] + oz, nn[2]) * k.ny + wrap_p(cc[1] + oy, nn[1])) * k.nx;
-          lo[r] = cs[base + cc[0] - (use[0][0] ? 1 : 0)];
-          hi[r] = cs[base + cc[0] + 1 + (use[0][2] ? 1 : 0)];
+        base[r] = base_of((r & 1) * sy, (r >> 1) * sz);
+        if ((!(r & 1) || ny2) && (!(r >> 1) || nz2)) {
+          lo[r] = ldu(cs, base[r] + xl);
+          hi[r] = ldu(cs, base[r] + xh);
         }
       }
 #pragma unroll
-      for (int r = 0; r < 9; ++r)
-        for (int t = lo[r]; t < hi[r]; ++t) test(t);
+      for (int r = 0; r < 4; ++r)
+        for (int t = lo[r]; t < hi[r]; ++t) test(t, base[r], (r & 1) * sy, (r >> 1) * sz);
     } else {
-      for (int oz = -1; oz <= 1; ++oz) {
-        if (!use[2][oz + 1]) continue;
-        for (int oy = -1; oy <= 1; ++oy) {
-          if (!use[1][oy + 1]) continue;
+      for (int r = 0; r < 9; ++r) {
+        const int oz = r / 3 - 1, oy = r - 3 * (oz + 1) - 1;
+        if (!(oy < 0 ? use[1][0] : (oy > 0 ? use[1][2] : true))) continue;
+        if (!(oz < 0 ? use[2][0] : (oz > 0 ? use[2][2] : true))) continue;
+        const int base = base_of(oy, oz);
+        if (xin) {
+          const int hi = ldu(cs, base + cc[0] + 1 + (use[0][2] ? 1 : 0));
+          for (int t = ldu(cs, base + cc[0] - (use[0][0] ? 1 : 0)); t < hi; ++t) test(t, base, oy, oz);
+        } else {
           for (int ox = -1; ox <= 1; ++ox) {
-            if (!use[0][ox + 1]) continue;
-            const int nb =
-                (wrap_p(cc[2] + oz, nn[2]) * k.ny + wrap_p(cc[1] + oy, nn[1])) * k.nx + wrap_p(cc[0] + ox, nn[0]);
-            for (int t = cs[nb]; t < cs[nb + 1]; ++t) test(t);
+            if (!(ox < 0 ? use[0][0] : (ox > 0 ? use[0][2] : true))) continue;
+            const int nb = base + wrap_p(cc[0] + ox, nn[0]), hi = ldu(cs, nb + 1);
+            for (int t = ldu(cs, nb); t < hi; ++t) test(t, base, oy, oz);
           }
         }
       }
@@ -1011,17 +1139,18 @@ __global__ __launch_bounds__(BLOCK) void k3_cons_final(const double *__restrict_
   if (threadIdx.x == 0) out[7] = *nonfinite ? 1.0 : 0.0;
 }
 
-// A field to FP64: one plane (out[i] = add + a[i]) or three interleaved
-// (out[3 i + q] = plane q).
+// A field to FP64: one plane (out[i] = add + a[i]), or three interleaved
+// (out[3 i + q] = plane q), each value `stride` from the one before.
 template <class T>
 __global__ __launch_bounds__(BLOCK) void k3_get_field(const T *__restrict__ a, const T *__restrict__ b,
-                                                      const T *__restrict__ c, long long n, double *out, double add) {
+                                                      const T *__restrict__ c, int stride, long long n, double *out,
+                                                      double add) {
   const long long i = (long long)blockIdx.x * BLOCK + threadIdx.x;
   if (i >= n) return;
   if (b) {
-    out[3 * i] = (double)a[i];
-    out[3 * i + 1] = (double)b[i];
-    out[3 * i + 2] = (double)c[i];
+    out[3 * i] = (double)a[stride * i];
+    out[3 * i + 1] = (double)b[stride * i];
+    out[3 * i + 2] = (double)c[stride * i];
   } else {
     out[i] = add + (double)a[i];
   }

@@ -126,18 +126,24 @@ template <> struct Prec<PREC_BF16DEV> {
 // populations close to the weights keep their digits in single precision.
 template <int P> constexpr bool kDev = P != PREC_FP64;
 
+template <int P> __device__ __forceinline__ typename Prec<P>::T from_store(typename Prec<P>::S v) {
+  if constexpr (P == PREC_FP64 || P == PREC_FP32) return v;
+  else if constexpr (P == PREC_FP16DEV) return (float)v;
+  else return bf16_to_f32(v);
+}
+template <int P> __device__ __forceinline__ typename Prec<P>::S to_store(typename Prec<P>::T v) {
+  if constexpr (P == PREC_FP64 || P == PREC_FP32) return v;
+  else if constexpr (P == PREC_FP16DEV) return (_Float16)v;  // round to nearest even
+  else return f32_to_bf16(v);
+}
 template <int P>
 __device__ __forceinline__ typename Prec<P>::T load_v(const typename Prec<P>::S *f, size_t idx) {
-  if constexpr (P == PREC_FP64 || P == PREC_FP32) return f[idx];
-  else if constexpr (P == PREC_FP16DEV) return (float)f[idx];
-  else return bf16_to_f32(f[idx]);
+  return from_store<P>(f[idx]);
 }
 
 template <int P>
 __device__ __forceinline__ void store_v(typename Prec<P>::S *f, size_t idx, typename Prec<P>::T v) {
-  if constexpr (P == PREC_FP64 || P == PREC_FP32) f[idx] = v;
-  else if constexpr (P == PREC_FP16DEV) f[idx] = (_Float16)v;  // round to nearest even
-  else f[idx] = f32_to_bf16(v);
+  f[idx] = to_store<P>(v);
 }
 
 // Population i as FP64 f_i (canonical value).
@@ -209,6 +215,10 @@ template <int P, class T> __device__ __forceinline__ T pw(T a, T e) {
 // particle count and the lattice size at creation).
 template <class T> __device__ __forceinline__ T ldu(const T *base, int i) {
   return *(const T *)((const char *)base + (unsigned)i * (unsigned)sizeof(T));
+}
+
+template <class T> __device__ __forceinline__ void stu(T *base, int i, T v) {
+  *(T *)((char *)base + (unsigned)i * (unsigned)sizeof(T)) = v;
 }
 
 // Particle storage (structure of arrays, one "slot" per particle).

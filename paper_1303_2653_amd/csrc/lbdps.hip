@@ -2077,7 +2077,7 @@ struct lbdps3_ctx {
   long long step = 0;
   double dtau = 0, dd = 0, dmu = 0, dvp = 0, dm = 0, done_e = 0, dfp = 0, dgeff[3]{}, dhalfG[3]{}, dsrc[Q3]{};
   void *f[2]{};
-  void *fld[10]{};  // rho, ugx, ugy, ugz, beta, es, fpx, fpy, fpz, the packed interpolation nodes [C][8]
+  void *fld[7]{};  // rho, beta, fpx, fpy, fpz, the interpolation's records [C][4] of the gas and of beta, grad p
   int32_t *key[2]{}, *pid[2]{};
   void *pos[2][3]{}, *vel[2][3]{};
   int32_t *count = nullptr, *cs = nullptr, *rank = nullptr, *slot = nullptr, *deg = nullptr, *done = nullptr;
@@ -2138,9 +2138,8 @@ size_t carve3(const lbdps3_params &p, long long nmax, char *base, lbdps3_ctx *x)
   const size_t C = (size_t)p.nx * p.ny * p.nz, N = (size_t)std::max(nmax, 1ll);
   auto raw = [&](size_t bytes) { return cv.take<char>(bytes); };
   char *f0 = raw(Q3 * C * sS), *f1 = raw(Q3 * C * sS);
-  char *fl[10];
-  for (int i = 0; i < 9; ++i) fl[i] = raw(C * sT);
-  fl[9] = raw(8 * C * sT);  // packed interpolation nodes
+  char *fl[7];
+  for (int i = 0; i < 7; ++i) fl[i] = raw((i < 5 ? 1 : 4) * C * sT);
   int32_t *key[2], *pid[2];
   char *pos[2][3], *vel[2][3];
   for (int b = 0; b < 2; ++b) {
@@ -2175,7 +2174,7 @@ size_t carve3(const lbdps3_params &p, long long nmax, char *base, lbdps3_ctx *x)
   if (x) {
     x->f[0] = f0;
     x->f[1] = f1;
-    for (int i = 0; i < 10; ++i) x->fld[i] = fl[i];
+    for (int i = 0; i < 7; ++i) x->fld[i] = fl[i];
     for (int b = 0; b < 2; ++b) {
       x->key[b] = key[b];
       x->pid[b] = pid[b];
@@ -2242,6 +2241,8 @@ template <int P> struct Impl3 {
       k.halfG[a] = (T)x->dhalfG[a];
     }
     for (int i = 0; i < Q3; ++i) k.src[i] = (T)x->dsrc[i];
+    k.div_nx = divisor(x->nx);
+    k.div_ny = divisor(x->ny);
     k.flags = x->flags;
     k.spin_limit = 1u << 22;
     return k;
@@ -2251,9 +2252,9 @@ template <int P> struct Impl3 {
                      (T *)x->vel[b][0], (T *)x->vel[b][1], (T *)x->vel[b][2]};
   }
   static Fields3<T> fields(const lbdps3_ctx *x) {
-    T *q[10];
-    for (int i = 0; i < 10; ++i) q[i] = (T *)x->fld[i];
-    return Fields3<T>{q[0], q[1], q[2], q[3], q[4], q[5], q[6], q[7], q[8], q[9]};
+    T *q[5];
+    for (int i = 0; i < 5; ++i) q[i] = (T *)x->fld[i];
+    return Fields3<T>{q[0], q[1], q[2], q[3], q[4], (Node4<T> *)x->fld[5], (Node4<T> *)x->fld[6]};
   }
   static void scan(lbdps3_ctx *x, int32_t *in, long long n, int32_t *out, int zero_in) {
     const int tiles = (int)((n + SCAN_TILE - 1) / SCAN_TILE) + (n == 0);
@@ -2338,10 +2339,10 @@ template <int P> struct Impl3 {
                          (const int32_t *)x->slot, (int)x->n, consts(x), d_pos, d_vel);
     }
   }
-  static void get_field(lbdps3_ctx *x, const void *a, const void *b, const void *c, double *out, double add,
-                        long long n) {
+  static void get_field(lbdps3_ctx *x, const void *a, const void *b, const void *c, int stride, double *out,
+                        double add, long long n) {
     hipLaunchKernelGGL(k3_get_field<T>, dim3(nblocks(n)), dim3(BLOCK), 0, x->stream, (const T *)a, (const T *)b,
-                       (const T *)c, n, out, add);
+                       (const T *)c, stride, n, out, add);
   }
 };
 
@@ -2497,10 +2498,12 @@ lbdps_status lbdps3_get_fields(lbdps3_ctx *x, double *d_rho, double *d_ugas, dou
   lbdps_status st = dispatch3(x, [&](auto impl) {
     using I = decltype(impl);
     const double add = x->prec == PREC_FP64 ? 0.0 : 1.0;  // the deviation modes keep rho - 1
-    if (d_rho) I::get_field(x, x->fld[0], nullptr, nullptr, d_rho, add, x->C);
-    if (d_ugas) I::get_field(x, x->fld[1], x->fld[2], x->fld[3], d_ugas, 0.0, x->C);
-    if (d_beta) I::get_field(x, x->fld[4], nullptr, nullptr, d_beta, 0.0, x->C);
-    if (d_fpg) I::get_field(x, x->fld[6], x->fld[7], x->fld[8], d_fpg, 0.0, x->C);
+    using T = typename I::T;
+    const T *u = (const T *)x->fld[5];
+    if (d_rho) I::get_field(x, x->fld[0], nullptr, nullptr, 1, d_rho, add, x->C);
+    if (d_ugas) I::get_field(x, u, u + 1, u + 2, 4, d_ugas, 0.0, x->C);
+    if (d_beta) I::get_field(x, x->fld[1], nullptr, nullptr, 1, d_beta, 0.0, x->C);
+    if (d_fpg) I::get_field(x, x->fld[2], x->fld[3], x->fld[4], 1, d_fpg, 0.0, x->C);
     if (d_ncell)
       (void)check_hip(hipMemcpyAsync(d_ncell, x->dg_n, (size_t)x->C * 4, hipMemcpyDeviceToDevice, x->stream),
                       "lbdps3_get_fields");
@@ -2516,8 +2519,8 @@ lbdps_status lbdps3_get_drag(lbdps3_ctx *x, double *d_fd, double *d_acc) {
   if (x->n > 0) {
     lbdps_status st = dispatch3(x, [&](auto impl) {
       using I = decltype(impl);
-      if (d_fd) I::get_field(x, x->dg_fd, nullptr, nullptr, d_fd, 0.0, 3 * x->n);
-      if (d_acc) I::get_field(x, x->dg_acc, nullptr, nullptr, d_acc, 0.0, 3 * x->n);
+      if (d_fd) I::get_field(x, x->dg_fd, nullptr, nullptr, 1, d_fd, 0.0, 3 * x->n);
+      if (d_acc) I::get_field(x, x->dg_acc, nullptr, nullptr, 1, d_acc, 0.0, 3 * x->n);
       return launch_status("lbdps3_get_drag");
     });
     if (st != LBDPS_OK) return st;
