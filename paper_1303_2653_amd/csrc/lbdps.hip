@@ -98,22 +98,21 @@ int cluster_blocks(long long n, int lists = RC_LISTS, int groups_max = RC_GROUPS
 // lattice if the bed fills it, and denser in a lattice much taller than the bed;
 // hence the floor under a single bed's density, as a 2-D solid fraction.  A
 // patch denser than assumed goes in bands of rows, one after the other, and
-// leaves more: a bed of fraction 0.4 in 486 x 2072 cells, 276 000 spheres, takes
-// 145 us with no floor, 84 with 0.4 (and 1 300 where the final workgroup got
-// what two passes had left).  A patch sparser than assumed costs its fixed part:
+// leaves more: the three kernels take 230 us with no floor and 84 with 0.4 on a
+// bed of fraction 0.4 in 486 x 2072 cells, 276 000 spheres.  A patch sparser than assumed costs its fixed part:
 // the first pass over 64 beds of 0.05 to 0.4, 4.2 M spheres, takes 174 us with no
 // floor and 235 with 0.4.  In a batch the workgroups of other beds hide the
 // bands, so its beds go by the mean, and aim higher (1 % of a step).
 constexpr double PATCH_AIM = 210.0, PATCH_AIM_BATCH = 235.0, PATCH_DENSE = 2.4;
-constexpr double PATCH_FRACTION0 = 0.35, PATCH_FRACTION = 0.4;  // floors of the first pass and of the later ones
+constexpr double PATCH_FRACTION = 0.4;
 constexpr int PATCH_AREA_MIN = 16, PATCH_AREA_MAX = 1024;
-double patch_density(const lbdps_params &p, long long n, double fraction) {  // particles per cell where they are
+double patch_density(const lbdps_params &p, long long n, bool batch) {  // particles per cell where they are
   const bool even = p.bc[2] == BC_PERIODIC || p.particles_periodic_y;
   const double mean = std::max((double)n, 1.0) / ((double)p.nx * p.ny);
-  return even ? mean : std::max(PATCH_DENSE * mean, fraction / (kPi * p.d_p * p.d_p / 4.0));
+  return even ? mean : std::max(PATCH_DENSE * mean, batch ? 0.0 : PATCH_FRACTION / (kPi * p.d_p * p.d_p / 4.0));
 }
 PatchGrid patch_grid(const lbdps_params &p, long long n, int pass, int beds = 1) {
-  const double dens = patch_density(p, n, beds > 1 ? 0.0 : (pass ? PATCH_FRACTION : PATCH_FRACTION0));
+  const double dens = patch_density(p, n, beds > 1);
   const double touch = 1.0 - std::exp(-kPi * p.d_p * p.d_p * dens);
   const double held = std::min((beds > 1 ? PATCH_AIM_BATCH : PATCH_AIM) / std::max(touch, 1e-3), 0.94 * PATCH_HELD0);
   const double area = std::min(std::max(held / dens, (double)PATCH_AREA_MIN), (double)PATCH_AREA_MAX);
@@ -133,14 +132,21 @@ PatchGrid patch_grid(const lbdps_params &p, long long n, int pass, int beds = 1)
 // many as leave it about PATCH_LEFT particles.  With kappa contacts per particle,
 // about a share 0.053 kappa of the particles with contacts is left after one
 // pass (0.04 measured at kappa 0.75, 0.09 at 1.6), 0.001 and 0.007 after two;
-// from about kappa 1.75 on contacts may percolate.  A batch makes the second
-// pass for some bed anyway, so all of its beds take both.
+// from about kappa 1.75 on contacts may percolate.
 constexpr double PATCH_LEFT = 2500.0;
 constexpr int PATCH_WHOLE = 2048;
-int patch_passes(const lbdps_params &p, long long n, int beds = 1) {
+int patch_passes(const lbdps_params &p, long long n) {
   if (n <= PATCH_WHOLE) return 0;
-  const double kappa = kPi * p.d_p * p.d_p * patch_density(p, n, PATCH_FRACTION);
-  return beds == 1 && (1.0 - std::exp(-kappa)) * (double)n * 0.053 * kappa <= PATCH_LEFT && kappa < 1.75 ? 1 : 2;
+  const double kappa = kPi * p.d_p * p.d_p * patch_density(p, n, false);
+  return (1.0 - std::exp(-kappa)) * (double)n * 0.053 * kappa <= PATCH_LEFT && kappa < 1.75 ? 1 : 2;
+}
+// The beds of a batch take as many passes as the one that needs the most, since
+// the launch is there; the final workgroups run side by side, so a bed may leave
+// as many as one holds.
+constexpr double PATCH_LEFT_BATCH = 0.85 * FINAL_CAP;
+int patch_passes_batch(const lbdps_params &p, long long n) {
+  const double kappa = kPi * p.d_p * p.d_p * patch_density(p, n, true);
+  return n <= PATCH_WHOLE ? 0 : ((1.0 - std::exp(-kappa)) * (double)n * 0.053 * kappa <= PATCH_LEFT_BATCH ? 1 : 2);
 }
 int rest_blocks(const lbdps_params &p, long long n, int passes, int beds = 1) {  // of one bed of `beds`
   return passes > 0 ? std::max(1, std::min(patch_grid(p, n, passes, beds).count(), REST_BLOCKS / beds)) : 1;
@@ -1550,6 +1556,7 @@ struct lbdps_batch {
   bool tab_inflight = false;
   int total[2][PH_COUNT]{};
   int tile[2]{};  // drag tile shape each table was written for
+  int most[2]{};  // patch passes of its beds with the most of them
   // bed state the graph's table describes
   std::vector<int> snap_cf, snap_cp;
   std::vector<long long> snap_n;
@@ -1585,7 +1592,16 @@ template <int P> struct BatchImpl {
   static size_t args_bytes(int nbeds) { return align256((size_t)nbeds * sizeof(BedArgs<P>)); }
   static size_t table_bytes(int nbeds) { return args_bytes(nbeds) + align256((size_t)PH_COUNT * (nbeds + 1) * 4); }
 
-  static BedArgs<P> args(const lbdps_ctx *x, int nbeds) {
+  // Patch passes of bed x in a batch whose beds take at most `most`.
+  static int bed_passes(const lbdps_ctx *x, int nbeds, int most) {
+    return nbeds == 1 ? patch_passes(x->p, x->n) : (x->n <= PATCH_WHOLE ? 0 : most);
+  }
+  static int most_passes(const lbdps_batch *B) {
+    int m = 0;
+    for (const auto *x : B->beds) m = std::max(m, patch_passes_batch(x->p, x->n));
+    return m;
+  }
+  static BedArgs<P> args(const lbdps_ctx *x, int nbeds, int most) {
     BedArgs<P> a{};
     a.k = I::consts(x);
     for (int b = 0; b < 2; ++b) {
@@ -1615,7 +1631,7 @@ template <int P> struct BatchImpl {
     a.cf = x->cf;
     a.cp = x->cp;
     a.cp_moves = x->n > 0;
-    a.npass = patch_passes(x->p, x->n, nbeds);
+    a.npass = bed_passes(x, nbeds, most);
     for (int i = 0; i <= PATCH_PASSES; ++i) {
       if (i < PATCH_PASSES) a.pg[i] = patch_grid(x->p, x->n, i, nbeds);
       a.pcoll_part[i] = x->pcoll_part[i];
@@ -1625,8 +1641,8 @@ template <int P> struct BatchImpl {
   }
 
   // Workgroups of each phase for one bed, as the single-bed step launches
-  // them, in a batch of nbeds; the drag under the batch's tile shape `tile`.
-  static void blocks(const lbdps_ctx *x, int nbeds, int tile, int nb[PH_COUNT]) {
+  // them, in a batch of nbeds and at most `most` patch passes; the drag under the batch's tile shape `tile`.
+  static void blocks(const lbdps_ctx *x, int nbeds, int most, int tile, int nb[PH_COUNT]) {
     for (int i = 0; i < PH_COUNT; ++i) nb[i] = 0;
     nb[PH_COLLIDE] = nblocks(x->C);
     if (x->n == 0) return;
@@ -1634,7 +1650,7 @@ template <int P> struct BatchImpl {
     nb[PH_SCAN] = x->ntiles;
     nb[PH_SCATTER] = nblocks(x->n);
     nb[PH_CONTACTS] = nblocks(x->n);
-    const int np = patch_passes(x->p, x->n, nbeds);
+    const int np = bed_passes(x, nbeds, most);
     for (int i = 0; i < np; ++i) nb[PH_PATCH0 + i] = patch_grid(x->p, x->n, i, nbeds).count();
     nb[PH_REST] = rest_blocks(x->p, x->n, np, nbeds);
   }
@@ -1657,11 +1673,12 @@ template <int P> struct BatchImpl {
       if (B->beds[b]->tune.drag_tile != tile)
         return fail(LBDPS_E_INVALID, "the beds of a batch must share one drag tile shape");
     B->tile[t] = tile;
+    const int most = B->most[t] = most_passes(B);
     for (int b = 0; b < B->nbeds; ++b) {
       const lbdps_ctx *x = B->beds[b];
-      a[b] = args(x, B->nbeds);
+      a[b] = args(x, B->nbeds, most);
       int nb[PH_COUNT];
-      blocks(x, B->nbeds, tile, nb);
+      blocks(x, B->nbeds, most, tile, nb);
       for (int ph = 0; ph < PH_COUNT; ++ph) {
         const long long v = (long long)off[ph * nb1 + b] + nb[ph];
         if (v > 0x7fffffffll) return fail(LBDPS_E_SHAPE, "batch too large for one launch per phase");
@@ -1749,10 +1766,10 @@ template <int P> struct BatchImpl {
     }
   }
 
-  static void advance(lbdps_batch *B, int nsteps) {
+  static void advance(lbdps_batch *B, int t, int nsteps) {
     for (auto *x : B->beds) {
       x->sphere_tiles = 0;  // the batched collision stage takes the patches
-      if (x->n > 0) x->passes = patch_passes(x->p, x->n, B->nbeds);
+      if (x->n > 0) x->passes = bed_passes(x, B->nbeds, B->most[t]);
       x->stage_beds = B->nbeds;
       x->cf ^= nsteps & 1;
       if (x->n > 0) x->cp ^= nsteps & 1;
@@ -1771,7 +1788,7 @@ template <int P> struct BatchImpl {
     lbdps_status st = write_table(B, 0);
     if (st != LBDPS_OK) return st;
     launch_steps(B, 0, nsteps);
-    advance(B, nsteps);
+    advance(B, 0, nsteps);
     return launch_status("lbdps_batch_step");
   }
 
@@ -1933,7 +1950,7 @@ lbdps_status lbdps_batch_launch(lbdps_batch *B) {
   lbdps_status st = check_hip(hipGraphLaunch(B->exec, B->stream), "lbdps_batch_launch");
   if (st != LBDPS_OK) return st;
   return dispatch_batch(B->prec, [&](auto impl) {
-    decltype(impl)::advance(B, B->graph_steps);
+    decltype(impl)::advance(B, 1, B->graph_steps);
     return LBDPS_OK;
   });
 }
