@@ -1047,21 +1047,27 @@ template <int P>
 __global__ __launch_bounds__(BLOCK) void k3_set_f(const double *__restrict__ fin, typename Prec<P>::S *__restrict__ f,
                                                   int C) {
   using T = typename Prec<P>::T;
-  const long long e = (long long)blockIdx.x * BLOCK + threadIdx.x;
-  if (e >= (long long)Q3 * C) return;
-  const int i = (int)(e / C);
-  const double v = fin ? fin[e] : w3<double>(i);
-  if constexpr (P == PREC_FP64) f[e] = v;
-  else store_v<P>(f, (size_t)e, (T)(v - w3<double>(i)));
+  const int i = blockIdx.y;
+  const size_t at = (size_t)i * C;
+  layout_cells(
+      C, [&](int c) { return fin ? fin[at + c] : w3<double>(i); },
+      [&](int c, double v) {
+        if constexpr (P == PREC_FP64) f[at + c] = v;
+        else f[at + c] = to_store<P>((T)(v - w3<double>(i)));
+      });
 }
 
 template <int P>
 __global__ __launch_bounds__(BLOCK) void k3_get_f(const typename Prec<P>::S *__restrict__ f, double *__restrict__ out,
                                                   int C) {
-  const long long e = (long long)blockIdx.x * BLOCK + threadIdx.x;
-  if (e >= (long long)Q3 * C) return;
-  if constexpr (P == PREC_FP64) out[e] = f[e];
-  else out[e] = w3<double>((int)(e / C)) + (double)load_v<P>(f, (size_t)e);
+  const int i = blockIdx.y;
+  const size_t at = (size_t)i * C;
+  layout_cells(
+      C, [&](int c) { return f[at + c]; },
+      [&](int c, typename Prec<P>::S v) {
+        if constexpr (P == PREC_FP64) out[at + c] = v;
+        else out[at + c] = w3<double>(i) + (double)from_store<P>(v);
+      });
 }
 
 // ---------------------------------------------------------------- FP64 conservation sums (fixed-order reductions)

@@ -99,10 +99,11 @@ int cluster_blocks(long long n, int lists = RC_LISTS, int groups_max = RC_GROUPS
 // hence the floor under a single bed's density, as a 2-D solid fraction.  A
 // patch denser than assumed goes in bands of rows, one after the other, and
 // leaves more: the three kernels take 230 us with no floor and 84 with 0.4 on a
-// bed of fraction 0.4 in 486 x 2072 cells, 276 000 spheres.  A patch sparser than assumed costs its fixed part:
-// the first pass over 64 beds of 0.05 to 0.4, 4.2 M spheres, takes 174 us with no
-// floor and 235 with 0.4.  In a batch the workgroups of other beds hide the
-// bands, so its beds go by the mean, and aim higher (1 % of a step).
+// bed of fraction 0.4 in 486 x 2072 cells, 276 000 spheres.  A patch sparser than
+// assumed costs its fixed part: the first pass over 64 beds of 0.05 to 0.4, 4.2 M
+// spheres, takes 174 us with no floor and 235 with 0.4.  In a batch the
+// workgroups of other beds hide the bands, so its beds go by the mean, and aim
+// higher (1 % of a step).
 constexpr double PATCH_AIM = 210.0, PATCH_AIM_BATCH = 235.0, PATCH_DENSE = 2.4;
 constexpr double PATCH_FRACTION = 0.4;
 constexpr int PATCH_AREA_MIN = 16, PATCH_AREA_MAX = 1024;
@@ -812,8 +813,7 @@ template <int P> struct Impl {
 
   static lbdps_status set_state(lbdps_ctx *x, const double *d_f, const double *d_pos, const double *d_vel,
                                 long long n) {
-    const long long e = (long long)Q * x->C;
-    hipLaunchKernelGGL(k_set_f<P>, dim3((unsigned)((e + BLOCK - 1) / BLOCK)), dim3(BLOCK), 0, x->stream, d_f,
+    hipLaunchKernelGGL(k_set_f<P>, layout_grid(x->C, Q), dim3(BLOCK), 0, x->stream, d_f,
                        (S *)x->f[x->cf], x->C);
     x->n = n;
     const Consts<T> k = consts(x);
@@ -846,8 +846,7 @@ template <int P> struct Impl {
   }
 
   static void get_f(lbdps_ctx *x, double *out) {
-    const long long e = (long long)Q * x->C;
-    hipLaunchKernelGGL(k_get_f<P>, dim3((unsigned)((e + BLOCK - 1) / BLOCK)), dim3(BLOCK), 0, x->stream,
+    hipLaunchKernelGGL(k_get_f<P>, layout_grid(x->C, Q), dim3(BLOCK), 0, x->stream,
                        (const S *)x->f[x->cf], out, x->C);
   }
 
@@ -2331,8 +2330,7 @@ template <int P> struct Impl3 {
   }
   static lbdps_status set_state(lbdps3_ctx *x, const double *d_f, const double *d_pos, const double *d_vel,
                                 long long n) {
-    const long long e = (long long)Q3 * x->C;
-    hipLaunchKernelGGL(k3_set_f<P>, dim3((unsigned)((e + BLOCK - 1) / BLOCK)), dim3(BLOCK), 0, x->stream, d_f,
+    hipLaunchKernelGGL(k3_set_f<P>, layout_grid(x->C, Q3), dim3(BLOCK), 0, x->stream, d_f,
                        (S *)x->f[x->cf], x->C);
     x->n = n;
     const Consts3<T> k = consts(x);
@@ -2346,9 +2344,8 @@ template <int P> struct Impl3 {
     return launch_status("lbdps3_set_state");
   }
   static void get_state(lbdps3_ctx *x, double *d_f, double *d_pos, double *d_vel) {
-    const long long e = (long long)Q3 * x->C;
     if (d_f)
-      hipLaunchKernelGGL(k3_get_f<P>, dim3((unsigned)((e + BLOCK - 1) / BLOCK)), dim3(BLOCK), 0, x->stream,
+      hipLaunchKernelGGL(k3_get_f<P>, layout_grid(x->C, Q3), dim3(BLOCK), 0, x->stream,
                          (const S *)x->f[x->cf], d_f, x->C);
     if (x->n > 0 && (d_pos || d_vel)) {
       if (!x->bins_valid) sort(x, false);
