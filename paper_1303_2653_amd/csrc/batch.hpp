@@ -29,6 +29,7 @@ template <int P> struct BedArgs {
   long long *pair_part, *wall0_part;
   PatchGrid pg[PATCH_PASSES];
   int npass;  // patch passes of this bed before the rest; 0: the whole bed in the final workgroup
+  int listed;  // the first pass lists what it leaves
   int32_t *pcoll_part[PATCH_PASSES + 1], *pwall_part[PATCH_PASSES + 1];
   TileSums ts;
   int cf;        // population buffer holding the state when the table was written
@@ -117,9 +118,17 @@ __global__ __launch_bounds__(BLOCK) void kb_patches(const BedArgs<P> *__restrict
   LBDPS_BED_PROLOGUE(XCD_RUN_PATCHES)
   __shared__ PatchLds<typename Prec<P>::T, BLOCK, HELD> S;
   (void)nbk;
-  patches_body<P, BLOCK, HELD, FIRST>(S, bid, a.parts(1 - cp), a.cs, a.k, a.adj, a.deg, a.pg[pass], pass + 1 == a.npass,
-                                   a.rest.left, a.rest.place_of, a.rest.sweep + SW_LEFT, a.pcoll_part[pass],
-                                   a.pwall_part[pass]);
+  // Listed: every pass lists what it leaves, and the second does its work only
+  // where the final workgroup could not hold the first's rest.
+  const bool second = !FIRST && a.listed;
+  if (second && a.rest.sweep[SW_LEFT] <= FINAL_CAP) {  // uniform
+    if (threadIdx.x == 0) a.pcoll_part[pass][bid] = a.pwall_part[pass][bid] = 0;
+    return;
+  }
+  patches_body<P, BLOCK, HELD, FIRST>(S, bid, a.parts(1 - cp), a.cs, a.k, a.adj, a.deg, a.pg[pass],
+                                      a.listed || pass + 1 == a.npass, second ? a.rest.left2 : a.rest.left,
+                                      a.rest.place_of, a.rest.sweep + (second ? SW_LEFT2 : SW_LEFT),
+                                      a.pcoll_part[pass], a.pwall_part[pass]);
 }
 
 template <int P>
@@ -127,7 +136,7 @@ __global__ __launch_bounds__(FINAL_THREADS) void kb_rest(const BedArgs<P> *__res
                                                          const int *__restrict__ off, int nbeds, int flip) {
   LBDPS_BED_PROLOGUE(-1)
   const int np = a.npass;
-  rest_body<P>(bid, nbk, a.parts(1 - cp), a.cs, a.k, a.adj, a.deg, np == 0, a.pg[np], a.rest, a.pcoll_part[np],
+  rest_body<P>(bid, nbk, a.listed && np == 2, a.parts(1 - cp), a.cs, a.k, a.adj, a.deg, np == 0, a.pg[np], a.rest, a.pcoll_part[np],
                a.pwall_part[np], a.pcoll_part[PATCH_PASSES], a.pwall_part[PATCH_PASSES]);
 }
 

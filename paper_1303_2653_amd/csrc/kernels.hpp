@@ -326,9 +326,9 @@ constexpr int RES_ITEMS = 8;                  // particle indices per lane and r
 constexpr int DONE_WHOLE = 1 << 30;
 constexpr int RES_CHUNK = BLOCK * RES_ITEMS;  // particle indices per chunk
 // The collision stage's counters: whether the ordered sweep has to run, the
-// tile kernel's candidate roots, the particles the patches left before and in
-// the last pass, and that pass's workgroups that have ended.
-enum { SW_NEED = 0, SW_ROOTS, SW_LEFT, SW_LEFT2, SW_ENDED, SW_COUNT };
+// tile kernel's candidate roots, the particles the patches left in up to three
+// passes that list them, and the workgroups of the last pass that have ended.
+enum { SW_NEED = 0, SW_ROOTS, SW_LEFT, SW_LEFT2, SW_LEFT3, SW_ENDED, SW_COUNT };
 
 // Block-wide exclusive scan of one int per thread; total = block sum.
 __device__ __forceinline__ int block_excl_scan(int v, int *sh, int &total) {

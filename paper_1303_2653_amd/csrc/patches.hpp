@@ -682,11 +682,11 @@ __device__ __forceinline__ void final_body(FinalLds<P> &S, Parts<typename Prec<P
 constexpr int REST_BLOCKS = 256;
 struct RestBuffers {
   int32_t *left, *left2, *place_of;
-  int32_t *sweep;  // SW_LEFT, SW_LEFT2, SW_ENDED
+  int32_t *sweep;  // SW_LEFT to SW_LEFT3, SW_ENDED
   FinalMem mem;
 };
 template <int P>
-__device__ __forceinline__ void rest_body(const int bidx, const int gdim, Parts<typename Prec<P>::T> pt,
+__device__ __forceinline__ void rest_body(const int bidx, const int gdim, const bool listed, Parts<typename Prec<P>::T> pt,
     const int32_t *__restrict__ cs, const Consts<typename Prec<P>::T> &k, Adj adj, int32_t *deg, const bool whole,
     const PatchGrid g, const RestBuffers R, int32_t *__restrict__ pass_coll, int32_t *__restrict__ pass_wall,
     int32_t *__restrict__ coll_part, int32_t *__restrict__ wall_part) {
@@ -696,17 +696,24 @@ __device__ __forceinline__ void rest_body(const int bidx, const int gdim, Parts<
   } U;
   __shared__ int ended;
   int n = 0;
-  int32_t *left = R.left;
+  int32_t *left = R.left, *next = R.left2;
   if (!whole) {
     n = R.sweep[SW_LEFT];
+    int at = SW_LEFT2;
+    if (listed && n > FINAL_CAP) {  // the second pass was needed
+      n = R.sweep[SW_LEFT2];
+      at = SW_LEFT3;
+      left = R.left2;
+      next = R.left;
+    }
     if (n <= FINAL_CAP) {  // uniform over the launch
       for (int i = bidx * FINAL_THREADS + (int)threadIdx.x; i < g.count(); i += gdim * FINAL_THREADS)
         pass_coll[i] = pass_wall[i] = 0;
       if (bidx != 0) return;
     } else {
       for (int i = bidx; i < g.count(); i += gdim) {
-        patches_body<P, PATCH_WIDE, PATCH_HELD2, false>(U.patch, i, pt, cs, k, adj, deg, g, true, R.left2,
-                                                        R.place_of, R.sweep + SW_LEFT2, pass_coll, pass_wall);
+        patches_body<P, PATCH_WIDE, PATCH_HELD2, false>(U.patch, i, pt, cs, k, adj, deg, g, true, next,
+                                                        R.place_of, R.sweep + at, pass_coll, pass_wall);
         __syncthreads();
       }
       __threadfence();
@@ -715,8 +722,8 @@ __device__ __forceinline__ void rest_body(const int bidx, const int gdim, Parts<
       __syncthreads();
       if (ended != gdim - 1) return;  // uniform
       __threadfence();
-      n = __hip_atomic_load(&R.sweep[SW_LEFT2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      left = R.left2;
+      n = __hip_atomic_load(&R.sweep[at], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      left = next;
     }
   }
   final_body<P>(U.fin, pt, k, adj, deg, whole, left, R.place_of, n, R.mem, coll_part, wall_part);
@@ -728,7 +735,7 @@ __global__ __launch_bounds__(FINAL_THREADS) void k_rest(Parts<typename Prec<P>::
                                                         int32_t *__restrict__ pass_wall,
                                                         int32_t *__restrict__ coll_part,
                                                         int32_t *__restrict__ wall_part) {
-  rest_body<P>(blockIdx.x, gridDim.x, pt, cs, k, adj, deg, !PASSES, g, R, pass_coll, pass_wall, coll_part,
+  rest_body<P>(blockIdx.x, gridDim.x, false, pt, cs, k, adj, deg, !PASSES, g, R, pass_coll, pass_wall, coll_part,
                wall_part);
 }
 

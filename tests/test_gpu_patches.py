@@ -90,3 +90,38 @@ def test_collision_stage(name):
             assert (c["pairs"], c["collisions"], c["walls"]) == want, (name, prec, again, c, want)
             assert np.array_equal(got, ref.astype(np.float64)), (name, prec, again)
         gpu.close()
+
+
+def batch_beds(kind, prec):
+    """Beds for each way a batch can go through the patches."""
+    t, small = synth.tiny, dict(bc=PER, g=(0.0, 0.0), vel_scale=5e-3)
+    beds = [t(nx=48, ny=50, n=2600, seed=21, **small), t(nx=30, ny=31, n=700, seed=22, **small),
+            t(nx=90, ny=40, n=2049, seed=23, **small), t(nx=33, ny=70, n=3000, seed=24, **small)]
+    if kind == "second-pass-for-one":  # a quarter of the beds leaves more than the final workgroup holds
+        beds[0] = t(nx=180, ny=160, n=60_000, seed=25, **small)
+    if kind == "second-pass-for-most":
+        beds[0] = t(nx=180, ny=160, n=60_000, seed=25, **small)
+        beds[2] = t(nx=140, ny=150, n=50_000, seed=26, **small)
+    if kind == "percolating":  # and more than the final workgroup holds after the second
+        beds[0] = t(nx=100, ny=100, n=46_000, seed=27, **small)
+    for b in beds:
+        b["precision"] = prec
+    return beds
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("kind", ["first-pass-only", "second-pass-for-one", "second-pass-for-most", "percolating"])
+def test_batch_takes_the_same_course(kind, prec):
+    """A batch against the same beds alone, bit for bit, with its counters."""
+    cfgs = batch_beds(kind, prec)
+    print("batch", kind, prec, [len(c["pos"]) for c in cfgs], flush=True)
+    batch = L.Batch(cfgs)
+    batch.step(2)
+    for i, c in enumerate(cfgs):
+        one = L.Sim(c, precision=prec)
+        one.step(2)
+        a, b = batch.beds[i], one
+        for x, y in zip(a.state()[:3], b.state()[:3]):
+            assert np.array_equal(x, y), (kind, prec, i)
+        assert a.counters() == b.counters(), (kind, prec, i)
+        one.close()
