@@ -136,8 +136,8 @@ __global__ __launch_bounds__(FINAL_THREADS) void kb_rest(const BedArgs<P> *__res
                                                          const int *__restrict__ off, int nbeds, int flip) {
   LBDPS_BED_PROLOGUE(-1)
   const int np = a.npass;
-  rest_body<P>(bid, nbk, a.listed && np == 2, a.parts(1 - cp), a.cs, a.k, a.adj, a.deg, np == 0, a.pg[np], a.rest, a.pcoll_part[np],
-               a.pwall_part[np], a.pcoll_part[PATCH_PASSES], a.pwall_part[PATCH_PASSES]);
+  rest_body<P>(bid, nbk, a.listed && np == 2, a.parts(1 - cp), a.cs, a.k, a.adj, a.deg, np == 0, a.pg[np], a.rest,
+               a.pcoll_part[np], a.pwall_part[np], a.pcoll_part[PATCH_PASSES], a.pwall_part[PATCH_PASSES]);
 }
 
 #undef LBDPS_BED_PROLOGUE

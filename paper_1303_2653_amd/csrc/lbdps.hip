@@ -735,7 +735,8 @@ template <int P> struct Impl {
                   x->pcoll_part[i], x->pwall_part[i]);
       }
       const PatchGrid g = patch_grid(x->p, x->n, np);
-      tlaunch_n(x, LBDPS_K_RESOLVE, extra || np > 0, np > 0 ? k_rest<P, true> : k_rest<P, false>, dim3(rest_blocks(x->p, x->n, np)), dim3(FINAL_THREADS),
+      tlaunch_n(x, LBDPS_K_RESOLVE, extra || np > 0, np > 0 ? k_rest<P, true> : k_rest<P, false>,
+                dim3(rest_blocks(x->p, x->n, np)), dim3(FINAL_THREADS),
                 parts(x, x->cp), (const int32_t *)x->cs, k, x->adj(), x->deg, g, x->rest(),
                 x->pcoll_part[np], x->pwall_part[np], x->pcoll_part[PATCH_PASSES], x->pwall_part[PATCH_PASSES]);
     }

@@ -107,7 +107,8 @@ template <class T, int NT, int HELD> struct PatchLds {
 };
 
 template <int P, int NT, int HELD, bool FIRST>
-__device__ __forceinline__ void patches_body(PatchLds<typename Prec<P>::T, NT, HELD> &S, const int bidx, Parts<typename Prec<P>::T> pt,
+__device__ __forceinline__ void patches_body(PatchLds<typename Prec<P>::T, NT, HELD> &S, const int bidx,
+    Parts<typename Prec<P>::T> pt,
     const int32_t *__restrict__ cs, const Consts<typename Prec<P>::T> &k, Adj adj, int32_t *__restrict__ deg,
     const PatchGrid g, const bool last, int32_t *__restrict__ left, int32_t *__restrict__ place_of,
     int32_t *__restrict__ nleft, int32_t *__restrict__ coll_part, int32_t *__restrict__ wall_part) {
@@ -407,12 +408,12 @@ __global__ __launch_bounds__(BLOCK) void k_patches(Parts<typename Prec<P>::T> pt
 
 // The clusters that are left, of the whole bed in one workgroup, by the same
 // firing rule.  The particles come from the list of the last pass, or, with no
-// pass, from the degrees (a bed of at most FINAL_CAP particles needs no
-// patches); place_of maps a slot to its place among them.  A pair can only become ready when one of the two has just gone on to
-// it, so a particle that goes on wakes itself and its new partner, and a round
-// looks at the awake alone: most wavefronts read one word and meet at the
-// barriers, and a long chain of pairs (150 rounds in a settled bed of 15 000
-// spheres) takes 0.6 us a link.
+// pass, from the degrees (a bed of few particles needs no
+// patches); place_of maps a slot to its place among them.  A pair can only become
+// ready when one of the two has just gone on to it, so a particle that goes on
+// wakes itself and its new partner, and a round looks at the awake alone: most
+// wavefronts read one word and meet at the barriers, and a long chain of pairs
+// (150 rounds in a settled bed of 15 000 spheres) takes 0.6 us a link.
 template <int P> struct FinalLds {
   using T = typename Prec<P>::T;
   T x[FINAL_CAP], y[FINAL_CAP], vx[FINAL_CAP], vy[FINAL_CAP];
@@ -483,7 +484,7 @@ __device__ __forceinline__ void final_lds(FinalLds<P> &S, Parts<typename Prec<P>
   unsigned *const mine = reinterpret_cast<unsigned *>(S.wake + tid * PT);
   *mine = 0x01010101u;
   __syncthreads();
-  // busy[rd]: pairs of this round.  They are dealt to the threads densely, while
+  // busy[rd]: the round's pairs.  They are dealt to the threads densely, while
   // each particle of a pair goes on to its next partner in its own thread.
   for (int rd = 0;; rd = rd == 2 ? 0 : rd + 1) {
     const unsigned awake = *mine;
@@ -686,8 +687,8 @@ struct RestBuffers {
   FinalMem mem;
 };
 template <int P>
-__device__ __forceinline__ void rest_body(const int bidx, const int gdim, const bool listed, Parts<typename Prec<P>::T> pt,
-    const int32_t *__restrict__ cs, const Consts<typename Prec<P>::T> &k, Adj adj, int32_t *deg, const bool whole,
+__device__ __forceinline__ void rest_body(const int bidx, const int gdim, const bool listed,
+    Parts<typename Prec<P>::T> pt, const int32_t *__restrict__ cs, const Consts<typename Prec<P>::T> &k, Adj adj, int32_t *deg, const bool whole,
     const PatchGrid g, const RestBuffers R, int32_t *__restrict__ pass_coll, int32_t *__restrict__ pass_wall,
     int32_t *__restrict__ coll_part, int32_t *__restrict__ wall_part) {
   __shared__ union {
