@@ -133,8 +133,10 @@ PatchGrid patch_grid(const lbdps_params &p, long long n, int pass, int beds = 1)
 // many as leave it about PATCH_LEFT particles.  With kappa contacts per particle,
 // about a share 0.053 kappa of the particles with contacts is left after one
 // pass (0.04 measured at kappa 0.75, 0.09 at 1.6), 0.001 and 0.007 after two;
-// from about kappa 1.75 on contacts may percolate.
-constexpr double PATCH_LEFT = 2500.0;
+// from about kappa 1.75 on contacts may percolate.  With 1 800 left of 509 000
+// spheres in 606 x 2374 cells the rest takes 36 us, against 11 + 8 with a second
+// pass before it.
+constexpr double PATCH_LEFT = 1200.0;
 constexpr int PATCH_WHOLE = 2048;
 int patch_passes(const lbdps_params &p, long long n) {
   if (n <= PATCH_WHOLE) return 0;
