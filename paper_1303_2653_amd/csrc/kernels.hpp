@@ -685,8 +685,11 @@ __global__ __launch_bounds__(BLOCK) void k_collide(const typename Prec<P>::S *__
 
 // One symplectic Euler step of length h = 1 / n_sub of Eq. 16 for the particle
 // in slot s of cell (cx, cy) = c: v <- v + a h, P <- P + v h, then the periodic
-// wrap or wall mirror.  Stores the record and returns the new cell (the old
-// one, with the domain flag raised, if the result is not a valid cell).
+// wrap or wall mirror.  Stores the record and returns the new cell.  If the
+// result is not a valid cell the domain flag is raised, and the particle keeps
+// its cell and its position in it: a position always lies in the cell it is
+// stored with, so contacts are mutual, which the resolution relies on when it
+// follows a row entry to the partner.
 template <int P>
 __device__ __forceinline__ int advance_one(const Consts<typename Prec<P>::T> &k, Parts<typename Prec<P>::T> &pt,
                                            int s, int cx, int cy, int c, typename Prec<P>::T x,
@@ -700,10 +703,11 @@ __device__ __forceinline__ int advance_one(const Consts<typename Prec<P>::T> &k,
   if (nk < 0) {
     atomicOr(&flags[FLAG_DOMAIN], 1);
     nk = c;
+  } else {
+    pt.px[s] = x;
+    pt.py[s] = y;
   }
   pt.key[s] = nk;
-  pt.px[s] = x;
-  pt.py[s] = y;
   pt.vx[s] = vx;
   pt.vy[s] = vy;
   return nk;

@@ -229,12 +229,16 @@ __device__ __forceinline__ void patches_body(PatchLds<typename Prec<P>::T, NT, H
       continue;
     }
     // place of the partner of an entry of a particle in row `row_of`, or
-    // PATCH_NONE if it is outside the band
+    // PATCH_NONE if it is outside the band.  Contacts are mutual, so a partner in
+    // the band has its place in loc; the test against n keeps the access inside
+    // the LDS whatever a row holds.
     auto place = [&](long long e, int row_of) -> int {
       const int rr = row_of + adj_dy(e);
       if (rr < r0 || rr >= r1) return PATCH_NONE;
       const int q = adj_slot(e) - S.rlo[rr], b = S.rbase[rr];
-      return q >= 0 && q < S.rbase[rr + 1] - b ? (int)S.loc[b - base0 + q] : PATCH_NONE;
+      if (q < 0 || q >= S.rbase[rr + 1] - b) return PATCH_NONE;
+      const int c = S.loc[b - base0 + q];
+      return c < n ? c : PATCH_NONE;
     };
     // this thread's particle
     const bool act = tid < n;
@@ -423,6 +427,12 @@ template <int P> struct FinalLds {
   unsigned ready[FINAL_CAP / 2];  // the round's pairs: lower index's place | the other's << 16
 };
 static_assert(FINAL_PT == 4, "a thread's marks are one 32-bit word");
+// Place of an entry's partner: contacts are mutual and whole clusters are left,
+// so it has one; the mask keeps the access inside the LDS whatever a row holds.
+__device__ __forceinline__ int final_place(const int32_t *place_of, long long e) {
+  static_assert((FINAL_CAP & (FINAL_CAP - 1)) == 0 && FINAL_CAP < PATCH_NONE, "a mask of the places");
+  return place_of[adj_slot(e)] & (FINAL_CAP - 1);
+}
 
 // n <= FINAL_CAP particles in LDS, places tid, tid + FINAL_THREADS, ... per thread; the
 // marks of a thread's particles are one word.
@@ -470,13 +480,13 @@ __device__ __forceinline__ void final_lds(FinalLds<P> &S, Parts<typename Prec<P>
       for (int a = 0; a < PATCH_NB; ++a)
         if (a < dg[j]) {
           const long long e = a == 0 ? e0[j] : (a == 1 ? e1[j] : row[a]);
-          nb[j].set(a, place_of[adj_slot(e)]);
+          nb[j].set(a, final_place(place_of, e));
           low[j] += (int)(e >> 32) < id[j];
         }
       for (int a = PATCH_NB; a < dg[j]; ++a) {  // later partners: their places go into the row itself
         const long long e = row[a];
         low[j] += (int)(e >> 32) < id[j];
-        row[a] = place_of[adj_slot(e)];
+        row[a] = final_place(place_of, e);
       }
       nx[j] = nb[j].get(0);
       S.nxt[at_place(j)] = (unsigned short)nx[j];
@@ -572,7 +582,8 @@ __device__ __forceinline__ void final_mem(const FinalMem M, Parts<typename Prec<
     for (int a = 0; a < dg; ++a) {
       const long long e = row[a];
       low += (int)(e >> 32) < id;
-      row[a] = place_of[adj_slot(e)];  // the row now holds places
+      const int c1 = place_of[adj_slot(e)];
+      row[a] = (unsigned)c1 < (unsigned)n ? c1 : -1;  // the row now holds places
     }
     M.state[c] = dg << 8 | low << 16;
     M.next[c] = (int)row[0];
