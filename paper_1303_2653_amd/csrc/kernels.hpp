@@ -703,11 +703,12 @@ __device__ __forceinline__ int advance_one(const Consts<typename Prec<P>::T> &k,
   if (nk < 0) {
     atomicOr(&flags[FLAG_DOMAIN], 1);
     nk = c;
-  } else {
-    pt.px[s] = x;
-    pt.py[s] = y;
+    x = pt.px[s];
+    y = pt.py[s];
   }
   pt.key[s] = nk;
+  pt.px[s] = x;
+  pt.py[s] = y;
   pt.vx[s] = vx;
   pt.vy[s] = vy;
   return nk;
