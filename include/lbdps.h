@@ -442,6 +442,17 @@ typedef enum {
 lbdps_status lbdps_tile_stats(lbdps_ctx *ctx, int64_t h_out[2]);
 
 /*
+ * The course of the most recent collision stage through the neighbour rows:
+ * h_out[0] = 0 the whole bed in one workgroup, 1 or 2 by patches of cells in as
+ * many passes, 3 by contact clusters, -1 by the tile kernel (the others are 0
+ * then); h_out[1] = particles the patches left to the final workgroup, in a
+ * batch that lists them after the first pass; h_out[2] = those left by the second
+ * pass there; h_out[3] = particles in patches too full to be taken; h_out[4] = 1
+ * if a cluster was too large for the search by clusters.  Synchronises.
+ */
+lbdps_status lbdps_row_stats(lbdps_ctx *ctx, int64_t h_out[5]);
+
+/*
  * Time every later launch of the kernels in `mask` (bit k = lbdps_kernel k):
  * the launch carries a pair of hipEvents that its dispatch stamps at the
  * kernel's start and end (hipExtLaunchKernel), so the time is the kernel's own.
@@ -471,7 +482,7 @@ lbdps_status lbdps_kernel_times(lbdps_ctx *ctx, double *h_ms, int64_t *h_launche
  *                      particles and the ring of cells around it are held in LDS
  *                      (contacts, clusters inside the tile resolved there, the
  *                      rest through neighbour rows): 0 = none, every particle
- *                      through the rows, resolved patch by patch (default),
+ *                      through the rows, by patches of cells or by clusters (default),
  *                      1 = 32 x 8, 2 = 16 x 16, 3 = 64 x 4.  A batched step takes 0.
  * A context starts with the defaults.
  */
@@ -526,7 +537,7 @@ lbdps_status lbdps_batch_create(const lbdps_params *beds, int32_t nbeds, const i
 /* The context of bed `bed` (owned by the batch). */
 lbdps_status lbdps_batch_bed(lbdps_batch *batch, int32_t bed, lbdps_ctx **out);
 
-/* Enqueue nsteps steps of every bed: one launch per phase for the whole batch (6 to 8 per step).
+/* Enqueue nsteps steps of every bed: one launch per phase for the whole batch (6 to 9 per step).
  * Results equal nsteps calls of lbdps_step on each bed, bit for bit. */
 lbdps_status lbdps_batch_step(lbdps_batch *batch, int32_t nsteps);
 

@@ -12,7 +12,7 @@
 
 namespace lbdps {
 
-enum { PH_COLLIDE = 0, PH_DRAG, PH_SCAN, PH_SCATTER, PH_CONTACTS, PH_PATCH0, PH_PATCH1, PH_REST, PH_COUNT };
+enum { PH_COLLIDE = 0, PH_DRAG, PH_SCAN, PH_SCATTER, PH_CONTACTS, PH_PATCH0, PH_PATCH1, PH_CLUSTERS, PH_REST, PH_COUNT };
 
 template <int P> struct BedArgs {
   using T = typename Prec<P>::T;
@@ -28,9 +28,10 @@ template <int P> struct BedArgs {
   Adj adj;
   long long *pair_part, *wall0_part;
   PatchGrid pg[PATCH_PASSES];
-  int npass;  // patch passes of this bed before the rest; 0: the whole bed in the final workgroup
+  int plan;    // PLAN_*
   int listed;  // the first pass lists what it leaves
-  int32_t *pcoll_part[PATCH_PASSES + 1], *pwall_part[PATCH_PASSES + 1];
+  int32_t *pcoll_part[PATCH_PASSES], *pwall_part[PATCH_PASSES];
+  long long *collc_part, *wallc_part;
   TileSums ts;
   int cf;        // population buffer holding the state when the table was written
   int cp;        // particle record set holding the state when the table was written
@@ -116,7 +117,7 @@ template <int P, int HELD, bool FIRST>
 __global__ __launch_bounds__(BLOCK) void kb_patches(const BedArgs<P> *__restrict__ tab, const int *__restrict__ off,
                                                  int nbeds, int flip, int pass) {
   LBDPS_BED_PROLOGUE(XCD_RUN_PATCHES)
-  __shared__ PatchLds<typename Prec<P>::T, BLOCK, HELD> S;
+  __shared__ PatchLds<typename Prec<P>::T, HELD> S;
   (void)nbk;
   // Listed: every pass lists what it leaves, and the second does its work only
   // where the final workgroup could not hold the first's rest.
@@ -125,19 +126,28 @@ __global__ __launch_bounds__(BLOCK) void kb_patches(const BedArgs<P> *__restrict
     if (threadIdx.x == 0) a.pcoll_part[pass][bid] = a.pwall_part[pass][bid] = 0;
     return;
   }
-  patches_body<P, BLOCK, HELD, FIRST>(S, bid, a.parts(1 - cp), a.cs, a.k, a.adj, a.deg, a.pg[pass],
-                                      a.listed || pass + 1 == a.npass, second ? a.rest.left2 : a.rest.left,
+  patches_body<P, HELD, FIRST>(S, bid, a.parts(1 - cp), a.cs, a.k, a.adj, a.deg, a.pg[pass],
+                                      a.listed || pass + 1 == a.plan, second ? a.rest.left2 : a.rest.left,
                                       a.rest.place_of, a.rest.sweep + (second ? SW_LEFT2 : SW_LEFT),
-                                      a.pcoll_part[pass], a.pwall_part[pass]);
+                               a.rest.sweep + SW_FULL, a.pcoll_part[pass], a.pwall_part[pass]);
 }
 
 template <int P>
+__global__ __launch_bounds__(BLOCK) void kb_clusters(const BedArgs<P> *__restrict__ tab, const int *__restrict__ off,
+                                                     int nbeds, int flip) {
+  LBDPS_BED_PROLOGUE(XCD_RUN_CLUSTERS)
+  __shared__ RootsLds<P, 1> S;
+  (void)nbk;
+  clusters_body<P, 1>(S, bid, a.parts(1 - cp), a.k, a.adj, a.deg, a.rest.sweep, a.collc_part, a.wallc_part);
+}
+
+// CLUSTERS: some bed went by clusters.
+template <int P, bool CLUSTERS>
 __global__ __launch_bounds__(FINAL_THREADS) void kb_rest(const BedArgs<P> *__restrict__ tab,
                                                          const int *__restrict__ off, int nbeds, int flip) {
   LBDPS_BED_PROLOGUE(-1)
-  const int np = a.npass;
-  rest_body<P>(bid, nbk, a.listed && np == 2, a.parts(1 - cp), a.cs, a.k, a.adj, a.deg, np == 0, a.pg[np], a.rest,
-               a.pcoll_part[np], a.pwall_part[np], a.pcoll_part[PATCH_PASSES], a.pwall_part[PATCH_PASSES]);
+  rest_body<P, true, CLUSTERS>(bid, nbk, a.plan, a.listed && a.plan == PLAN_TWO_PASSES, a.parts(1 - cp), a.k, a.adj,
+                               a.deg, a.rest);
 }
 
 #undef LBDPS_BED_PROLOGUE

@@ -879,7 +879,7 @@ __global__ __launch_bounds__(BLOCK) void k3c_clusters(Parts3<typename Prec<P>::T
     if ((int)threadIdx.x < nb) pre[threadIdx.x] = o;
     if (threadIdx.x == 0) pre[nb] = tot;
     __syncthreads();
-    const LdsColumn ql{qs + threadIdx.x};
+    const LdsColumn<BLOCK> ql{qs + threadIdx.x};
     for (int f = threadIdx.x; f < tot; f += BLOCK) {
       int lo = 0, hi = nb;  // list j with pre[j] <= f < pre[j + 1]
       while (hi - lo > 1) {

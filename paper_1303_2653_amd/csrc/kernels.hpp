@@ -325,10 +325,16 @@ constexpr int RES_ITEMS = 8;                  // particle indices per lane and r
 // a cluster left to the sweep keeps the plain count of its finished pairs.
 constexpr int DONE_WHOLE = 1 << 30;
 constexpr int RES_CHUNK = BLOCK * RES_ITEMS;  // particle indices per chunk
-// The collision stage's counters: whether the ordered sweep has to run, the
-// tile kernel's candidate roots, the particles the patches left in up to three
-// passes that list them, and the workgroups of the last pass that have ended.
-enum { SW_NEED = 0, SW_ROOTS, SW_LEFT, SW_LEFT2, SW_LEFT3, SW_ENDED, SW_COUNT };
+// Entries of a row of degree dg, which may carry DONE_WHOLE: the row stage marks
+// a resolved particle in its degree.
+__device__ __forceinline__ int row_length(int dg) { return min(dg & ~DONE_WHOLE, KMAX); }
+// The collision stage's counters: whether the ordered sweep has to run and the
+// candidate roots, of the tile stage; of the row stage, the particles listed by
+// the first and the second patch pass, those in patches too full for the first,
+// whether the cluster search left any cluster
+// to the final workgroup, the particles listed for that, and the workgroups of
+// the rest that have ended.
+enum { SW_NEED = 0, SW_ROOTS, SW_LEFT, SW_LEFT2, SW_FULL, SW_MORE, SW_LISTED, SW_ENDED, SW_COUNT };
 
 // Block-wide exclusive scan of one int per thread; total = block sum.
 __device__ __forceinline__ int block_excl_scan(int v, int *sh, int &total) {
@@ -1652,9 +1658,9 @@ constexpr int CL_LDS = 8;
 constexpr int RC_LISTS = 1;           // candidate lists per resolution workgroup (default)
 constexpr int RC_GROUPS_MAX = 1 << 30;  // most resolution workgroups (default: no limit)
 
-struct LdsColumn {  // entry i of a lane's column of a [CL_LDS][BLOCK] LDS array
+template <int NT> struct LdsColumn {  // entry i of a lane's column of a [CL_LDS][NT] LDS array
   long long *p;
-  __device__ long long &operator[](int i) const { return p[i * BLOCK]; }
+  __device__ long long &operator[](int i) const { return p[i * NT]; }
 };
 
 // A gathered member is stored as (index << 32 | pos << 29 | slot): pos is its
@@ -1672,8 +1678,8 @@ __device__ __forceinline__ unsigned long long cl_bit(int a, int b) { return 1ull
 // two at a time, so the rows of both are loaded together.  The members' slots
 // are also kept in registers, where the membership test looks them up.
 template <class Row>
-__device__ __forceinline__ int gather_cluster(Row q, int cap, int s, int g, Adj adj,
-                                              const int32_t *__restrict__ deg, unsigned long long &A) {
+__device__ __forceinline__ int gather_cluster(Row q, int cap, int s, int g, Adj adj, const int32_t *deg,
+                                              unsigned long long &A) {
   q[0] = ((long long)g << 32) | (unsigned)s;
   A = 0;
   int m = 1;
@@ -1688,7 +1694,7 @@ __device__ __forceinline__ int gather_cluster(Row q, int cap, int s, int g, Adj 
         res = 0;
         return false;
       }
-      const int es = (int)(e & 0x1fffffffll);
+      const int es = adj_slot(e);
       int p = -1;
 #pragma unroll
       for (int i = 0; i < CL_LDS; ++i)
@@ -1699,7 +1705,7 @@ __device__ __forceinline__ int gather_cluster(Row q, int cap, int s, int g, Adj 
           return false;
         }
         p = m;
-        q[m] = e | ((long long)m << 29);
+        q[m] = (e & ~0xffffffffll) | ((long long)m << 29) | es;
 #pragma unroll
         for (int i = 1; i < CL_LDS; ++i)
           if (i == m) sl[i] = es;
@@ -1719,7 +1725,7 @@ __device__ __forceinline__ int gather_cluster(Row q, int cap, int s, int g, Adj 
     }
     if (!two) u1 = u0;
     const AdjRow r0 = adj.row(u0), r1 = adj.row(u1);
-    const int d0 = min(ldu(deg, u0), KMAX), d1 = two ? min(ldu(deg, u1), KMAX) : 0;
+    const int d0 = row_length(ldu(deg, u0)), d1 = two ? row_length(ldu(deg, u1)) : 0;
     // the dense parts of both rows
     const Dense4 f(r0.a), h(r1.a);
     int res = 0;
@@ -1880,7 +1886,7 @@ template <int P, int G> struct ClusterLds {
 // exceeds the group's capacity (nothing was changed).
 template <int P, int G>
 __device__ int resolve_group(ClusterLds<P, G> &B, int *shi, int s0, int g, const Consts<typename Prec<P>::T> &k,
-                             Parts<typename Prec<P>::T> &pt, Adj adj, const int32_t *__restrict__ deg, int32_t *done,
+                             Parts<typename Prec<P>::T> &pt, Adj adj, const int32_t *deg, int32_t *done,
                              long long &ncoll, long long &nwall) {
   using T = typename Prec<P>::T;
   using Gr = Group<G>;
@@ -1904,16 +1910,16 @@ __device__ int resolve_group(ClusterLds<P, G> &B, int *shi, int s0, int g, const
     Gr::sync();
     if (stop) break;
     for (int t = h0 + tid; t < h1; t += G) {
-      const int u = (int)(B.q[t] & 0xffffffffll);
+      const int u = adj_slot(B.q[t]);
       const AdjRow ru = adj.row(u);
-      const int du = min(deg[u], KMAX);
+      const int du = row_length(deg[u]);
       for (int a = 0; a < du; ++a) {
         const long long e = ru[a];
         if ((int)(e >> 32) < g) {
           B.notroot = 1;  // a lower index: the cluster belongs to another candidate
           break;
         }
-        const int r = B.insert((int)(e & 0xffffffffll));
+        const int r = B.insert(adj_slot(e));
         if (r < 0) {
           B.over = 1;
           break;
@@ -1949,7 +1955,7 @@ __device__ int resolve_group(ClusterLds<P, G> &B, int *shi, int s0, int g, const
     }
   // member copies, slot -> sorted index, pairs (i, j), i < j, per member
   const bool mem = tid < m;
-  const int u = mem ? (int)(B.q[tid] & 0xffffffffll) : 0;
+  const int u = mem ? adj_slot(B.q[tid]) : 0;
   const int gu = mem ? (int)(B.q[tid] >> 32) : 0;
   int cnt = 0;
   if (mem) {
@@ -1960,7 +1966,7 @@ __device__ int resolve_group(ClusterLds<P, G> &B, int *shi, int s0, int g, const
     B.vx[tid] = pt.vx[u];
     B.vy[tid] = pt.vy[u];
     const AdjRow ru = adj.row(u);
-    const int du = min(deg[u], KMAX);
+    const int du = row_length(deg[u]);
     for (int a = 0; a < du; ++a) cnt += (int)(ru[a] >> 32) > gu;
   }
   int npairs;
@@ -1969,11 +1975,11 @@ __device__ int resolve_group(ClusterLds<P, G> &B, int *shi, int s0, int g, const
   Gr::sync();  // every member's slot -> index entry is written
   if (mem) {
     const AdjRow ru = adj.row(u);
-    const int du = min(deg[u], KMAX);
+    const int du = row_length(deg[u]);
     int w = off;
     for (int a = 0; a < du; ++a) {
       const long long e = ru[a];
-      if ((int)(e >> 32) > gu) B.pairs[w++] = ((unsigned)tid << 16) | (unsigned)B.hidx[B.find((int)(e & 0xffffffffll))];
+      if ((int)(e >> 32) > gu) B.pairs[w++] = ((unsigned)tid << 16) | (unsigned)B.hidx[B.find(adj_slot(e))];
     }
   }
   Gr::sync();
@@ -2005,88 +2011,99 @@ __device__ int resolve_group(ClusterLds<P, G> &B, int *shi, int s0, int g, const
   return 0;
 }
 
+// Resolves the clusters of `tot` candidate roots, cand(f) = (index << 32 | slot),
+// dealt to the lanes of a workgroup of NT threads; up to BIG of them that a lane
+// cannot hold are queued for the wavefronts and, with NT = BLOCK, the workgroup.
+// Every thread of the workgroup calls it.  A cluster that is too large, or that
+// the queue does not take, sets *more and stays as it was.  done: where a resolved
+// particle is marked, as DONE_WHOLE with its degree; it may be deg itself.
+template <int P, int NT, int BIG> struct ClustersLds {
+  static constexpr int G = NT == BLOCK ? BLOCK : WAVE;
+  // In a workgroup of 1 024 threads a lane has too few registers for a cluster of
+  // its own: the wavefronts take all.
+  static constexpr bool LANES = NT == BLOCK;
+  long long bigc[BIG], hugec[G == BLOCK ? BIG : 1];
+  int nbig, nhuge;
+  int shi[BLOCK / 64];
+  // the per-lane gathering area, reused afterwards for the group paths
+  union {
+    long long qs[CL_LDS * NT];
+    ClusterLds<P, WAVE> wave[NT / WAVE];
+    ClusterLds<P, G> big;
+  };
+};
+template <int P, int NT, int BIG, class Cand>
+__device__ __forceinline__ void resolve_candidates(ClustersLds<P, NT, BIG> &S, const int tot, Cand cand,
+    Parts<typename Prec<P>::T> pt, Adj adj, const int32_t *deg, int32_t *done,
+    const Consts<typename Prec<P>::T> &k, int32_t *more, long long &ncoll, long long &nwall) {
+  if (threadIdx.x == 0) S.nbig = S.nhuge = 0;
+  __syncthreads();
+  const LdsColumn<NT> ql{S.qs + threadIdx.x};
+  for (int f = threadIdx.x; f < tot; f += NT) {
+    const long long r = cand(f);
+    const int s = (int)(r & 0xffffffffll), g = (int)(r >> 32);
+    int m = -1;
+    if constexpr (ClustersLds<P, NT, BIG>::LANES) {
+      unsigned long long A;
+      m = gather_cluster(ql, CL_LDS, s, g, adj, deg, A);
+      if (m > 0) resolve_cluster<P>(ql, m, A, k, pt, done, ncoll, nwall);
+    }
+    if (m < 0) {
+      const int slot = atomicAdd(&S.nbig, 1);  // the workgroup resolves it below
+      if (slot < BIG) S.bigc[slot] = r;
+      else atomicOr(more, 1);  // queue full
+    }
+  }
+  __syncthreads();
+  // queued clusters: one wavefront each, then the whole workgroup for those too large
+  const int nb_big = min(S.nbig, BIG), wv = (int)threadIdx.x / WAVE;
+  for (int c = wv; c < nb_big; c += NT / WAVE) {
+    const long long r = S.bigc[c];
+    const int st = resolve_group<P, WAVE>(S.wave[wv], S.shi, (int)(r & 0xffffffffll), (int)(r >> 32), k, pt, adj, deg,
+                                          done, ncoll, nwall);
+    if (st == 2 && Group<WAVE>::rank() == 0) {
+      if constexpr (NT == BLOCK) S.hugec[atomicAdd(&S.nhuge, 1)] = r;
+      else atomicOr(more, 1);
+    }
+  }
+  if constexpr (NT == BLOCK) {
+    __syncthreads();
+    const int nb_huge = S.nhuge;
+    for (int c = 0; c < nb_huge; ++c) {
+      const long long r = S.hugec[c];
+      const int st = resolve_group<P, BLOCK>(S.big, S.shi, (int)(r & 0xffffffffll), (int)(r >> 32), k, pt, adj, deg,
+                                             done, ncoll, nwall);
+      if (st == 2 && threadIdx.x == 0) atomicOr(more, 1);
+    }
+  }
+}
+
+// The tile stage's clusters: its roots, in runs of BLOCK.
 template <int P>
 __device__ __forceinline__ void resolve_clusters_body(const int bidx, const int gdim, Parts<typename Prec<P>::T> pt,
-    Adj adj, const int32_t *__restrict__ deg, int32_t *done, Consts<typename Prec<P>::T> k, int32_t *need_sweep,
+    Adj adj, const int32_t *deg, int32_t *done, const Consts<typename Prec<P>::T> &k, int32_t *need_sweep,
     long long *coll_part, long long *wall_part, const long long *__restrict__ roots, int nlists,
     const int32_t *nroots) {
   __shared__ long long sh[BLOCK / 64];
-  __shared__ int shi[BLOCK / 64];
-  __shared__ int pre[BLOCK + 1];
-  __shared__ long long bigc[BIG_LIST], hugec[BIG_LIST];
-  __shared__ int nbig, nhuge;
-  // the per-lane gathering area, reused afterwards for the group paths
-  __shared__ union {
-    long long qs[CL_LDS * BLOCK];
-    ClusterLds<P, WAVE> wave[BLOCK / WAVE];
-    ClusterLds<P, BLOCK> big;
-  } U;
-  long long *const qs = U.qs;
-  if (threadIdx.x == 0) {
-    nbig = 0;
-    nhuge = 0;
-  }
-  // candidate lists [b0, b0 + nb): list j is the j-th run of BLOCK candidates
+  __shared__ ClustersLds<P, BLOCK, BIG_LIST> S;
+  // runs [b0, b0 + nb) of the candidates
   const int per = (nlists + gdim - 1) / gdim;  // <= BLOCK (host grid choice)
-  const int b0 = bidx * per;
-  const int nb = max(0, min(nlists - b0, per));
-  int tot;
+  const int b0 = min(bidx * per, nlists), nb = min(nlists - b0, per);
   // a contact row over its capacity leaves the contact graph incomplete: the
   // resolution is skipped and the step reports LBDPS_E_CAPACITY
   const bool overflow = __hip_atomic_load(&k.flags[FLAG_CAPACITY], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
   // (the count is loaded alongside the flag, not after it)
-  int c = 0;
-  if ((int)threadIdx.x < nb) c = min(max(*nroots - (b0 + (int)threadIdx.x) * BLOCK, 0), BLOCK);
-  if (overflow) c = 0;
-  const int o = block_excl_scan(c, shi, tot);
-  if (tot == 0) {  // no candidate roots in these lists (uniform: the scan's total)
+  const int left = *nroots - b0 * BLOCK, tot = overflow ? 0 : max(min(left, nb * BLOCK), 0);
+  if (tot == 0) {  // uniform
     if (threadIdx.x == 0) {
       coll_part[bidx] = 0;
       wall_part[bidx] = 0;
     }
     return;
   }
-  if ((int)threadIdx.x < nb) pre[threadIdx.x] = o;
-  if (threadIdx.x == 0) pre[nb] = tot;
-  __syncthreads();
-  const LdsColumn ql{qs + threadIdx.x};
   long long ncoll = 0, nwall = 0;
-  for (int f = threadIdx.x; f < tot; f += BLOCK) {
-    int lo = 0, hi = nb;  // list j with pre[j] <= f < pre[j + 1]
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (pre[mid] <= f) lo = mid;
-      else hi = mid;
-    }
-    const long long r = roots[(size_t)(b0 + lo) * BLOCK + (f - pre[lo])];
-    const int s = (int)(r & 0xffffffffll), g = (int)(r >> 32);
-    unsigned long long A;
-    int m = gather_cluster(ql, CL_LDS, s, g, adj, deg, A);
-    if (m > 0) {
-      resolve_cluster<P>(ql, m, A, k, pt, done, ncoll, nwall);
-    } else if (m < 0) {
-      const int slot = atomicAdd(&nbig, 1);  // the workgroup resolves it below
-      if (slot < BIG_LIST) bigc[slot] = r;
-      else atomicOr(need_sweep, 1);  // queue full: the ordered sweep takes it
-    }
-  }
-  __syncthreads();
-  // queued clusters: one wavefront each, then the whole workgroup for those too large
-  const int nb_big = min(nbig, BIG_LIST), wv = (int)threadIdx.x / WAVE;
-  for (int c = wv; c < nb_big; c += BLOCK / WAVE) {
-    const long long r = bigc[c];
-    const int st = resolve_group<P, WAVE>(U.wave[wv], shi, (int)(r & 0xffffffffll), (int)(r >> 32), k, pt, adj, deg,
-                                          done, ncoll, nwall);
-    if (st == 2 && Group<WAVE>::rank() == 0) hugec[atomicAdd(&nhuge, 1)] = r;
-  }
-  __syncthreads();
-  const int nb_huge = nhuge;
-  for (int c = 0; c < nb_huge; ++c) {
-    const long long r = hugec[c];
-    const int st = resolve_group<P, BLOCK>(U.big, shi, (int)(r & 0xffffffffll), (int)(r >> 32), k, pt, adj, deg, done,
-                                           ncoll, nwall);
-    if (st == 2 && threadIdx.x == 0) atomicOr(need_sweep, 1);
-  }
+  resolve_candidates<P>(S, tot, [&](int f) { return roots[(size_t)b0 * BLOCK + f]; }, pt, adj, deg, done, k,
+                        need_sweep, ncoll, nwall);
   long long tc, tw;
   block_sum2(ncoll, nwall, sh, tc, tw);
   if (threadIdx.x == 0) {
@@ -2097,7 +2114,7 @@ __device__ __forceinline__ void resolve_clusters_body(const int bidx, const int 
 template <int P>
 __global__ __launch_bounds__(BLOCK) void k_resolve_clusters(Parts<typename Prec<P>::T> pt,
                                                             Adj adj,
-                                                            const int32_t *__restrict__ deg, int32_t *done,
+                                                            const int32_t *deg, int32_t *done,
                                                             Consts<typename Prec<P>::T> k, int32_t *need_sweep,
                                                             long long *coll_part, long long *wall_part,
                                                             const long long *__restrict__ roots, int nlists,

@@ -91,26 +91,29 @@ int cluster_blocks(long long n, int lists = RC_LISTS, int groups_max = RC_GROUPS
 // The patches of cells of resolution pass `pass`.  A patch of the first pass
 // aims at PATCH_AIM particles with contacts, under the BLOCK its workgroup holds
 // at once: with discs of diameter d at density r, a share 1 - exp(-pi d^2 r) has
-// any.  Few are left for the later passes, whose patches are two and four times
-// as wide and high, their edges a half and a quarter of the first ones' off.
+// any.  Few are left for the second pass, whose patches are twice as wide and
+// high, their edges half of the first ones' off.
 //
 // Spheres over a bottom face lie about 2.4 times as dense as their mean over the
 // lattice if the bed fills it, and denser in a lattice much taller than the bed;
-// hence the floor under a single bed's density, as a 2-D solid fraction.  A
-// patch denser than assumed goes in bands of rows, one after the other, and
-// leaves more: the three kernels take 230 us with no floor and 84 with 0.4 on a
-// bed of fraction 0.4 in 486 x 2072 cells, 276 000 spheres.  A patch sparser than
-// assumed costs its fixed part: the first pass over 64 beds of 0.05 to 0.4, 4.2 M
-// spheres, takes 174 us with no floor and 235 with 0.4.  In a batch the
-// workgroups of other beds hide the bands, so its beds go by the mean, and aim
-// higher (1 % of a step).
+// hence the floor under a single bed's density, as a 2-D solid fraction, up to
+// PATCH_RATIO times the mean.  A patch denser than assumed goes in bands of rows,
+// one after the other, and leaves more: a bed of 75 000 spheres six times as
+// dense as their mean, in 215 x 1377 cells, takes 31 + 25 + 32 us with a ratio of
+// 4 and 14 + 14 + 16 with 8.  A patch sparser than assumed costs its fixed part:
+// 3 M spheres spread over walled 1000 x 1000 cells take 180 us, against 76 by
+// clusters.  The first pass over 64 beds of 0.05 to 0.4, 4.2 M spheres, takes 174
+// us with no floor and 235 with 0.4: in a batch the workgroups of other beds hide
+// the bands, so its beds go by the mean, and aim higher (1 % of a step).
 constexpr double PATCH_AIM = 210.0, PATCH_AIM_BATCH = 235.0, PATCH_DENSE = 2.4;
-constexpr double PATCH_FRACTION = 0.4;
+constexpr double PATCH_FRACTION = 0.4, PATCH_RATIO = 8.0;
 constexpr int PATCH_AREA_MIN = 16, PATCH_AREA_MAX = 1024;
+// Spheres per cell over the lattice, and whether they may be anywhere in it.
+double mean_density(const lbdps_params &p, long long n) { return std::max((double)n, 1.0) / ((double)p.nx * p.ny); }
+bool patch_even(const lbdps_params &p) { return p.bc[2] == BC_PERIODIC || p.particles_periodic_y; }
 double patch_density(const lbdps_params &p, long long n, bool batch) {  // particles per cell where they are
-  const bool even = p.bc[2] == BC_PERIODIC || p.particles_periodic_y;
-  const double mean = std::max((double)n, 1.0) / ((double)p.nx * p.ny);
-  return even ? mean : std::max(PATCH_DENSE * mean, batch ? 0.0 : PATCH_FRACTION / (kPi * p.d_p * p.d_p / 4.0));
+  const double mean = mean_density(p, n), dense = PATCH_FRACTION / (kPi * p.d_p * p.d_p / 4.0);
+  return patch_even(p) ? mean : std::max(PATCH_DENSE * mean, batch ? 0.0 : std::min(dense, PATCH_RATIO * mean));
 }
 PatchGrid patch_grid(const lbdps_params &p, long long n, int pass, int beds = 1) {
   const double dens = patch_density(p, n, beds > 1);
@@ -128,36 +131,55 @@ PatchGrid patch_grid(const lbdps_params &p, long long n, int pass, int beds = 1)
   g.nty = (p.ny + g.oy + g.th - 1) / g.th;
   return g;
 }
-// Patch passes of a bed of n particles before the rest: none where the final
-// workgroup alone is as fast (2 048 particles: 21 us, against 13 + 15), else as
-// many as leave it about PATCH_LEFT particles.  With kappa contacts per particle,
-// about a share 0.053 kappa of the particles with contacts is left after one
-// pass (0.04 measured at kappa 0.75, 0.09 at 1.6), 0.001 and 0.007 after two;
-// from about kappa 1.75 on contacts may percolate.  With 1 800 left of 509 000
+// How the row stage resolves a bed of n particles.  The final workgroup alone is
+// as fast up to 2 048 particles (21 us, against 13 + 15).
+//
+// By clusters, which need no layout, where that is as fast or the patches do not
+// suit.  kappa is the contacts per particle if they are spread over the lattice.
+//  - Few contacts.  Risers of 200 000 and 2 M spheres, with launches and search, FP32:
+//    kappa 0.24 25 and 72 us by clusters, 36 and 95 by patches; 0.39 33 and 97,
+//    49 and 105; 0.55 49 and 113, 50 and 109.  In FP64, where a lane's cluster does
+//    not fit its registers, 40 and 119, 37 and 99 at 0.24.  A dense clump in a wide
+//    periodic lattice, which no layout by the mean fits, then costs 65 us (200 000
+//    spheres in a sixth of 1000 x 1000 cells), against 177 by patches.  Over a
+//    bottom face the spheres may be denser than that and patches laid out for it:
+//    1 M spheres at kappa 0.13 in walled 1000 x 1000 cells take 41 us by clusters
+//    and 69 by patches, settled beds of kappa 0.2 on the mean 78 and 47.
+//  - Clusters larger than patches, from about kappa 2: 300 000 spheres at kappa 2.4
+//    take 290 us by clusters and 594 by patches, 4 M at 3.1 4.6 ms and 60.
+//
+// Else by patches, in as many passes as leave the final workgroup about PATCH_LEFT
+// particles.  About a share 0.053 kappa of the particles with contacts is left
+// after one pass (0.04 measured at kappa 0.75, 0.09 at 1.6), 0.001 and 0.007 after
+// two; from about kappa 1.75 on contacts may percolate.  With 1 800 left of 509 000
 // spheres in 606 x 2374 cells the rest takes 36 us, against 11 + 8 with a second
-// pass before it.
-constexpr double PATCH_LEFT = 1200.0;
+// pass before it.  In a batch the final workgroups run side by side, so a bed may
+// leave as many as one holds, and a sparse bed over a bottom face takes the
+// patches that the others need anyway (a launch of the cluster kernel for a few
+// of 64 beds costs 20 us).
+constexpr double PATCH_LEFT = 1200.0, PATCH_LEFT_BATCH = 0.85 * FINAL_CAP;
+constexpr double CLUSTERS_EVEN[2] = {0.45, 0.2}, CLUSTERS_BELOW[2] = {0.128, 0.08}, CLUSTERS_ABOVE = 2.0;
 constexpr int PATCH_WHOLE = 2048;
-int patch_passes(const lbdps_params &p, long long n) {
-  if (n <= PATCH_WHOLE) return 0;
-  const double kappa = kPi * p.d_p * p.d_p * patch_density(p, n, false);
-  return (1.0 - std::exp(-kappa)) * (double)n * 0.053 * kappa <= PATCH_LEFT && kappa < 1.75 ? 1 : 2;
+int row_plan(const lbdps_params &p, long long n, bool batch) {
+  if (n <= PATCH_WHOLE) return PLAN_WHOLE;
+  const double a = kPi * p.d_p * p.d_p, mean = a * mean_density(p, n), kappa = a * patch_density(p, n, batch);
+  const double below = (patch_even(p) ? CLUSTERS_EVEN : CLUSTERS_BELOW)[p.precision == PREC_FP64];
+  if (mean > CLUSTERS_ABOVE || (mean < below && (!batch || patch_even(p)))) return PLAN_CLUSTERS;
+  const double left = (1.0 - std::exp(-kappa)) * (double)n * 0.053 * kappa;
+  const bool one = batch ? left <= PATCH_LEFT_BATCH : left <= PATCH_LEFT && kappa < 1.75;
+  return one ? PLAN_ONE_PASS : PLAN_TWO_PASSES;
 }
-// The beds of a batch take as many passes as the one that needs the most, since
-// the launch is there; the final workgroups run side by side, so a bed may leave
-// as many as one holds.  If only a quarter of the beds or less is expected to
-// need a second pass, the first lists what it leaves by a counter per bed, and
-// the second ends at once in the beds whose final workgroup can hold that: the
-// second takes 4 us then instead of 11 on 28 beds of 34 000 spheres that have
-// drifted apart (the step 3 % faster), but where 64 beds of up to 200 000 need it
-// the lists make the step 4 % slower.
-constexpr double PATCH_LEFT_BATCH = 0.85 * FINAL_CAP;
-int patch_passes_batch(const lbdps_params &p, long long n) {
-  const double kappa = kPi * p.d_p * p.d_p * patch_density(p, n, true);
-  return n <= PATCH_WHOLE ? 0 : ((1.0 - std::exp(-kappa)) * (double)n * 0.053 * kappa <= PATCH_LEFT_BATCH ? 1 : 2);
+// Workgroups of the rest for one bed of `beds`.
+int rest_blocks(int plan, long long n, int beds = 1) {
+  if (plan == PLAN_WHOLE) return 1;
+  return (int)std::max(1ll, std::min((n + FINAL_THREADS - 1) / FINAL_THREADS, (long long)REST_BLOCKS / beds));
 }
-int rest_blocks(const lbdps_params &p, long long n, int passes, int beds = 1) {  // of one bed of `beds`
-  return passes > 0 ? std::max(1, std::min(patch_grid(p, n, passes, beds).count(), REST_BLOCKS / beds)) : 1;
+// Slots per lane of the cluster kernel for n particles: one, until its workgroups
+// are more than are resident together, and in a batch.
+int clusters_slots(long long n, int beds) { return beds == 1 && n > 512ll * 1024 ? CLUSTERS_SL : 1; }
+int clusters_blocks(long long n, int beds) {
+  const int slots = clusters_slots(n, beds) * BLOCK;
+  return (int)((n + slots - 1) / slots);
 }
 
 size_t pop_bytes(int prec) { return prec == PREC_FP64 ? 8 : (prec == PREC_FP32 ? 4 : 2); }
@@ -297,8 +319,8 @@ struct lbdps_ctx {
   long long step = 0;
   bool in_batch = false;  // owned by a batch: destroyed with it
   lbdps_tuning tune{RC_LISTS, RC_GROUPS_MAX, 0, 0};
-  int passes = 0;        // patch passes of the most recent collision stage (-1: it took the tile kernel)
-  int stage_beds = 1;    // and beds its launches were for
+  int plan = PLAN_WHOLE;  // of the most recent collision stage; its partial sums:
+  int patches[PATCH_PASSES]{}, clusters = 0, rests = 0;
   int sphere_tiles = 0;  // tiles of the tile kernel in the most recent collision stage (0: not used)
   int drag_blocks = 0;  // drag workgroups of the most recent step (its partial sums)
   int cluster_groups() const { return cluster_blocks(n, tune.cluster_lists, tune.cluster_groups_max); }
@@ -319,18 +341,17 @@ struct lbdps_ctx {
   int32_t *tile_sum = nullptr, *chunk_busy = nullptr, *need_sweep = nullptr;
   int tile_shift = 11;
   long long *roots = nullptr;
-  // slots of the particles the patches left (done then holds their places), and
-  // what the final workgroup keeps when it works in memory (rank and perm are
-  // free in the collision stage)
-  int32_t *fin_state = nullptr;
-  int32_t *left() const { return (int32_t *)roots; }
-  int32_t *left2 = nullptr;
+  // slots of the particles the patches left (in roots; done then holds their
+  // places), and what the final workgroup keeps when it works in memory (rank and
+  // perm are free in the collision stage)
+  int32_t *fin_state = nullptr, *left2 = nullptr;
   RestBuffers rest() const {
-    return RestBuffers{left(), left2, done, need_sweep, FinalMem{perm, fin_state, {rank, (int32_t *)roots + nmax}}};
+    return RestBuffers{(int32_t *)roots, left2, done, need_sweep, rest_coll, rest_wall,
+                       FinalMem{perm, fin_state, {rank, (int32_t *)roots + nmax}}};
   }
   long long *collc_part = nullptr, *wallc_part = nullptr;
-  // collisions and wall hits per patch of each pass, and of the final workgroup
-  int32_t *pcoll_part[PATCH_PASSES + 1]{}, *pwall_part[PATCH_PASSES + 1]{};
+  // collisions and wall hits per patch of each pass, and per workgroup of the rest
+  int32_t *pcoll_part[PATCH_PASSES]{}, *pwall_part[PATCH_PASSES]{}, *rest_coll = nullptr, *rest_wall = nullptr;
   long long *tile_part = nullptr;  // the tile kernel's pairs, collisions, wall hits and particles left, per tile
   int ntiles = 0;
   double *cons_pc = nullptr, *cons_pp = nullptr, *cons_out = nullptr;
@@ -404,13 +425,14 @@ size_t carve(const lbdps_params &p, long long nmax, char *base, lbdps_ctx *x) {
   const size_t ntiles = (C + ((size_t)1 << shift) - 1) >> shift;
   int32_t *tile_sum = cv.take<int32_t>(ntiles + 1);
   long long *roots = cv.take<long long>(nbN * BLOCK);
-  int32_t *pcoll[PATCH_PASSES + 1], *pwall[PATCH_PASSES + 1];
-  for (int i = 0; i <= PATCH_PASSES; ++i) {  // a patch has at least 4 x 4 cells, twice that after the first pass
+  int32_t *pcoll[PATCH_PASSES], *pwall[PATCH_PASSES];
+  for (int i = 0; i < PATCH_PASSES; ++i) {  // a patch has at least 4 x 4 cells, 8 x 8 in the second pass
     const size_t w = i == 0 ? 4 : 8;
-    const size_t np = i < PATCH_PASSES ? ((size_t)p.nx / w + 2) * ((size_t)p.ny / w + 2) : 1;
+    const size_t np = ((size_t)p.nx / w + 2) * ((size_t)p.ny / w + 2);
     pcoll[i] = cv.take<int32_t>(np);
     pwall[i] = cv.take<int32_t>(np);
   }
+  int32_t *rest_coll = cv.take<int32_t>(REST_BLOCKS), *rest_wall = cv.take<int32_t>(REST_BLOCKS);
   int32_t *chunk_busy = cv.take<int32_t>(N / RES_CHUNK + 1), *need_sweep = cv.take<int32_t>(SW_COUNT);
   int32_t *fin_state = cv.take<int32_t>(N), *left2 = cv.take<int32_t>(N);
   long long *collc_part = cv.take<long long>(nbN), *wallc_part = cv.take<long long>(nbN);
@@ -483,10 +505,12 @@ size_t carve(const lbdps_params &p, long long nmax, char *base, lbdps_ctx *x) {
     x->fin_state = fin_state;
     x->left2 = left2;
     x->collc_part = collc_part;
-    for (int i = 0; i <= PATCH_PASSES; ++i) {
+    for (int i = 0; i < PATCH_PASSES; ++i) {
       x->pcoll_part[i] = pcoll[i];
       x->pwall_part[i] = pwall[i];
     }
+    x->rest_coll = rest_coll;
+    x->rest_wall = rest_wall;
     x->tile_part = tile_part;
     x->wallc_part = wallc_part;
     x->ntiles = (int)ntiles;
@@ -568,6 +592,18 @@ lbdps_status check_hip(hipError_t e, const char *what) {
 }
 
 lbdps_status launch_status(const char *what) { return check_hip(hipGetLastError(), what); }
+
+// Patch passes of a plan.
+int patch_passes(int plan) { return plan == PLAN_ONE_PASS || plan == PLAN_TWO_PASSES ? plan : 0; }
+// Notes the collision stage's plan and the workgroups of its launches, in a batch
+// of `beds`.
+void set_plan(lbdps_ctx *x, int plan, int beds) {
+  x->plan = plan;
+  for (int i = 0; i < PATCH_PASSES; ++i)
+    x->patches[i] = i < patch_passes(plan) ? patch_grid(x->p, x->n, i, beds).count() : 0;
+  x->clusters = plan == PLAN_CLUSTERS ? clusters_blocks(x->n, beds) : 0;
+  x->rests = plan == PLAN_TILES ? 0 : rest_blocks(plan, x->n, beds);
+}
 
 template <int P> struct Impl {
   using T = typename Prec<P>::T;
@@ -706,14 +742,19 @@ template <int P> struct Impl {
   // finds the contacts and resolves the clusters that lie within its tiles'
   // reach, and writes rows and one compact root list only for the rest,
   // which the cluster kernel and the ordered sweep then take as before.
+  // The kernel of the rest for a plan.
+  using RestKern = void (*)(Parts<T>, Consts<T>, Adj, int32_t *, RestBuffers);
+  static RestKern rest_kernel(int plan) {
+    return plan == PLAN_WHOLE ? k_rest<P, PLAN_WHOLE>
+                              : (plan == PLAN_CLUSTERS ? k_rest<P, PLAN_CLUSTERS> : k_rest<P, PLAN_TWO_PASSES>);
+  }
   static void hard_spheres(lbdps_ctx *x, bool extra = false) {
     const int N = (int)x->n;
     if (N == 0) return;
     const Consts<T> k = consts(x);
     const int st = x->tune.sphere_tile;
     x->sphere_tiles = st > 0 ? sphere_tiles(x, st) : 0;
-    x->passes = st > 0 ? -1 : patch_passes(x->p, x->n);
-    x->stage_beds = 1;
+    set_plan(x, st > 0 ? (int)PLAN_TILES : row_plan(x->p, x->n, false), 1);
     if (st > 0) {
       tlaunch(x, LBDPS_K_CONTACTS, extra, tile_kernel(st), dim3(x->sphere_tiles), parts(x, x->cp),
               (const int32_t *)x->cs, k, x->adj(), x->deg, x->done, x->ticket, x->need_sweep, x->chunk_busy,
@@ -725,22 +766,20 @@ template <int P> struct Impl {
               (const int32_t *)x->slot, x->adj(), (const int32_t *)x->deg, x->done, x->ticket, k, x->flags,
               x->coll_part, x->wall_part, x->chunk_busy, x->need_sweep);
     } else {
-      tlaunch(x, LBDPS_K_CONTACTS, extra, k_contacts<P>, dim3(nblocks(N)), parts(x, x->cp), (const int32_t *)x->cs, k, x->adj(), x->deg, x->flags, x->pair_part,
-              x->wall0_part, x->need_sweep);
-      const int np = x->passes;
-      for (int i = 0; i < np; ++i) {
-        const PatchGrid g = patch_grid(x->p, x->n, i);
-        tlaunch_n(x, LBDPS_K_RESOLVE, extra || i > 0,
-                  i == 0 ? k_patches<P, PATCH_HELD0, true> : k_patches<P, PATCH_HELD1, false>,
-                  dim3(g.count()), dim3(BLOCK), parts(x, x->cp), (const int32_t *)x->cs, k,
-                  x->adj(), x->deg, g, (int)(i + 1 == np), x->left(), x->done, x->need_sweep + SW_LEFT,
-                  x->pcoll_part[i], x->pwall_part[i]);
-      }
-      const PatchGrid g = patch_grid(x->p, x->n, np);
-      tlaunch_n(x, LBDPS_K_RESOLVE, extra || np > 0, np > 0 ? k_rest<P, true> : k_rest<P, false>,
-                dim3(rest_blocks(x->p, x->n, np)), dim3(FINAL_THREADS),
-                parts(x, x->cp), (const int32_t *)x->cs, k, x->adj(), x->deg, g, x->rest(),
-                x->pcoll_part[np], x->pwall_part[np], x->pcoll_part[PATCH_PASSES], x->pwall_part[PATCH_PASSES]);
+      tlaunch(x, LBDPS_K_CONTACTS, extra, k_contacts<P>, dim3(nblocks(N)), parts(x, x->cp), (const int32_t *)x->cs, k,
+              x->adj(), x->deg, x->flags, x->pair_part, x->wall0_part, x->need_sweep);
+      const int np = patch_passes(x->plan);
+      for (int i = 0; i < np; ++i)
+        tlaunch(x, LBDPS_K_RESOLVE, true, i == 0 ? k_patches<P, PATCH_HELD0, true> : k_patches<P, PATCH_HELD1, false>,
+                dim3(x->patches[i]), parts(x, x->cp), (const int32_t *)x->cs, k, x->adj(), x->deg,
+                patch_grid(x->p, x->n, i), (int)(i + 1 == np), (int32_t *)x->roots, x->done, x->need_sweep + SW_LEFT,
+                x->need_sweep + SW_FULL, x->pcoll_part[i], x->pwall_part[i]);
+      if (x->plan == PLAN_CLUSTERS)
+        tlaunch(x, LBDPS_K_RESOLVE, true, clusters_slots(x->n, 1) == 1 ? k_clusters<P, 1> : k_clusters<P, CLUSTERS_SL>,
+                dim3(x->clusters), parts(x, x->cp), k, x->adj(), x->deg, x->need_sweep, x->collc_part, x->wallc_part);
+      // the rest always runs: it is the resolution launch that counts
+      tlaunch_n(x, LBDPS_K_RESOLVE, extra, rest_kernel(x->plan), dim3(x->rests), dim3(FINAL_THREADS), parts(x, x->cp),
+                k, x->adj(), x->deg, x->rest());
     }
   }
 
@@ -1333,10 +1372,10 @@ lbdps_status lbdps_counters(lbdps_ctx *x, int64_t h_out[4]) {
   const int nbN = nblocks(x->n), nbC = x->drag_blocks;
   // contacts: one partial per workgroup of the contact kernel; collisions and
   // wall hits of the resolution kernels: one per workgroup of each
-  const bool tile = x->passes < 0;  // the tile kernel counts its own contacts
+  const bool tile = x->plan == PLAN_TILES;  // the tile kernel counts its own contacts
   long long *src[6] = {x->pair_part, x->wall0_part, x->collc_part, x->wallc_part, x->coll_part, x->wall_part};
   const int dst[6] = {0, 2, 1, 2, 1, 2};
-  const int nres = tile ? Impl<PREC_FP32>::resolve_blocks(x) : 0, ncl = tile ? x->cluster_groups() : 0;
+  const int nres = tile ? Impl<PREC_FP32>::resolve_blocks(x) : 0, ncl = tile ? x->cluster_groups() : x->clusters;
   const int nct = tile ? 0 : nbN;
   const int len[6] = {nct, nct, ncl, ncl, nres, nres};
   std::vector<long long> buf((size_t)std::max({nbN, nbC, ncl, nres}) + 1);
@@ -1348,14 +1387,14 @@ lbdps_status lbdps_counters(lbdps_ctx *x, int64_t h_out[4]) {
       if (st != LBDPS_OK) return st;
       for (int b = 0; b < len[j]; ++b) h_out[dst[j]] += buf[b];
     }
-  if (x->n > 0 && !tile)  // the patch passes and the final workgroup
+  if (x->n > 0)  // the patches and the rest
     for (int i = 0; i <= PATCH_PASSES; ++i) {
-      if (i < PATCH_PASSES && (i > x->passes || x->passes == 0)) continue;  // the rest's pass comes after the passes
-      const int np = i < PATCH_PASSES ? patch_grid(x->p, x->n, i, x->stage_beds).count() : 1;
+      const bool rest = i == PATCH_PASSES;
+      const int np = rest ? x->rests : x->patches[i];
       std::vector<int32_t> pb((size_t)np);
-      for (int j = 0; j < 2; ++j) {
-        st = check_hip(hipMemcpy(pb.data(), j ? x->pwall_part[i] : x->pcoll_part[i], (size_t)np * 4,
-                                 hipMemcpyDeviceToHost), "lbdps_counters");
+      for (int j = 0; j < 2 && np > 0; ++j) {
+        const int32_t *part = rest ? (j ? x->rest_wall : x->rest_coll) : (j ? x->pwall_part[i] : x->pcoll_part[i]);
+        st = check_hip(hipMemcpy(pb.data(), part, (size_t)np * 4, hipMemcpyDeviceToHost), "lbdps_counters");
         if (st != LBDPS_OK) return st;
         for (int32_t v : pb) h_out[1 + j] += v;
       }
@@ -1394,6 +1433,23 @@ lbdps_status lbdps_tile_stats(lbdps_ctx *x, int64_t h_out[2]) {
   if (st != LBDPS_OK) return st;
   for (long long v : buf) h_out[1] += v;
   h_out[0] = x->n - h_out[1];
+  return LBDPS_OK;
+}
+
+lbdps_status lbdps_row_stats(lbdps_ctx *x, int64_t h_out[5]) {
+  if (!x || !h_out) return fail(LBDPS_E_INVALID, "ctx or out is NULL");
+  lbdps_status st = sync_and_check(x, "lbdps_row_stats");
+  if (st != LBDPS_OK) return st;
+  int32_t sw[SW_COUNT] = {0};
+  if (x->n > 0 && x->plan != PLAN_TILES) {
+    st = check_hip(hipMemcpy(sw, x->need_sweep, sizeof(sw), hipMemcpyDeviceToHost), "lbdps_row_stats");
+    if (st != LBDPS_OK) return st;
+  }
+  h_out[0] = x->plan;
+  h_out[1] = sw[SW_LEFT];
+  h_out[2] = sw[SW_LEFT2];
+  h_out[3] = sw[SW_FULL];
+  h_out[4] = sw[SW_MORE];
   return LBDPS_OK;
 }
 
@@ -1599,14 +1655,21 @@ template <int P> struct BatchImpl {
   static size_t args_bytes(int nbeds) { return align256((size_t)nbeds * sizeof(BedArgs<P>)); }
   static size_t table_bytes(int nbeds) { return args_bytes(nbeds) + align256((size_t)PH_COUNT * (nbeds + 1) * 4); }
 
-  // Patch passes of bed x in a batch whose beds take at most `most`.
-  static int bed_passes(const lbdps_ctx *x, int nbeds, int most) {
-    return nbeds == 1 ? patch_passes(x->p, x->n) : (x->n <= PATCH_WHOLE ? 0 : most);
+  // Plan of bed x in a batch whose beds take at most `most` patch passes: as many
+  // as the bed that needs the most, since the launch is there.  If only a quarter
+  // of the beds or less is expected to need a second pass, the first lists what it
+  // leaves by a counter per bed, and the second ends at once in the beds whose
+  // final workgroup can hold that: the second takes 4 us then instead of 11 on 28
+  // beds of 34 000 spheres that have drifted apart (the step 3 % faster), but where
+  // 64 beds of up to 200 000 need it the lists make the step 4 % slower.
+  static int bed_plan(const lbdps_ctx *x, int nbeds, int most) {
+    const int plan = row_plan(x->p, x->n, nbeds > 1);
+    return patch_passes(plan) > 0 ? most : plan;
   }
   static int most_passes(const lbdps_batch *B, bool &listed) {
     int m = 0, two = 0;
     for (const auto *x : B->beds) {
-      const int np = patch_passes_batch(x->p, x->n);
+      const int np = patch_passes(row_plan(x->p, x->n, B->nbeds > 1));
       m = std::max(m, np);
       two += np == 2;
     }
@@ -1643,10 +1706,12 @@ template <int P> struct BatchImpl {
     a.cf = x->cf;
     a.cp = x->cp;
     a.cp_moves = x->n > 0;
-    a.npass = bed_passes(x, nbeds, most);
+    a.plan = bed_plan(x, nbeds, most);
     a.listed = listed;
-    for (int i = 0; i <= PATCH_PASSES; ++i) {
-      if (i < PATCH_PASSES) a.pg[i] = patch_grid(x->p, x->n, i, nbeds);
+    a.collc_part = x->collc_part;
+    a.wallc_part = x->wallc_part;
+    for (int i = 0; i < PATCH_PASSES; ++i) {
+      a.pg[i] = patch_grid(x->p, x->n, i, nbeds);
       a.pcoll_part[i] = x->pcoll_part[i];
       a.pwall_part[i] = x->pwall_part[i];
     }
@@ -1654,7 +1719,8 @@ template <int P> struct BatchImpl {
   }
 
   // Workgroups of each phase for one bed, as the single-bed step launches
-  // them, in a batch of nbeds and at most `most` patch passes; the drag under the batch's tile shape `tile`.
+  // them, in a batch of nbeds and at most `most` patch passes; the drag under the
+  // batch's tile shape `tile`.
   static void blocks(const lbdps_ctx *x, int nbeds, int most, int tile, int nb[PH_COUNT]) {
     for (int i = 0; i < PH_COUNT; ++i) nb[i] = 0;
     nb[PH_COLLIDE] = nblocks(x->C);
@@ -1663,9 +1729,10 @@ template <int P> struct BatchImpl {
     nb[PH_SCAN] = x->ntiles;
     nb[PH_SCATTER] = nblocks(x->n);
     nb[PH_CONTACTS] = nblocks(x->n);
-    const int np = bed_passes(x, nbeds, most);
-    for (int i = 0; i < np; ++i) nb[PH_PATCH0 + i] = patch_grid(x->p, x->n, i, nbeds).count();
-    nb[PH_REST] = rest_blocks(x->p, x->n, np, nbeds);
+    const int plan = bed_plan(x, nbeds, most);
+    for (int i = 0; i < patch_passes(plan); ++i) nb[PH_PATCH0 + i] = patch_grid(x->p, x->n, i, nbeds).count();
+    if (plan == PLAN_CLUSTERS) nb[PH_CLUSTERS] = clusters_blocks(x->n, nbeds);
+    nb[PH_REST] = rest_blocks(plan, x->n, nbeds);
   }
 
   // Fills table t (0 eager, 1 graph) from the beds' current state.
@@ -1716,7 +1783,7 @@ template <int P> struct BatchImpl {
       case PH_SCAN: return LBDPS_K_SCAN;
       case PH_SCATTER: return LBDPS_K_SCATTER;
       case PH_CONTACTS: return LBDPS_K_CONTACTS;
-      default: return LBDPS_K_RESOLVE;  // the patch passes and the final workgroup
+      default: return LBDPS_K_RESOLVE;  // the patch passes, the clusters and the rest
     }
   }
   // Events for a timed launch of kernel class k in an eager batched step,
@@ -1774,7 +1841,12 @@ template <int P> struct BatchImpl {
       // the rest always runs: it is the resolution launch that counts
       LBDPS_LAUNCH_N((kb_patches<P, PATCH_HELD0, true>), PH_PATCH0, BLOCK, true, 0)
       LBDPS_LAUNCH_N((kb_patches<P, PATCH_HELD1, false>), PH_PATCH1, BLOCK, true, 1)
-      LBDPS_LAUNCH_N(kb_rest<P>, PH_REST, FINAL_THREADS, false)
+      LBDPS_LAUNCH_N(kb_clusters<P>, PH_CLUSTERS, BLOCK, true)
+      if (tot[PH_CLUSTERS] > 0) {
+        LBDPS_LAUNCH_N((kb_rest<P, true>), PH_REST, FINAL_THREADS, false)
+      } else {
+        LBDPS_LAUNCH_N((kb_rest<P, false>), PH_REST, FINAL_THREADS, false)
+      }
 #undef LBDPS_LAUNCH_N
 #undef LBDPS_LAUNCH
     }
@@ -1783,8 +1855,7 @@ template <int P> struct BatchImpl {
   static void advance(lbdps_batch *B, int t, int nsteps) {
     for (auto *x : B->beds) {
       x->sphere_tiles = 0;  // the batched collision stage takes the patches
-      if (x->n > 0) x->passes = bed_passes(x, B->nbeds, B->most[t]);
-      x->stage_beds = B->nbeds;
+      if (x->n > 0) set_plan(x, bed_plan(x, B->nbeds, B->most[t]), B->nbeds);
       x->cf ^= nsteps & 1;
       if (x->n > 0) x->cp ^= nsteps & 1;
       x->step += nsteps;

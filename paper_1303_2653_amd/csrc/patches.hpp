@@ -17,24 +17,27 @@
 // go back to memory and leave the stage (degree 0).  The marked ones are as if
 // nothing had happened.
 //
-// Passes with larger patches, moved against the ones before, leave the few
-// clusters that cross an edge in every pass (of the particles with contacts on
-// a 512 x 4096 riser 4 % after one pass, 0.1 % after two); one workgroup takes
-// those of the whole bed at once.  Where it could not hold them, because the
-// clusters span many patches or the patches were too full, there is a pass of
-// wide workgroups before it (k_rest).
+// A second pass with larger patches, moved against the first's, leaves the few
+// clusters that cross an edge in both (of the particles with contacts on a
+// 512 x 4096 riser 4 % after one pass, 0.1 % after two); one workgroup takes those
+// of the whole bed at once.  Where it could not hold them, because the patches
+// were too full or the clusters span many of them, the particles left are taken
+// cluster by cluster before it (k_rest), wherever they lie.  A bed whose particles
+// seldom touch, or whose clusters no patch holds, goes by clusters from the start
+// (k_clusters).
 //
 // The first pass is bound by its chain of dependent loads, barriers and rounds:
 // on the 2 M-sphere riser it issues for 17 of its 46 us, eight patches of 400
-// particles per CU.  Hence the single range check per row entry (the entry carries the partner's
-// row of cells), and the rounds of one wavefront once at most 64 particles have
-// partners left, while the others wait at the barrier.  Measured there, FP32:
-// 47 us for the first pass, 16 us for the second, 19 us for the final workgroup,
-// against 145 us (88 us in its best launch shape) and 5 us for one lane per
-// cluster and the ordered sweep; 310 + 129 + 30 against 1 034 us at 16 M spheres.
-// The later kernels are such chains too.  A counter all patches add to
-// costs 7 ns each, one after the other, so only the last pass lists what it
-// leaves (34 us more for the first pass where it did).
+// particles per CU.  Hence the single range check per row entry (the entry
+// carries the partner's row of cells), and the rounds of one wavefront once at
+// most 64 particles have partners left, while the others wait at the barrier.
+// Measured there, FP32: 47 us for the first pass, 16 us for the second, 19 us for
+// the final workgroup, against 145 us (88 us in its best launch shape) and 5 us
+// for one lane per cluster and the ordered sweep; 310 + 129 + 30 against 1 034 us
+// at 16 M spheres.  The later kernels are such chains too.  A counter all patches
+// add to costs 7 ns each, one after the other, so a pass lists what it leaves only
+// where it may be the last one of its bed (34 us more for the first pass of the
+// riser, had it listed).
 #pragma once
 
 #include "kernels.hpp"
@@ -48,18 +51,24 @@ struct PatchGrid {
   __host__ __device__ int count() const { return ntx * nty; }
 };
 
-constexpr int PATCH_PASSES = 3;      // most passes, the last one with the final workgroup
+// How the row stage resolves a bed: all of it in the final workgroup, by one or
+// two passes of patches, or by clusters; or the tile stage.
+enum { PLAN_TILES = -1, PLAN_WHOLE = 0, PLAN_ONE_PASS = 1, PLAN_TWO_PASSES = 2, PLAN_CLUSTERS };
+constexpr int PATCH_PASSES = 2;      // most passes
 constexpr int PATCH_ROWS = 64;       // most rows of cells in a patch
 constexpr int PATCH_NB = 8;          // partners' places kept in registers
 constexpr int PATCH_NONE = 0xffff;   // no partner, or one outside
-// Particles a patch's workgroup of BLOCK threads looks at together: of the first
-// pass, where about half of them have contacts, and of the second, where few are
-// left.  The pass before the final workgroup has PATCH_WIDE threads: it runs
-// where the bed is much denser in places than patch_grid assumes.
+// Bands of rows a patch of the first pass is taken in, before the rest of it is
+// left, and the share (one in PATCH_FLOOD) of the bed that may be left so before
+// the second pass only lists: its patches would be as full.  1 M spheres in the
+// bottom 30 % of a periodic 512 x 4096 riser: 36 + 45 us for the passes, 75 + 79
+// without the limits.  Beds laid out about right take two bands at most.
+constexpr int PATCH_BANDS = 3, PATCH_FLOOD = 16;
+// Particles a patch's workgroup looks at together: of the first pass, where about
+// half of them have contacts, and of the second, where few are left.
 constexpr int PATCH_HELD0 = 2 * BLOCK, PATCH_HELD1 = 8 * BLOCK;
-constexpr int PATCH_WIDE = 1024, PATCH_HELD2 = 2 * PATCH_WIDE;
 // The final workgroup: threads, and particles it holds.
-constexpr int FINAL_THREADS = PATCH_WIDE, FINAL_PT = 4, FINAL_CAP = FINAL_THREADS * FINAL_PT;
+constexpr int FINAL_THREADS = 1024, FINAL_PT = 4, FINAL_CAP = FINAL_THREADS * FINAL_PT;
 // Cell of a particle relative to the patch, for the separation in the cell +
 // offset modes: partners are at most one cell apart after the periodic wrap.
 template <int P>
@@ -94,7 +103,8 @@ struct alignas(16) Partners {
 };
 static_assert(PATCH_NB == 8, "Partners holds eight places");
 
-template <class T, int NT, int HELD> struct PatchLds {
+template <class T, int HELD> struct PatchLds {
+  static constexpr int NT = BLOCK;
   T x[NT], y[NT], vx[NT], vy[NT];
   Partners nb[NT];
   int cell[NT], slot[NT], ext[NT], hits[NT];
@@ -106,13 +116,19 @@ template <class T, int NT, int HELD> struct PatchLds {
   int np, nleft, base, nlist, nwork, busy[3], alive[3], ncoll, nwall;
 };
 
-template <int P, int NT, int HELD, bool FIRST>
-__device__ __forceinline__ void patches_body(PatchLds<typename Prec<P>::T, NT, HELD> &S, const int bidx,
-    Parts<typename Prec<P>::T> pt,
-    const int32_t *__restrict__ cs, const Consts<typename Prec<P>::T> &k, Adj adj, int32_t *__restrict__ deg,
-    const PatchGrid g, const bool last, int32_t *__restrict__ left, int32_t *__restrict__ place_of,
-    int32_t *__restrict__ nleft, int32_t *__restrict__ coll_part, int32_t *__restrict__ wall_part) {
+// The first pass left so many particles of patches too full for it that they are
+// for the rest to take cluster by cluster; full counts them.
+__device__ __forceinline__ bool patches_flooded(int full, int npart) { return full > npart / PATCH_FLOOD; }
+
+template <int P, int HELD, bool FIRST>
+__device__ __forceinline__ void patches_body(PatchLds<typename Prec<P>::T, HELD> &S, const int bidx,
+    Parts<typename Prec<P>::T> pt, const int32_t *__restrict__ cs, const Consts<typename Prec<P>::T> &k, Adj adj,
+    int32_t *__restrict__ deg, const PatchGrid g, const bool last, int32_t *__restrict__ left,
+    int32_t *__restrict__ place_of, int32_t *__restrict__ nleft, int32_t *__restrict__ full, int32_t *__restrict__ coll_part,
+    int32_t *__restrict__ wall_part) {
   using T = typename Prec<P>::T;
+  constexpr int NT = BLOCK;
+  const bool flooded = !FIRST && patches_flooded(*full, k.npart);
   const int tid = (int)threadIdx.x, lane = tid & 63;
   const int bx = bidx % g.ntx, by = bidx / g.ntx;
   const int x0 = max(bx * g.tw - g.ox, 0), x1 = min((bx + 1) * g.tw - g.ox, k.nx);
@@ -147,29 +163,66 @@ __device__ __forceinline__ void patches_body(PatchLds<typename Prec<P>::T, NT, H
     left[to] = s;
     place_of[s] = to;
   };
+  // Slot of particle l of the rows from r0 on, and its row (rbase[row] <= base0 + l
+  // < rbase[row + 1], row < r1).
+  auto slot_of = [&](int l, int r0, int r1, int base0, int &row) {
+    int r = r0, hi = r1;
+    while (hi - r > 1) {
+      const int mid = (r + hi) >> 1;
+      if (S.rbase[mid] - base0 <= l) r = mid;
+      else hi = mid;
+    }
+    row = r;
+    return S.rlo[r] + (base0 + l - S.rbase[r]);
+  };
+  // Leaves the particles with contacts of rows [a, b) of the patch: counts them,
+  // takes their places by one addition to the bed's counter, lists them.
+  auto leave_rows = [&](int a, int b) {
+    if (!last) return;
+    const int base0 = S.rbase[a], total = S.rbase[b] - base0;
+    for (int listing = 0; listing < 2; ++listing) {
+      __syncthreads();
+      if (tid == 0) S.nleft = 0;
+      __syncthreads();
+      for (int l0 = 0; l0 < total; l0 += NT) {
+        int row, s = 0;
+        bool has = false;
+        if (l0 + tid < total) {
+          s = slot_of(l0 + tid, a, b, base0, row);
+          has = ldu(deg, s) > 0;
+        }
+        const unsigned long long m = __ballot(has);
+        int at = 0;
+        if (lane == 0 && m) at = atomicAdd(&S.nleft, __popcll(m));
+        at = __shfl(at, 0, 64) + __popcll(m & ((1ull << lane) - 1));
+        if (has && listing) leave(s, S.base + at);
+      }
+      __syncthreads();
+      if (tid == 0 && !listing) S.base = atomicAdd(nleft, S.nleft);
+    }
+  };
   // Bands of rows, one after the other; usually the patch is one.  A band holds
   // at most HELD particles, NT of them with contacts.
   int want = H;  // rows to try
+  int bands = 0;
   for (int r0 = 0, r1; r0 < H && !overflow; r0 = r1) {
+    if (FIRST && bands == PATCH_BANDS) {  // far too full
+      if (tid == 0) atomicAdd(full, S.rbase[H] - S.rbase[r0]);
+      leave_rows(r0, H);
+      break;
+    }
+    if (!FIRST && flooded) {
+      leave_rows(0, H);
+      break;
+    }
     const int base0 = S.rbase[r0];
     r1 = min(H, r0 + want);
     while (r1 > r0 + 1 && S.rbase[r1] - base0 > HELD) r1 = r0 + (r1 - r0 + 1) / 2;
     const int held = S.rbase[r1] - base0;
     want = H;
     if (held == 0) continue;
-    // the band's particles with contacts are left as they are
-    auto leave_band = [&]() {
-      if (!last) return;
-      for (int r = r0; r < r1; ++r) {
-        const int len = S.rbase[r + 1] - S.rbase[r];
-        for (int l = tid; l < len; l += NT) {
-          const int s = S.rlo[r] + l;
-          if (deg[s] > 0) leave(s, atomicAdd(nleft, 1));
-        }
-      }
-    };
     if (held > HELD) {  // one crowded row
-      leave_band();
+      leave_rows(r0, r1);
       continue;
     }
     __syncthreads();  // the previous band's LDS is free
@@ -183,19 +236,11 @@ __device__ __forceinline__ void patches_body(PatchLds<typename Prec<P>::T, NT, H
 #pragma unroll
     for (int j = 0; j < PT; ++j) {
       const int l = tid + j * NT;
-      int r = r0;
-      ps[j] = pd[j] = 0;
+      ps[j] = pd[j] = pr[j] = 0;
       if (l < held) {
-        int hi = r1;  // the row: rbase[r] <= base0 + l < rbase[r + 1]
-        while (hi - r > 1) {
-          const int mid = (r + hi) >> 1;
-          if (S.rbase[mid] - base0 <= l) r = mid;
-          else hi = mid;
-        }
-        ps[j] = S.rlo[r] + (base0 + l - S.rbase[r]);
+        ps[j] = slot_of(l, r0, r1, base0, pr[j]);
         pd[j] = ldu(deg, ps[j]);
       }
-      pr[j] = r;
     }
     __syncthreads();
 #pragma unroll
@@ -224,10 +269,11 @@ __device__ __forceinline__ void patches_body(PatchLds<typename Prec<P>::T, NT, H
         want = (r1 - r0) / 2;
         r1 = r0;
       } else {
-        leave_band();
+        leave_rows(r0, r1);
       }
       continue;
     }
+    ++bands;
     // place of the partner of an entry of a particle in row `row_of`, or
     // PATCH_NONE if it is outside the band.  Contacts are mutual, so a partner in
     // the band has its place in loc; the test against n keeps the access inside
@@ -404,16 +450,82 @@ __global__ __launch_bounds__(BLOCK) void k_patches(Parts<typename Prec<P>::T> pt
                                                    Consts<typename Prec<P>::T> k, Adj adj, int32_t *__restrict__ deg,
                                                 PatchGrid g, int last, int32_t *__restrict__ left,
                                                 int32_t *__restrict__ place_of, int32_t *__restrict__ nleft,
-                                                int32_t *__restrict__ coll_part, int32_t *__restrict__ wall_part) {
-  __shared__ PatchLds<typename Prec<P>::T, BLOCK, HELD> S;
-  patches_body<P, BLOCK, HELD, FIRST>(S, xcd_block<XCD_RUN_PATCHES>(blockIdx.x, gridDim.x), pt, cs, k, adj, deg, g,
-                                   last != 0, left, place_of, nleft, coll_part, wall_part);
+                                                int32_t *__restrict__ full, int32_t *__restrict__ coll_part,
+                                                int32_t *__restrict__ wall_part) {
+  __shared__ PatchLds<typename Prec<P>::T, HELD> S;
+  patches_body<P, HELD, FIRST>(S, xcd_block<XCD_RUN_PATCHES>(blockIdx.x, gridDim.x), pt, cs, k, adj, deg, g,
+                                   last != 0, left, place_of, nleft, full, coll_part, wall_part);
+}
+
+constexpr int CLUSTERS_SL = 4;  // slots per lane of the cluster kernel over many particles
+
+// The whole bed by clusters, one from each candidate root: a particle whose
+// partners all have higher indices.  A workgroup takes SL BLOCK slots.  A resolved
+// particle is marked DONE_WHOLE in its degree, not cleared, since other candidates
+// of its cluster may still be gathering.  Bound by the chain of dependent loads
+// from a root through its cluster, in the lanes' cluster size at a time: on the
+// 2 M-sphere riser, FP32, 82 us with four slots per lane, whose candidates fill
+// the lanes, against 143 from candidate lists of one slot per lane.
+template <int P, int SL> struct RootsLds {
+  ClustersLds<P, BLOCK, SL * BIG_LIST> cl;
+  long long cand[SL * BLOCK];
+  long long sh[BLOCK / 64];
+  int n;
+};
+template <int P, int SL>
+__device__ __forceinline__ void clusters_body(RootsLds<P, SL> &S, const int bidx, Parts<typename Prec<P>::T> pt,
+    const Consts<typename Prec<P>::T> &k, Adj adj, int32_t *deg, int32_t *sweep, long long *coll_part,
+    long long *wall_part) {
+  const int tid = (int)threadIdx.x, lane = tid & 63, s0 = bidx * SL * BLOCK + tid;
+  // an overflowed contact row leaves the graph incomplete: nothing is resolved
+  const bool overflow = __hip_atomic_load(&k.flags[FLAG_CAPACITY], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+  if (tid == 0) S.n = 0;
+  int d[SL], id[SL];
+  long long e[SL];
+#pragma unroll
+  for (int j = 0; j < SL; ++j) d[j] = s0 + j * BLOCK < k.npart ? ldu(deg, s0 + j * BLOCK) : 0;
+#pragma unroll
+  for (int j = 0; j < SL; ++j)
+    if (d[j] > 0) {
+      id[j] = ldu(pt.pid, s0 + j * BLOCK);
+      e[j] = adj.row(s0 + j * BLOCK).a[0];
+    }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < SL; ++j) {
+    const bool c = d[j] > 0 && (int)(e[j] >> 32) > id[j];
+    const unsigned long long m = __ballot(c);
+    int b = 0;
+    if (lane == 0 && m) b = atomicAdd(&S.n, __popcll(m));
+    b = __shfl(b, 0, 64);
+    if (c) S.cand[b + __popcll(m & ((1ull << lane) - 1))] = ((long long)id[j] << 32) | (unsigned)(s0 + j * BLOCK);
+  }
+  __syncthreads();
+  const int tot = overflow ? 0 : S.n;
+  if (tot == 0) {  // uniform
+    if (tid == 0) coll_part[bidx] = wall_part[bidx] = 0;
+    return;
+  }
+  long long ncoll = 0, nwall = 0, tc, tw;
+  resolve_candidates<P>(S.cl, tot, [&](int f) { return S.cand[f]; }, pt, adj, deg, deg, k, &sweep[SW_MORE], ncoll,
+                        nwall);
+  block_sum2(ncoll, nwall, S.sh, tc, tw);
+  if (tid == 0) {
+    coll_part[bidx] = tc;
+    wall_part[bidx] = tw;
+  }
+}
+template <int P, int SL>
+__global__ __launch_bounds__(BLOCK) void k_clusters(Parts<typename Prec<P>::T> pt,
+                                                         Consts<typename Prec<P>::T> k, Adj adj, int32_t *deg,
+                                                         int32_t *sweep, long long *coll_part, long long *wall_part) {
+  __shared__ RootsLds<P, SL> S;
+  clusters_body<P, SL>(S, xcd_block<XCD_RUN_CLUSTERS>(blockIdx.x, gridDim.x), pt, k, adj, deg, sweep, coll_part,
+                            wall_part);
 }
 
 // The clusters that are left, of the whole bed in one workgroup, by the same
-// firing rule.  The particles come from the list of the last pass, or, with no
-// pass, from the degrees (a bed of few particles needs no
-// patches); place_of maps a slot to its place among them.  A pair can only become
+// firing rule.  left lists them; place_of maps a slot to its place among them.  A pair can only become
 // ready when one of the two has just gone on to it, so a particle that goes on
 // wakes itself and its new partner, and a round looks at the awake alone: most
 // wavefronts read one word and meet at the barriers, and a long chain of pairs
@@ -438,7 +550,7 @@ __device__ __forceinline__ int final_place(const int32_t *place_of, long long e)
 // marks of a thread's particles are one word.
 template <int P>
 __device__ __forceinline__ void final_lds(FinalLds<P> &S, Parts<typename Prec<P>::T> pt,
-    const Consts<typename Prec<P>::T> &k, Adj adj, int32_t *deg, const int32_t *left, const int32_t *place_of,
+    const Consts<typename Prec<P>::T> &k, Adj adj, const int32_t *deg, const int32_t *left, const int32_t *place_of,
     const int n, int *busy, int &ncoll, int &nwall) {
   using T = typename Prec<P>::T;
   constexpr int PT = FINAL_PT;
@@ -553,7 +665,6 @@ __device__ __forceinline__ void final_lds(FinalLds<P> &S, Parts<typename Prec<P>
       nwall += Pos<P>::walls_key(k, ldu(pt.key, sl[j]), S.x[at_place(j)], S.y[at_place(j)], vx, vy);
       pt.vx[sl[j]] = vx;
       pt.vy[sl[j]] = vy;
-      deg[sl[j]] = 0;
     }
 }
 
@@ -565,7 +676,7 @@ struct FinalMem {  // by place, each [N]
 };
 template <int P>
 __device__ __forceinline__ void final_mem(const FinalMem M, Parts<typename Prec<P>::T> pt,
-    const Consts<typename Prec<P>::T> &k, Adj adj, int32_t *deg, const int32_t *left, const int32_t *place_of,
+    const Consts<typename Prec<P>::T> &k, Adj adj, const int32_t *deg, const int32_t *left, const int32_t *place_of,
     const int n, int *cnt,
     int &ncoll, int &nwall) {
   constexpr int NT = FINAL_THREADS;
@@ -637,118 +748,177 @@ __device__ __forceinline__ void final_mem(const FinalMem M, Parts<typename Prec<
     __syncthreads();
     m = cnt[b];
   }
-  for (int c = tid; c < n; c += NT) {
-    nwall += wall_pass<P>(k, pt, left[c]);
-    deg[left[c]] = 0;
-  }
+  for (int c = tid; c < n; c += NT) nwall += wall_pass<P>(k, pt, left[c]);
 }
 
-template <int P>
-__device__ __forceinline__ void final_body(FinalLds<P> &S, Parts<typename Prec<P>::T> pt,
-    const Consts<typename Prec<P>::T> &k, Adj adj, int32_t *deg, const bool whole, int32_t *left, int32_t *place_of,
-    const int nleft, const FinalMem M, int32_t *__restrict__ coll_part, int32_t *__restrict__ wall_part) {
-  __shared__ int cnt[3], tot[2], np;
+// What is left, for the final workgroup: of a bed of few particles everything
+// (PLAN_WHOLE); after the patches what the last pass listed, where it is more than
+// the final workgroup holds only what is left once the lanes and wavefronts of
+// all workgroups have taken its clusters; of a bed resolved by clusters those too
+// large for a workgroup.  The final workgroup is then the one that ends last; if
+// there is nothing to do before it, the others end at once.  At most one
+// workgroup per CU, since each has the LDS of the final one.  1 M spheres in the
+// bottom 30 % of a riser laid out for twice the height, 300 000 of them left: 180
+// us, against 250 with a pass of wider patches and the final workgroup in memory.
+constexpr int REST_BLOCKS = 256, REST_BIG = 512;
+struct RestBuffers {
+  int32_t *left, *left2, *place_of;
+  int32_t *sweep;        // SW_LEFT to SW_ENDED
+  int32_t *coll, *wall;  // by workgroup
+  FinalMem mem;
+};
+template <int P> union RestLds {
+  FinalLds<P> fin;
+  struct {
+    ClustersLds<P, FINAL_THREADS, REST_BIG> cl;
+    long long cand[FINAL_THREADS];
+    int n;
+  };
+};
+// A value that is the same in every lane, in a scalar register.
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+// LISTS: the bed may have come by patches, or whole; CLUSTERS: by clusters.
+template <int P, bool LISTS, bool CLUSTERS>
+__device__ __forceinline__ void rest_body(const int bidx, const int gdim, const int plan, const bool listed,
+    Parts<typename Prec<P>::T> pt, const Consts<typename Prec<P>::T> &k, Adj adj, int32_t *deg, const RestBuffers R) {
+  __shared__ RestLds<P> U;
+  __shared__ int cnt[3], tot[2], np, base, ended;
   const int tid = (int)threadIdx.x, lane = tid & 63;
-  const bool overflow = __hip_atomic_load(&k.flags[FLAG_CAPACITY], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
-  int n = nleft;
+  // an overflowed contact row leaves the graph incomplete: nothing is resolved
+  const bool overflow =
+      uniform(__hip_atomic_load(&k.flags[FLAG_CAPACITY], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != 0;
+  int n = 0;
+  bool second = false;  // the list is left2
+  bool first = false;  // work for all workgroups before the final one
+  const bool clusters = CLUSTERS && (!LISTS || plan == PLAN_CLUSTERS), whole = LISTS && plan == PLAN_WHOLE;
+  if (clusters) {
+    first = uniform(R.sweep[SW_MORE]) != 0;
+  } else if (!whole) {
+    n = uniform(R.sweep[SW_LEFT]);
+    if (listed && n > FINAL_CAP) {  // the second pass was needed
+      n = uniform(R.sweep[SW_LEFT2]);
+      second = true;
+    }
+    first = n > FINAL_CAP;
+  }
+  if (overflow) {
+    first = false;
+    n = 0;
+  }
+  if (!first && bidx != 0) {  // nothing to do but for the final workgroup
+    if (tid == 0) R.coll[bidx] = R.wall[bidx] = 0;
+    return;
+  }
+  // Appends the particle in slot l, where `has`, to the list `to`, whose length is
+  // np; with count, *count is the length and the others append to it too.
+  auto append = [&](bool has, int l, int32_t *to, int32_t *count) {
+    const unsigned long long m = __ballot(has);
+    int at = 0;
+    if (lane == 0 && m) at = atomicAdd(&np, __popcll(m));
+    at = __shfl(at, 0, 64) + __popcll(m & ((1ull << lane) - 1));
+    if (count) {
+      __syncthreads();
+      if (tid == 0) {
+        base = np > 0 ? atomicAdd(count, np) : 0;
+        np = 0;
+      }
+      __syncthreads();
+      at += base;
+    }
+    if (has) {
+      to[at] = l;
+      R.place_of[l] = at;
+    }
+  };
+  int ncoll = 0, nwall = 0;
+  // The final workgroup's n particles in `left`, and the sums.
+  auto finish = [&](const int32_t *left) {
+    if (n > 0) {
+      if (n <= FINAL_CAP) final_lds<P>(U.fin, pt, k, adj, deg, left, R.place_of, n, cnt, ncoll, nwall);
+      else final_mem<P>(R.mem, pt, k, adj, deg, left, R.place_of, n, cnt, ncoll, nwall);
+    }
+    if (ncoll) atomicAdd(&tot[0], ncoll);
+    if (nwall) atomicAdd(&tot[1], nwall);
+    __syncthreads();
+    if (tid == 0) {
+      R.coll[bidx] = tot[0];
+      R.wall[bidx] = tot[1];
+    }
+  };
   if (tid < 2) tot[tid] = 0;
   if (tid == 0) np = 0;
   __syncthreads();
-  if (whole) {
-    for (int l0 = 0; l0 < k.npart; l0 += FINAL_THREADS) {
-      const int l = l0 + tid;
-      const bool has = l < k.npart && ldu(deg, l) > 0;
-      const unsigned long long m = __ballot(has);
-      int at = 0;
-      if (lane == 0 && m) at = atomicAdd(&np, __popcll(m));
-      at = __shfl(at, 0, 64);
-      if (has) {
-        const int to = at + __popcll(m & ((1ull << lane) - 1));
-        left[to] = l;
-        place_of[l] = to;
+  if (!first) {
+    if (whole) {
+      for (int l0 = 0; l0 < k.npart && !overflow; l0 += FINAL_THREADS)
+        append(l0 + tid < k.npart && ldu(deg, l0 + tid) > 0, l0 + tid, R.left, nullptr);
+      __syncthreads();
+      n = uniform(np);
+    }
+    finish(second ? R.left2 : R.left);
+  } else {  // (the final workgroup's code again: its registers are its own so)
+    if (clusters) {
+      for (int l0 = bidx * FINAL_THREADS; l0 < k.npart; l0 += gdim * FINAL_THREADS) {
+        const int d = l0 + tid < k.npart ? ldu(deg, l0 + tid) : 0;
+        append(d > 0 && d < DONE_WHOLE, l0 + tid, R.left, &R.sweep[SW_LISTED]);
       }
-    }
-    __syncthreads();
-    n = np;
-  }
-  int ncoll = 0, nwall = 0;
-  if (n > 0 && !overflow) {  // uniform
-    if (n <= FINAL_CAP) final_lds<P>(S, pt, k, adj, deg, left, place_of, n, cnt, ncoll, nwall);
-    else final_mem<P>(M, pt, k, adj, deg, left, place_of, n, cnt, ncoll, nwall);
-  }
-  if (ncoll) atomicAdd(&tot[0], ncoll);
-  if (nwall) atomicAdd(&tot[1], nwall);
-  __syncthreads();
-  if (tid == 0) {
-    coll_part[0] = tot[0];
-    wall_part[0] = tot[1];
-  }
-}
-
-// What the passes before left: the final workgroup, if it can hold it; else
-// another pass of patches first, after which the workgroup that ends last is
-// the final one.  The others end at once where the pass is not needed; it keeps
-// the final workgroup's share small where a bed is denser in places than the
-// patches were laid out for.  At most one workgroup per CU, since each has the
-// LDS of the final one.
-constexpr int REST_BLOCKS = 256;
-struct RestBuffers {
-  int32_t *left, *left2, *place_of;
-  int32_t *sweep;  // SW_LEFT to SW_LEFT3, SW_ENDED
-  FinalMem mem;
-};
-template <int P>
-__device__ __forceinline__ void rest_body(const int bidx, const int gdim, const bool listed,
-    Parts<typename Prec<P>::T> pt, const int32_t *__restrict__ cs, const Consts<typename Prec<P>::T> &k, Adj adj, int32_t *deg, const bool whole,
-    const PatchGrid g, const RestBuffers R, int32_t *__restrict__ pass_coll, int32_t *__restrict__ pass_wall,
-    int32_t *__restrict__ coll_part, int32_t *__restrict__ wall_part) {
-  __shared__ union {
-    PatchLds<typename Prec<P>::T, PATCH_WIDE, PATCH_HELD2> patch;
-    FinalLds<P> fin;
-  } U;
-  __shared__ int ended;
-  int n = 0;
-  int32_t *left = R.left, *next = R.left2;
-  if (!whole) {
-    n = R.sweep[SW_LEFT];
-    int at = SW_LEFT2;
-    if (listed && n > FINAL_CAP) {  // the second pass was needed
-      n = R.sweep[SW_LEFT2];
-      at = SW_LEFT3;
-      left = R.left2;
-      next = R.left;
-    }
-    if (n <= FINAL_CAP) {  // uniform over the launch
-      for (int i = bidx * FINAL_THREADS + (int)threadIdx.x; i < g.count(); i += gdim * FINAL_THREADS)
-        pass_coll[i] = pass_wall[i] = 0;
-      if (bidx != 0) return;
-    } else {
-      for (int i = bidx; i < g.count(); i += gdim) {
-        patches_body<P, PATCH_WIDE, PATCH_HELD2, false>(U.patch, i, pt, cs, k, adj, deg, g, true, next,
-                                                        R.place_of, R.sweep + at, pass_coll, pass_wall);
+    } else if constexpr (LISTS) {
+      // runs of the list, so many that every workgroup has one
+      const int32_t *left = second ? R.left2 : R.left;
+      const int run = min(max((n + gdim - 1) / gdim, WAVE), FINAL_THREADS);
+      long long nc = 0, nw = 0;
+      for (int i0 = bidx * run; i0 < n; i0 += gdim * run) {
+        if (tid == 0) U.n = 0;
+        __syncthreads();
+        bool c = false;
+        long long r = 0;
+        if (tid < run && i0 + tid < n) {
+          const int s = left[i0 + tid], id = pt.pid[s];
+          c = (int)(adj.row(s).a[0] >> 32) > id;
+          r = ((long long)id << 32) | (unsigned)s;
+        }
+        const unsigned long long m = __ballot(c);
+        int at = 0;
+        if (lane == 0 && m) at = atomicAdd(&U.n, __popcll(m));
+        at = __shfl(at, 0, 64);
+        if (c) U.cand[at + __popcll(m & ((1ull << lane) - 1))] = r;
+        __syncthreads();
+        resolve_candidates<P>(U.cl, U.n, [&](int f) { return U.cand[f]; }, pt, adj, deg, deg, k, &R.sweep[SW_MORE],
+                              nc, nw);
         __syncthreads();
       }
-      __threadfence();
-      __syncthreads();
-      if (threadIdx.x == 0) ended = atomicAdd(&R.sweep[SW_ENDED], 1);
-      __syncthreads();
-      if (ended != gdim - 1) return;  // uniform
-      __threadfence();
-      n = __hip_atomic_load(&R.sweep[at], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      left = next;
+      ncoll = (int)nc;
+      nwall = (int)nw;
     }
+    __threadfence();
+    __syncthreads();
+    if (tid == 0) ended = atomicAdd(&R.sweep[SW_ENDED], 1);
+    __syncthreads();
+    const int listed_n = n;
+    n = 0;
+    if (uniform(ended) == gdim - 1) {
+      __threadfence();
+      if (clusters) {
+        n = uniform(__hip_atomic_load(&R.sweep[SW_LISTED], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+      } else if (__hip_atomic_load(&R.sweep[SW_MORE], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
+        for (int i0 = 0; i0 < listed_n; i0 += FINAL_THREADS) {
+          const int l = i0 + tid < listed_n ? (second ? R.left2 : R.left)[i0 + tid] : -1;
+          append(l >= 0 && deg[l] < DONE_WHOLE, l, second ? R.left : R.left2, nullptr);
+        }
+        __syncthreads();
+        n = uniform(np);
+        second = !second;
+      }
+    }
+    finish(second ? R.left2 : R.left);
   }
-  final_body<P>(U.fin, pt, k, adj, deg, whole, left, R.place_of, n, R.mem, coll_part, wall_part);
 }
-template <int P, bool PASSES>
-__global__ __launch_bounds__(FINAL_THREADS) void k_rest(Parts<typename Prec<P>::T> pt, const int32_t *__restrict__ cs,
+template <int P, int PLAN>
+__global__ __launch_bounds__(FINAL_THREADS) void k_rest(Parts<typename Prec<P>::T> pt,
                                                         Consts<typename Prec<P>::T> k, Adj adj, int32_t *deg,
-                                                        PatchGrid g, RestBuffers R, int32_t *__restrict__ pass_coll,
-                                                        int32_t *__restrict__ pass_wall,
-                                                        int32_t *__restrict__ coll_part,
-                                                        int32_t *__restrict__ wall_part) {
-  rest_body<P>(blockIdx.x, gridDim.x, false, pt, cs, k, adj, deg, !PASSES, g, R, pass_coll, pass_wall, coll_part,
-               wall_part);
+                                                        RestBuffers R) {
+  constexpr bool CLUSTERS = PLAN == PLAN_CLUSTERS;
+  rest_body<P, !CLUSTERS, CLUSTERS>(blockIdx.x, gridDim.x, PLAN, false, pt, k, adj, deg, R);
 }
 
 }  // namespace lbdps

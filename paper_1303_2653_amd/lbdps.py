@@ -90,6 +90,7 @@ _SIGS = {
     "lbdps_counters": (c_i32, [c_vp, ctypes.POINTER(c_i64)]),
     "lbdps_outlet_crossings": (c_i32, [c_vp, ctypes.POINTER(c_i64), ctypes.POINTER(c_i64)]),
     "lbdps_tile_stats": (c_i32, [c_vp, ctypes.POINTER(c_i64)]),
+    "lbdps_row_stats": (c_i32, [c_vp, ctypes.POINTER(c_i64)]),
     "lbdps_time_kernels": (c_i32, [c_vp, ctypes.c_uint32]),
     "lbdps_kernel_times": (c_i32, [c_vp, ctypes.POINTER(c_dbl), ctypes.POINTER(c_i64)]),
     "lbdps_set_tuning": (c_i32, [c_vp, ctypes.POINTER(lbdps_tuning)]),
@@ -362,6 +363,12 @@ class Sim:
         out = (c_i64 * 2)()
         check(lbdps_tile_stats(self.ctx, out), "lbdps_tile_stats")
         return out[0], out[1]
+
+    def row_stats(self):
+        """lbdps_row_stats: the course of the most recent collision stage."""
+        out = (c_i64 * 5)()
+        check(lbdps_row_stats(self.ctx, out), "lbdps_row_stats")
+        return dict(plan=out[0], left=out[1], left2=out[2], full=out[3], more=out[4])
 
     def outlet_crossings(self):
         """(net particles across the outlet plane y = ny upward, steps) since
