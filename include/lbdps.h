@@ -499,9 +499,10 @@ lbdps_status lbdps_get_tuning(lbdps_ctx *ctx, lbdps_tuning *t);
  * the candidates in turn, time them with hipEvents on the context's stream and
  * keep the candidate with the fastest of its two times (written to *chosen if
  * not NULL): first the collision stage's tile shapes (4, none among them),
- * then the cluster-resolution shapes (9) and then the drag tile shapes (3),
- * each under the choices before it.  The bed advances by 2 x steps x 16.
- * Synchronises. */
+ * then, if it takes one, the cluster-resolution shapes (9), which have an effect
+ * there alone, and then the drag tile shapes (3), each under the choices before
+ * it.  The bed advances by 2 x steps x 7, or x 16 with the cluster-resolution
+ * shapes.  Synchronises. */
 lbdps_status lbdps_autotune(lbdps_ctx *ctx, int32_t steps, lbdps_tuning *chosen);
 
 /* Release the host context (the workspace stays the caller's).  A bed of a
@@ -557,22 +558,19 @@ lbdps_status lbdps_batch_sync(lbdps_batch *batch);
 
 /* As lbdps_time_kernels / lbdps_kernel_times, for the batched launches of
  * lbdps_batch_step (each timed launch covers every bed; graph replays are not
- * timed).  LBDPS_K_RESOLVE sums both resolution launches of a step and counts
+ * timed).  LBDPS_K_RESOLVE sums the resolution launches of a step and counts
  * them as one. */
 lbdps_status lbdps_batch_time_kernels(lbdps_batch *batch, uint32_t mask);
 lbdps_status lbdps_batch_kernel_times(lbdps_batch *batch, double *h_ms, int64_t *h_launches);
 
 /*
- * Autotuner of a batch: beds are grouped into size classes by particle count
- * (up to 2048, 4096, 8192, ...).  Class by class, every candidate
- * cluster-resolution shape is applied to the class's beds and `steps` batched
- * steps are timed, twice over the candidates in turn; the candidate with the
- * fastest of its two times is kept.  Then the drag tile shapes are timed the
- * same way on the whole batch (one drag launch covers every bed, so the beds
- * share the fastest).  Every bed advances by the steps taken.  cache_path (or
- * NULL): a text file of chosen shapes per class and precision; when every
- * class is found there nothing is timed, and the file is rewritten with all
- * classes.  Synchronises.
+ * Autotuner of a batch: `steps` batched steps are timed under each drag tile
+ * shape, twice over the shapes in turn, and the one with the fastest of its two
+ * times is kept (one drag launch covers every bed, so the beds share it).  Every
+ * bed advances by 2 x steps x 3.  cache_path (or NULL): a text file of the shapes
+ * per precision and size class of the beds by particle count (up to 2048, 4096,
+ * 8192, ...); when every class is found there nothing is timed, the beds take
+ * their class's shapes, and the file is rewritten with all classes.  Synchronises.
  */
 lbdps_status lbdps_batch_autotune(lbdps_batch *batch, int32_t steps, const char *cache_path);
 

@@ -1498,11 +1498,12 @@ lbdps_status lbdps_set_tuning(lbdps_ctx *x, const lbdps_tuning *t) {
 
 namespace {
 
-// Launch shapes the autotuner tries (all give identical results).
+// Launch shapes of the tile stage's cluster resolution that the autotuner tries
+// (all give identical results).
 const lbdps_tuning kTuneCandidates[] = {
     {1, RC_GROUPS_MAX, 0}, {2, RC_GROUPS_MAX, 0}, {4, RC_GROUPS_MAX, 0}, {8, RC_GROUPS_MAX, 0},
     {16, RC_GROUPS_MAX, 0}, {1, 4096, 0},         {1, 1024, 0},          {4, 1024, 0},
-    {1, 128, 0},  // few contacts: a small grid reads the candidate counts and is done
+    {1, 128, 0},  // the tiles leave few clusters: a small grid reads their number and is done
 };
 constexpr int kTuneN = (int)(sizeof(kTuneCandidates) / sizeof(kTuneCandidates[0]));
 
@@ -1537,9 +1538,7 @@ lbdps_status lbdps_autotune(lbdps_ctx *x, int32_t steps, lbdps_tuning *chosen) {
   if (!x) return fail(LBDPS_E_INVALID, "ctx is NULL");
   if (steps < 1) return fail(LBDPS_E_INVALID, "steps must be >= 1");
   // Two interleaved rounds over the candidates; each keeps its faster time, so
-  // a single disturbed measurement does not decide.  The cluster-resolution
-  // shapes first (under the context's drag tile), then the drag tile shapes
-  // under the chosen cluster shape: the two phases do not share work.
+  // a single disturbed measurement does not decide.
   const lbdps_tuning start = x->tune;
   constexpr int NC = SPHERE_TILES + kTuneN + DRAG_TILES;
   float t[NC];
@@ -1561,14 +1560,15 @@ lbdps_status lbdps_autotune(lbdps_ctx *x, int32_t steps, lbdps_tuning *chosen) {
     x->tune = cand[bc];
     return LBDPS_OK;
   };
-  // the collision stage's tile shapes (none among them), then the cluster
-  // shapes, then the drag tiles, each under the choices before it
+  // the collision stage's tile shapes (none among them), then, if it takes a tile,
+  // the cluster shapes, which act there alone, then the drag tiles, each under the
+  // choices before it
   for (int c = 0; c < SPHERE_TILES; ++c) {
     cand[c] = start;
     cand[c].sphere_tile = c;
   }
   lbdps_status st = run(0, SPHERE_TILES);
-  if (st == LBDPS_OK) {
+  if (st == LBDPS_OK && x->tune.sphere_tile > 0) {
     for (int c = 0; c < kTuneN; ++c) {
       cand[SPHERE_TILES + c] = kTuneCandidates[c];
       cand[SPHERE_TILES + c].drag_tile = x->tune.drag_tile;
@@ -2095,8 +2095,7 @@ lbdps_status lbdps_batch_autotune(lbdps_batch *B, int32_t steps, const char *cac
     }
   }
   // The drag tile shape is one for the whole batch (one launch per phase):
-  // the cached one, else bed 0's while the classes are tuned, then the
-  // fastest of the shapes on the whole batched step.
+  // the cached one, else the fastest of the shapes on the whole batched step.
   bool all_cached = true;
   for (auto &kv : cls) all_cached = all_cached && cached.count(kv.first);
   int tile = all_cached && !cached.empty() ? cached.begin()->second.drag_tile : B->beds[0]->tune.drag_tile;
@@ -2111,29 +2110,12 @@ lbdps_status lbdps_batch_autotune(lbdps_batch *B, int32_t steps, const char *cac
       }
       continue;
     }
-    float t[kTuneN];
-    for (int round = 0; round < 2; ++round)  // as lbdps_autotune: the faster of two times per candidate
-      for (int c = 0; c < kTuneN; ++c) {
-        for (int b : kv.second) {
-          B->beds[b]->tune = kTuneCandidates[c];
-          B->beds[b]->tune.drag_tile = tile;
-        }
-        float ms = 0.f;
-        lbdps_status st = time_on(B->stream, [&]() { return lbdps_batch_step(B, steps); }, &ms);
-        if (st != LBDPS_OK) return st;
-        t[c] = round == 0 ? ms : std::min(t[c], ms);
-      }
-    int bc = 0;
-    for (int c = 1; c < kTuneN; ++c)
-      if (t[c] < t[bc]) bc = c;
-    lbdps_tuning bt = kTuneCandidates[bc];
-    bt.drag_tile = tile;
-    for (int b : kv.second) B->beds[b]->tune = bt;
-    cached[kv.first] = bt;
+    // a batch has no tile stage, whose shapes the other fields are
+    cached[kv.first] = B->beds[kv.second[0]]->tune;
   }
   if (!all_cached) {
     float t[DRAG_TILES];
-    for (int round = 0; round < 2; ++round)
+    for (int round = 0; round < 2; ++round)  // as lbdps_autotune: the faster of two times per candidate
       for (int d = 0; d < DRAG_TILES; ++d) {
         for (auto *x : B->beds) x->tune.drag_tile = d;
         float ms = 0.f;

@@ -465,8 +465,8 @@ class Batch:
         check(lbdps_batch_step(self.batch, int(nsteps)), "lbdps_batch_step")
 
     def autotune(self, steps: int = 4, cache_path=None) -> list:
-        """Choose launch shapes per bed size class (see lbdps_batch_autotune);
-        returns each bed's tuning."""
+        """Choose the batch's launch shapes (see lbdps_batch_autotune); returns
+        each bed's tuning."""
         path = None if cache_path is None else os.fsencode(cache_path)
         check(lbdps_batch_autotune(self.batch, int(steps), path), "lbdps_batch_autotune")
         return [b.tuning() for b in self.beds]
