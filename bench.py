@@ -170,15 +170,17 @@ def run_gpu(cfg, prec, steps, warmup, torch, L, dominant=None, tuning=None):
 
 
 CSRC = os.path.join(ROOT, "paper_1303_2653_amd", "csrc")
-KERNEL_SOURCES = ("kernels.hpp", "device.hpp", "lattice3d.hpp", "spheres_tile.hpp")
+KERNEL_SOURCES = ("kernels.hpp", "device.hpp", "lattice3d.hpp", "patches.hpp", "spheres_tile.hpp")
 # the 3-D coupled step's kernels also live in coupled3d.hpp
 KERNEL_SOURCES_3D = KERNEL_SOURCES + ("coupled3d.hpp",)
 # the kernels of each phase (either form of a kernel, and every launch of the
 # phase: the collision stage's tile kernel with the contact kernel on what it
-# left, the cluster kernel with the ordered sweep)
+# left; the patch passes or the clusters with the rest, or behind the tiles the
+# cluster kernel with the ordered sweep).  The last one runs once per phase.
 KERNEL_KEYS = {"collide": ("k_collide",), "drag": ("k_drag", "k_drag_flat"), "scan": ("k_scan_cells",),
                "scatter": ("k_scatter",), "contacts": ("k_spheres_tile", "k_contacts", "k_contacts_small"),
-               "resolve": ("k_resolve_clusters", "k_resolve"), "k3_bgk": ("k3_bgk", "k3_bgk_pairs"), "k3_psm": ("k3_psm", "k3_psm_pairs")}
+               "resolve": ("k_resolve_clusters", "k_resolve", "k_patches", "k_clusters", "k_rest"),
+               "k3_bgk": ("k3_bgk", "k3_bgk_pairs"), "k3_psm": ("k3_psm", "k3_psm_pairs")}
 # the whole 3-D coupled step: every kernel it launches once per step
 STEP3D_KEYS = {"step3d": ("k3c_collide", "k3c_gradp", "k3c_drag", "k_scan_reduce", "k_scan_top", "k_scan_apply",
                           "k3c_scatter", "k3c_contacts", "k3c_clusters", "k3c_resolve")}
@@ -238,9 +240,9 @@ def summarize(args):
             acc = {}
             for r in rows(d, "*counter_collection.csv"):
                 acc.setdefault(short(r["Kernel_Name"]), []).append(float(r["Counter_Value"]) * 1024.0)
-            return {k: sum(v) / len(v) for k, v in acc.items()}
-        fetch, write = per_kernel(args.fetch), per_kernel(args.write)
-        cf, cw = per_kernel(args.copy_fetch), per_kernel(args.copy_write)
+            return {k: sum(v) / len(v) for k, v in acc.items()}, {k: len(v) for k, v in acc.items()}
+        (fetch, calls), (write, _) = per_kernel(args.fetch), per_kernel(args.write)
+        (cf, _), (cw, _) = per_kernel(args.copy_fetch), per_kernel(args.copy_write)
         copy_name = max(cf, key=lambda k: cf[k])  # the copy: the only probe kernel that reads
         f_scale = args.copy_bytes / cf[copy_name]
         w_scale = args.copy_bytes / cw[copy_name]
@@ -254,7 +256,7 @@ def summarize(args):
                 b = 0.0
                 for kname in names:
                     bk = fetch[kname] * f_scale + write[kname] * w_scale
-                    b += bk
+                    b += bk * calls[kname] / calls[names[-1]] if key == "resolve" else bk
                     lines.append(f"| {kname} | {fetch[kname] / 1024:.1f} | {write[kname] / 1024:.1f} | {int(bk)} |")
                 traffic[key] = int(b)
         lines += ["", "Counter commands: the same program under `rocprofv3 --pmc FETCH_SIZE` and "
@@ -486,8 +488,8 @@ def run_beds(args, torch, L):
     batch = L.Batch(cfgs, precision=prec)
     st = batch.stream
     batch.step(args.warmup)
-    # launch shapes per bed size class; two rounds of 2 steps per candidate and
-    # class keep the tuning run within the beds' stable span (they are reset below)
+    # the drag tile shape; two rounds of 2 steps per candidate keep the tuning run
+    # within the beds' stable span (they are reset below)
     tunings = batch.autotune(steps=2)
     # every measured region starts again from the initial beds, after the warmup
     batch.reset()

@@ -12,7 +12,9 @@
 
 namespace lbdps {
 
-enum { PH_COLLIDE = 0, PH_DRAG, PH_SCAN, PH_SCATTER, PH_CONTACTS, PH_PATCH0, PH_PATCH1, PH_CLUSTERS, PH_REST, PH_COUNT };
+enum {
+  PH_COLLIDE = 0, PH_DRAG, PH_SCAN, PH_SCATTER, PH_CONTACTS, PH_PATCH0, PH_PATCH1, PH_CLUSTERS, PH_REST, PH_COUNT
+};
 
 template <int P> struct BedArgs {
   using T = typename Prec<P>::T;
@@ -81,8 +83,8 @@ __global__ __launch_bounds__(BLOCK) LBDPS_WAVES8 void kb_drag(const BedArgs<P> *
                          nullptr, a.ts, a.stay);
 }
 template <int P, int TX>
-__global__ __launch_bounds__(BLOCK) LBDPS_WAVES6 void kb_drag_flat(const BedArgs<P> *__restrict__ tab, const int *__restrict__ off,
-                                                      int nbeds, int flip) {
+__global__ __launch_bounds__(BLOCK) LBDPS_WAVES6 void kb_drag_flat(const BedArgs<P> *__restrict__ tab,
+                                                      const int *__restrict__ off, int nbeds, int flip) {
   LBDPS_BED_PROLOGUE(XCD_RUN_DRAG)
   drag_body_flat<P, TX>(bid, nbk, a.parts(cp), a.fl, a.cs, a.lut, a.k, a.count, a.rank, a.flags, nullptr, nullptr,
                         nullptr, a.ts, a.stay);
@@ -105,8 +107,8 @@ __global__ __launch_bounds__(BLOCK) void kb_scatter(const BedArgs<P> *__restrict
 
 // After the scatter the records are in the other set.
 template <int P>
-__global__ __launch_bounds__(BLOCK) LBDPS_WAVES8 void kb_contacts(const BedArgs<P> *__restrict__ tab, const int *__restrict__ off,
-                                                     int nbeds, int flip) {
+__global__ __launch_bounds__(BLOCK) LBDPS_WAVES8 void kb_contacts(const BedArgs<P> *__restrict__ tab,
+                                                     const int *__restrict__ off, int nbeds, int flip) {
   LBDPS_BED_PROLOGUE(XCD_RUN_CONTACTS)
   (void)nbk;
   contacts_body<P>(bid, a.parts(1 - cp), a.cs, a.k, a.adj, a.deg, a.flags, a.pair_part, a.wall0_part,

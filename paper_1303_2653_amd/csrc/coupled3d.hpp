@@ -61,7 +61,9 @@ template <class T> struct Fields3 {
   Node4<T> *gas, *grad;  // (u_gas x, y, z, solid fraction), (beta, grad p x, y, z)
 };
 
-// i / n for 0 <= i < 2^31 as (2 i m) >> 32 >> s, m = ceil(2^(31 + s) / n), 2^s >= n.
+// i / n for 0 <= i < 2^31 as (2 i m) >> 32 >> s, m = ceil(2^(31 + s) / n), 2^s >= n:
+// division by an invariant integer using multiplication (Granlund and Montgomery,
+// PLDI 1994).
 struct Divisor {
   unsigned m;
   int s;

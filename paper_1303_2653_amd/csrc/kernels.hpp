@@ -1411,7 +1411,8 @@ __device__ __forceinline__ void contacts_body(const int bidx, Parts<typename Pre
     const T fx = Pos<P>::G ? x - (T)cx : x, fy = Pos<P>::G ? y - (T)cy : y;  // position in the cell
     const T margin = (T)1e-5, dd = k.d * k.d;
     const bool use_l = fx < k.d + margin, use_r = fx > (T)1 - k.d - margin;
-    const bool use_b = fy < k.d + margin && (cy > 0 || k.per_y), use_t = fy > (T)1 - k.d - margin && (cy + 1 < k.ny || k.per_y);
+    const bool use_b = fy < k.d + margin && (cy > 0 || k.per_y);
+    const bool use_t = fy > (T)1 - k.d - margin && (cy + 1 < k.ny || k.per_y);
     const int left = use_l && cx > 0, right = use_r && cx + 1 < k.nx;
     const int row0 = key - cx;
     const int row_b = cy > 0 ? row0 - k.nx : row0 + (k.ny - 1) * k.nx;
@@ -1563,8 +1564,8 @@ __device__ __forceinline__ void contacts_body(const int bidx, Parts<typename Pre
   }
 }
 template <int P, int MODE = CT_ALL>
-__global__ __launch_bounds__(BLOCK) LBDPS_WAVES8 void k_contacts(Parts<typename Prec<P>::T> pt, const int32_t *__restrict__ cs,
-                                                    Consts<typename Prec<P>::T> k, Adj adj,
+__global__ __launch_bounds__(BLOCK) LBDPS_WAVES8 void k_contacts(Parts<typename Prec<P>::T> pt,
+                                                    const int32_t *__restrict__ cs, Consts<typename Prec<P>::T> k, Adj adj,
                                                     int32_t *__restrict__ deg, int32_t *flags,
                                                     long long *pair_part, long long *wall_part, int32_t *sweep) {
   contacts_body<P, MODE>(xcd_block<XCD_RUN_CONTACTS>(blockIdx.x, gridDim.x), pt, cs, k, adj, deg, flags, pair_part,
@@ -1641,8 +1642,8 @@ __device__ __forceinline__ int wall_pass(const Consts<typename Prec<P>::T> &k, P
 // Contact clusters (connected components of the contact graph) are independent:
 // a pair only touches its two particles, so resolving every cluster's pairs in
 // lexicographic order gives the sequential sweep's result bit for bit.  The
-// tile kernel lists the particles whose neighbours all have higher indices:
-// every cluster's lowest index is among them.  A lane takes one
+// row stage looks for the particles whose neighbours all have higher indices, and
+// the tile kernel lists them: every cluster's lowest index is among them.  A lane takes one
 // such candidate, gathers its cluster breadth-first and gives up as soon as it
 // meets a lower index (the cluster belongs to another candidate).  Otherwise it
 // orders the members by index, applies the pairs in order, runs the wall pass
@@ -1650,10 +1651,10 @@ __device__ __forceinline__ int wall_pass(const Consts<typename Prec<P>::T> &k, P
 // waits for another.
 //
 // The cluster is gathered into CL_LDS entries of LDS; a larger one is queued
-// for the whole workgroup (below), and one the queue cannot take is left to
-// the ordered sweep of k_resolve.  Each workgroup takes the candidate lists of
-// a run of contact-kernel workgroups and deals their candidates out to its
-// lanes densely.
+// for the whole workgroup (below), and one the queue cannot take stays as it is,
+// for the final workgroup of the row stage or the ordered sweep of the tile stage.
+// Each workgroup takes the candidates of a run of slots, or of the tile kernel's
+// list, and deals them out to its lanes densely.
 constexpr int CL_LDS = 8;
 constexpr int RC_LISTS = 1;           // candidate lists per resolution workgroup (default)
 constexpr int RC_GROUPS_MAX = 1 << 30;  // most resolution workgroups (default: no limit)
@@ -1812,7 +1813,7 @@ __device__ __forceinline__ void resolve_cluster(Row q, int m, unsigned long long
 // wavefront (clusters of up to 64 members and 256 pairs; the four wavefronts of
 // a workgroup take queued clusters in parallel) or the whole workgroup (up to
 // 256 members and 1024 pairs, for clusters a wavefront could not hold).  A
-// cluster beyond that is left to the ordered sweep.
+// cluster beyond that stays as it is.
 constexpr int BIG_LIST = 64;  // clusters queued per workgroup for the group paths
 constexpr int WAVE = 64;
 
@@ -2119,8 +2120,8 @@ __global__ __launch_bounds__(BLOCK) void k_resolve_clusters(Parts<typename Prec<
                                                             long long *coll_part, long long *wall_part,
                                                             const long long *__restrict__ roots, int nlists,
                                                             const int32_t *nroots) {
-  resolve_clusters_body<P>(xcd_block<XCD_RUN_CLUSTERS>(blockIdx.x, gridDim.x), gridDim.x, pt, adj, deg, done, k, need_sweep, coll_part, wall_part, roots,
-      nlists, nroots);
+  resolve_clusters_body<P>(xcd_block<XCD_RUN_CLUSTERS>(blockIdx.x, gridDim.x), gridDim.x, pt, adj, deg, done, k,
+                           need_sweep, coll_part, wall_part, roots, nlists, nroots);
 }
 
 // Position of particle index g in the neighbour list of slot t: the number of

@@ -528,8 +528,9 @@ __global__ __launch_bounds__(BLOCK) void k_clusters(Parts<typename Prec<P>::T> p
 // firing rule.  left lists them; place_of maps a slot to its place among them.  A pair can only become
 // ready when one of the two has just gone on to it, so a particle that goes on
 // wakes itself and its new partner, and a round looks at the awake alone: most
-// wavefronts read one word and meet at the barriers, and a long chain of pairs
-// (150 rounds in a settled bed of 15 000 spheres) takes 0.6 us a link.
+// wavefronts read one word and meet at the barriers.  Bound by the longest chain of
+// pairs: 131 links in a settled bed of 15 000 spheres of d = 0.2, whose largest
+// cluster has 3 100, take 237 us in FP64, 1.8 us a link.
 template <int P> struct FinalLds {
   using T = typename Prec<P>::T;
   T x[FINAL_CAP], y[FINAL_CAP], vx[FINAL_CAP], vy[FINAL_CAP];

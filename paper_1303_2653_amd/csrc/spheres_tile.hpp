@@ -509,7 +509,8 @@ __device__ __forceinline__ void spheres_tile_body(const int bidx, Parts<typename
         done[s] = DONE_WHOLE;
         continue;
       }
-      // the neighbour row: every contact, sorted by index, as k_contacts writes it
+      // the neighbour row: every contact, sorted by index; without the partners' rows
+      // of cells, which k_contacts notes for the patches
       ++nleft;
       const AdjRow row = adj.row(s);
       const T x = L.x[q], y = L.y[q];
