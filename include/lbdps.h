@@ -455,15 +455,17 @@ lbdps_status lbdps_row_stats(lbdps_ctx *ctx, int64_t h_out[5]);
 /*
  * Time every later launch of the kernels in `mask` (bit k = lbdps_kernel k):
  * the launch carries a pair of hipEvents that its dispatch stamps at the
- * kernel's start and end (hipExtLaunchKernel), so the time is the kernel's own.
- * mask 0 stops.  For measurement only; the events belong to the context.
+ * kernel's start and end (hipExtLaunchKernel), so the time is the kernel's own;
+ * of a kernel class with several launches in a row (LBDPS_K_RESOLVE) the first
+ * carries one event and the last the other.  mask 0 stops.  For measurement only; the events belong to the context.
  */
 lbdps_status lbdps_time_kernels(lbdps_ctx *ctx, uint32_t mask);
 
 /*
  * Wait for the stream, then return per kernel the summed time in milliseconds
  * (h_ms[LBDPS_K_COUNT]) and the number of timed steps (h_launches[LBDPS_K_COUNT];
- * LBDPS_K_RESOLVE sums its two launches per step) since the previous call, and
+ * LBDPS_K_RESOLVE: from the start of its first launch to the end of its last)
+ * since the previous call, and
  * reset both.
  */
 lbdps_status lbdps_kernel_times(lbdps_ctx *ctx, double *h_ms, int64_t *h_launches);
@@ -558,7 +560,7 @@ lbdps_status lbdps_batch_sync(lbdps_batch *batch);
 
 /* As lbdps_time_kernels / lbdps_kernel_times, for the batched launches of
  * lbdps_batch_step (each timed launch covers every bed; graph replays are not
- * timed).  LBDPS_K_RESOLVE sums the resolution launches of a step and counts
+ * timed).  LBDPS_K_RESOLVE covers the resolution launches of a step and counts
  * them as one. */
 lbdps_status lbdps_batch_time_kernels(lbdps_batch *batch, uint32_t mask);
 lbdps_status lbdps_batch_kernel_times(lbdps_batch *batch, double *h_ms, int64_t *h_launches);

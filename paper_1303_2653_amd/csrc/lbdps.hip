@@ -372,6 +372,7 @@ struct lbdps_ctx {
   };
   std::vector<Mark> marks;
   size_t nmarks = 0;
+  bool open = false;  // the last mark waits for its end
   double ms[LBDPS_K_COUNT] = {0};
   long long launches[LBDPS_K_COUNT] = {0};
   ~lbdps_ctx() {
@@ -554,28 +555,43 @@ void tstop(lbdps_ctx *x, int k) {
   x->nmarks += 1;
 }
 
-// Launches a step kernel on x's stream.  When its phase k is being timed, the
-// launch carries a pair of events that the dispatch itself stamps at the
-// kernel's start and end, so the time is the kernel's own (an event pair
-// recorded around a launch also counts the queue's work between them, a few
-// microseconds).  extra: a further launch of the same phase.
-template <typename F, typename... Args>
-void tlaunch_n(lbdps_ctx *x, int k, bool extra, F kern, dim3 grid, dim3 block, Args... args) {
-  hipEvent_t a = nullptr, b = nullptr;
-  if (x->timed >> k & 1u) {
-    if (x->nmarks == x->marks.size()) {
-      lbdps_ctx::Mark m{};
-      if (hipEventCreate(&m.a) == hipSuccess && hipEventCreate(&m.b) == hipSuccess) x->marks.push_back(m);
-    }
-    if (x->nmarks < x->marks.size()) {
-      lbdps_ctx::Mark &m = x->marks[x->nmarks++];
-      m.k = k;
-      m.extra = extra;
-      a = m.a;
-      b = m.b;
-    }
+// Which end of its phase's launches a launch is.  When the phase is timed, the
+// first launch's dispatch stamps an event at its start and the last one's at its
+// end, so the time is that of the phase's kernels (an event pair recorded around
+// a launch also counts the queue's work between them, a few microseconds).  Each
+// stamped dispatch holds the queue up for about 5 us: with a pair on each of the
+// resolution's three launches the step of a bubbling bed took 94 us, not 60.
+enum Stamp { STAMP_BOTH, STAMP_START, STAMP_NONE, STAMP_END };
+// The events of a launch of phase k for C (a context or a batch); extra: of a
+// further stage of the same phase, whose time adds and whose launch does not count.
+template <class C> void stamps(C *x, int k, bool extra, Stamp at, hipEvent_t &a, hipEvent_t &b) {
+  a = b = nullptr;
+  if (!(x->timed >> k & 1u) || at == STAMP_NONE) return;
+  if (at == STAMP_END) {  // of the mark that the phase's first launch opened
+    if (x->open) b = x->marks[x->nmarks - 1].b;
+    x->open = false;
+    return;
   }
-  if (a)
+  x->open = false;
+  if (x->nmarks == x->marks.size()) {
+    typename std::remove_reference_t<decltype(x->marks)>::value_type m{};
+    if (hipEventCreate(&m.a) != hipSuccess || hipEventCreate(&m.b) != hipSuccess) return;
+    x->marks.push_back(m);
+  }
+  auto &m = x->marks[x->nmarks++];
+  m.k = k;
+  m.extra = extra;
+  a = m.a;
+  if (at == STAMP_BOTH) b = m.b;
+  else x->open = true;
+}
+
+// Launches a step kernel on x's stream.
+template <typename F, typename... Args>
+void tlaunch_n(lbdps_ctx *x, int k, bool extra, Stamp at, F kern, dim3 grid, dim3 block, Args... args) {
+  hipEvent_t a, b;
+  stamps(x, k, extra, at, a, b);
+  if (a || b)
     hipExtLaunchKernelGGL(kern, grid, block, 0, x->stream, a, b, 0, args...);
   else
     hipLaunchKernelGGL(kern, grid, block, 0, x->stream, args...);
@@ -583,7 +599,7 @@ void tlaunch_n(lbdps_ctx *x, int k, bool extra, F kern, dim3 grid, dim3 block, A
 
 template <typename F, typename... Args>
 void tlaunch(lbdps_ctx *x, int k, bool extra, F kern, dim3 grid, Args... args) {
-  tlaunch_n(x, k, extra, kern, grid, dim3(BLOCK), args...);
+  tlaunch_n(x, k, extra, STAMP_BOTH, kern, grid, dim3(BLOCK), args...);
 }
 
 lbdps_status check_hip(hipError_t e, const char *what) {
@@ -759,10 +775,11 @@ template <int P> struct Impl {
       tlaunch(x, LBDPS_K_CONTACTS, extra, tile_kernel(st), dim3(x->sphere_tiles), parts(x, x->cp),
               (const int32_t *)x->cs, k, x->adj(), x->deg, x->done, x->ticket, x->need_sweep, x->chunk_busy,
               x->roots, x->tile_part);
-      tlaunch(x, LBDPS_K_RESOLVE, extra, k_resolve_clusters<P>, dim3(x->cluster_groups()), parts(x, x->cp), x->adj(),
+      tlaunch_n(x, LBDPS_K_RESOLVE, extra, STAMP_START, k_resolve_clusters<P>, dim3(x->cluster_groups()), dim3(BLOCK),
+              parts(x, x->cp), x->adj(),
               (const int32_t *)x->deg, x->done, k, x->need_sweep, x->collc_part, x->wallc_part,
               (const long long *)x->roots, nblocks(N), (const int32_t *)x->need_sweep + SW_ROOTS);
-      tlaunch(x, LBDPS_K_RESOLVE, true, k_resolve<P>, dim3(resolve_blocks(x)), parts(x, x->cp),
+      tlaunch_n(x, LBDPS_K_RESOLVE, extra, STAMP_END, k_resolve<P>, dim3(resolve_blocks(x)), dim3(BLOCK), parts(x, x->cp),
               (const int32_t *)x->slot, x->adj(), (const int32_t *)x->deg, x->done, x->ticket, k, x->flags,
               x->coll_part, x->wall_part, x->chunk_busy, x->need_sweep);
     } else {
@@ -770,16 +787,17 @@ template <int P> struct Impl {
               x->adj(), x->deg, x->flags, x->pair_part, x->wall0_part, x->need_sweep);
       const int np = patch_passes(x->plan);
       for (int i = 0; i < np; ++i)
-        tlaunch(x, LBDPS_K_RESOLVE, true, i == 0 ? k_patches<P, PATCH_HELD0, true> : k_patches<P, PATCH_HELD1, false>,
-                dim3(x->patches[i]), parts(x, x->cp), (const int32_t *)x->cs, k, x->adj(), x->deg,
-                patch_grid(x->p, x->n, i), (int)(i + 1 == np), (int32_t *)x->roots, x->done, x->need_sweep + SW_LEFT,
-                x->need_sweep + SW_FULL, x->pcoll_part[i], x->pwall_part[i]);
+        tlaunch_n(x, LBDPS_K_RESOLVE, extra, i == 0 ? STAMP_START : STAMP_NONE,
+                  i == 0 ? k_patches<P, PATCH_HELD0, true> : k_patches<P, PATCH_HELD1, false>, dim3(x->patches[i]),
+                  dim3(BLOCK), parts(x, x->cp), (const int32_t *)x->cs, k, x->adj(), x->deg,
+                  patch_grid(x->p, x->n, i), (int)(i + 1 == np), (int32_t *)x->roots, x->done, x->need_sweep + SW_LEFT,
+                  x->need_sweep + SW_FULL, x->pcoll_part[i], x->pwall_part[i]);
       if (x->plan == PLAN_CLUSTERS)
-        tlaunch(x, LBDPS_K_RESOLVE, true, clusters_slots(x->n, 1) == 1 ? k_clusters<P, 1> : k_clusters<P, CLUSTERS_SL>,
-                dim3(x->clusters), parts(x, x->cp), k, x->adj(), x->deg, x->need_sweep, x->collc_part, x->wallc_part);
-      // the rest always runs: it is the resolution launch that counts
-      tlaunch_n(x, LBDPS_K_RESOLVE, extra, rest_kernel(x->plan), dim3(x->rests), dim3(FINAL_THREADS), parts(x, x->cp),
-                k, x->adj(), x->deg, x->rest());
+        tlaunch_n(x, LBDPS_K_RESOLVE, extra, STAMP_START,
+                  clusters_slots(x->n, 1) == 1 ? k_clusters<P, 1> : k_clusters<P, CLUSTERS_SL>, dim3(x->clusters),
+                  dim3(BLOCK), parts(x, x->cp), k, x->adj(), x->deg, x->need_sweep, x->collc_part, x->wallc_part);
+      tlaunch_n(x, LBDPS_K_RESOLVE, extra, x->plan == PLAN_WHOLE ? STAMP_BOTH : STAMP_END, rest_kernel(x->plan),
+                dim3(x->rests), dim3(FINAL_THREADS), parts(x, x->cp), k, x->adj(), x->deg, x->rest());
     }
   }
 
@@ -1630,6 +1648,7 @@ struct lbdps_batch {
   uint32_t timed = 0;
   std::vector<lbdps_ctx::Mark> marks;
   size_t nmarks = 0;
+  bool open = false;
   ~lbdps_batch() {
     for (auto &m : marks) {
       (void)hipEventDestroy(m.a);
@@ -1786,24 +1805,6 @@ template <int P> struct BatchImpl {
       default: return LBDPS_K_RESOLVE;  // the patch passes, the clusters and the rest
     }
   }
-  // Events for a timed launch of kernel class k in an eager batched step,
-  // stamped by the dispatch itself (the kernel's own time); false when k is
-  // not timed.  extra: a further launch of the same class in the step.
-  static bool bmark(lbdps_batch *B, int k, bool extra, hipEvent_t &a, hipEvent_t &b) {
-    if (!(B->timed >> k & 1u)) return false;
-    if (B->nmarks == B->marks.size()) {
-      lbdps_ctx::Mark m{};
-      if (hipEventCreate(&m.a) != hipSuccess || hipEventCreate(&m.b) != hipSuccess) return false;
-      B->marks.push_back(m);
-    }
-    lbdps_ctx::Mark &m = B->marks[B->nmarks++];
-    m.k = k;
-    m.extra = extra;
-    a = m.a;
-    b = m.b;
-    return true;
-  }
-
   static void launch_steps(lbdps_batch *B, int t, int nsteps) {
     const BedArgs<P> *tab = (const BedArgs<P> *)B->d_tab[t];
     const int *off = (const int *)(B->d_tab[t] + B->args_bytes);
@@ -1812,17 +1813,18 @@ template <int P> struct BatchImpl {
     const bool timing = t == 0;  // never inside a captured graph
     for (int it = 0; it < nsteps; ++it) {
       const int flip = it & 1;
-#define LBDPS_LAUNCH_N(kern, ph, threads, extra, ...)                                                                \
+#define LBDPS_LAUNCH_N(kern, ph, threads, at, ...)                                                                   \
   if (tot[ph] > 0) {                                                                                                \
     hipEvent_t ea = nullptr, eb = nullptr;                                                                          \
-    if (timing && bmark(B, phase_kernel(ph), extra, ea, eb))                                                        \
+    if (timing) stamps(B, phase_kernel(ph), false, at, ea, eb);                                                     \
+    if (ea || eb)                                                                                                   \
       hipExtLaunchKernelGGL(kern, dim3(tot[ph]), dim3(threads), 0, B->stream, ea, eb, 0, tab, off + (ph) * nb1,     \
                             nbeds, flip, ##__VA_ARGS__);                                                            \
     else                                                                                                            \
       hipLaunchKernelGGL(kern, dim3(tot[ph]), dim3(threads), 0, B->stream, tab, off + (ph) * nb1, nbeds, flip,      \
                          ##__VA_ARGS__);                                                                            \
   }
-#define LBDPS_LAUNCH(kern, ph) LBDPS_LAUNCH_N(kern, ph, BLOCK, false)
+#define LBDPS_LAUNCH(kern, ph) LBDPS_LAUNCH_N(kern, ph, BLOCK, STAMP_BOTH)
       LBDPS_LAUNCH(kb_collide<P>, PH_COLLIDE)
       const bool flat = drag_flat(tot[PH_DRAG]);
       switch (B->tile[t]) {
@@ -1838,14 +1840,16 @@ template <int P> struct BatchImpl {
       LBDPS_LAUNCH(kb_scan<P>, PH_SCAN)
       LBDPS_LAUNCH(kb_scatter<P>, PH_SCATTER)
       LBDPS_LAUNCH(kb_contacts<P>, PH_CONTACTS)
-      // the rest always runs: it is the resolution launch that counts
-      LBDPS_LAUNCH_N((kb_patches<P, PATCH_HELD0, true>), PH_PATCH0, BLOCK, true, 0)
-      LBDPS_LAUNCH_N((kb_patches<P, PATCH_HELD1, false>), PH_PATCH1, BLOCK, true, 1)
-      LBDPS_LAUNCH_N(kb_clusters<P>, PH_CLUSTERS, BLOCK, true)
-      if (tot[PH_CLUSTERS] > 0) {
-        LBDPS_LAUNCH_N((kb_rest<P, true>), PH_REST, FINAL_THREADS, false)
+      // the resolution's first launch is the first of these that has workgroups
+      const bool p0 = tot[PH_PATCH0] > 0, p = p0 || tot[PH_PATCH1] > 0, c = tot[PH_CLUSTERS] > 0;
+      const Stamp end = p || c ? STAMP_END : STAMP_BOTH;
+      LBDPS_LAUNCH_N((kb_patches<P, PATCH_HELD0, true>), PH_PATCH0, BLOCK, STAMP_START, 0)
+      LBDPS_LAUNCH_N((kb_patches<P, PATCH_HELD1, false>), PH_PATCH1, BLOCK, p0 ? STAMP_NONE : STAMP_START, 1)
+      LBDPS_LAUNCH_N(kb_clusters<P>, PH_CLUSTERS, BLOCK, p ? STAMP_NONE : STAMP_START)
+      if (c) {
+        LBDPS_LAUNCH_N((kb_rest<P, true>), PH_REST, FINAL_THREADS, end)
       } else {
-        LBDPS_LAUNCH_N((kb_rest<P, false>), PH_REST, FINAL_THREADS, false)
+        LBDPS_LAUNCH_N((kb_rest<P, false>), PH_REST, FINAL_THREADS, end)
       }
 #undef LBDPS_LAUNCH_N
 #undef LBDPS_LAUNCH
