@@ -167,3 +167,29 @@ def test_stage_time(name, nx, n, part, limit):
         best = min(best, (time.perf_counter() - t0) * 1e5)
     print(name, "us per stage", best, flush=True)
     assert best < limit
+
+
+@pytest.mark.parametrize("name", ["whole", "one-pass", "two-passes", "sparse", "dense", "layer-one", "layer-two"])
+def test_contact_overflow_in_every_course(name):
+    """One particle with more contacts than a row holds: nothing is resolved, every
+    kernel ends, LBDPS_E_CAPACITY is reported, and the bed without it goes on."""
+    make, plan, _ = BEDS[name]
+    cfg = make()
+    nx, ny, d = cfg["nx"], cfg["ny"], cfg["d"]
+    vel = np.zeros((len(cfg["pos"]), 2))
+    u = synth.uniform(5, 80).reshape(-1, 2)
+    at = np.array([0.5 * nx, 0.1 * ny]) + 0.3 * d * (u - 0.5)
+    pos = cfg["pos"].copy()
+    pos[:: len(pos) // 40][:40] = at  # 40 spheres within half a diameter, the number as it was
+    print(name, len(pos), flush=True)
+    sim = L.Sim(dict(cfg, vel=vel), precision="fp32")
+    sim.set_state(None, pos, vel)
+    sim.collide_particles()
+    with pytest.raises(L.LbdpsError) as e:
+        sim.counters()
+    assert e.value.status == L.LBDPS_E_CAPACITY
+    assert sim.row_stats()["plan"] == plan
+    assert (sim.particles()["vel"] == 0).all()
+    sim.set_state(None, cfg["pos"], vel)
+    sim.collide_particles()
+    assert sim.counters()["pairs"] > 0
