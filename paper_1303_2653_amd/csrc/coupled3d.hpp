@@ -792,7 +792,7 @@ __device__ __forceinline__ void resolve_cluster3(Row q, int m, unsigned long lon
                                                  Parts3<typename Prec<P>::T> &pt, int32_t *done, long long &ncoll) {
   using T = typename Prec<P>::T;
   constexpr int NB3 = 2;
-  sort_members(q, m);
+  sort_members<CL_LDS>(q, m);
   for (int i = 0; i < m; ++i) {
     const long long qi = q[i];
     const int u = (int)(qi & 0x1fffffffll);
@@ -892,7 +892,7 @@ __global__ __launch_bounds__(BLOCK) void k3c_clusters(Parts3<typename Prec<P>::T
       const long long r = roots[(size_t)(b0 + lo) * BLOCK + (f - pre[lo])];
       const int s = (int)(r & 0xffffffffll), g = (int)(r >> 32);
       unsigned long long A;
-      const int m = gather_cluster(ql, CL_LDS, s, g, adj, deg, A);
+      const int m = gather_cluster<CL_LDS>(ql, s, g, adj, deg, A);
       if (m > 0) resolve_cluster3<P>(ql, m, A, k, pt, done, ncoll);
       else if (m < 0) atomicOr(need_sweep, 1);  // too large: the ordered sweep takes it
     }

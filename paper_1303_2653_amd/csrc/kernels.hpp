@@ -1659,7 +1659,7 @@ constexpr int CL_LDS = 8;
 constexpr int RC_LISTS = 1;           // candidate lists per resolution workgroup (default)
 constexpr int RC_GROUPS_MAX = 1 << 30;  // most resolution workgroups (default: no limit)
 
-template <int NT> struct LdsColumn {  // entry i of a lane's column of a [CL_LDS][NT] LDS array
+template <int NT> struct LdsColumn {  // entry i of a lane's column of an LDS array [][NT]
   long long *p;
   __device__ long long &operator[](int i) const { return p[i * NT]; }
 };
@@ -1675,18 +1675,19 @@ __device__ __forceinline__ unsigned long long cl_bit(int a, int b) { return 1ull
 
 // Gathers the cluster of candidate slot s (index g) into q[0 .. m) and its
 // contacts into A; returns m, 0 if a member has a lower index than g, and -1
-// if the cluster has more than cap (<= CL_LDS) members.  Members are expanded
+// if the cluster has more than N (<= CL_LDS) members.  Members are expanded
 // two at a time, so the rows of both are loaded together.  The members' slots
 // are also kept in registers, where the membership test looks them up.
-template <class Row>
-__device__ __forceinline__ int gather_cluster(Row q, int cap, int s, int g, Adj adj, const int32_t *deg,
+template <int N, class Row>
+__device__ __forceinline__ int gather_cluster(Row q, int s, int g, Adj adj, const int32_t *deg,
                                               unsigned long long &A) {
+  static_assert(N <= CL_LDS, "the contact matrix has CL_LDS rows");
   q[0] = ((long long)g << 32) | (unsigned)s;
   A = 0;
   int m = 1;
-  int sl[CL_LDS];  // slot of the member at each place, -1 past m
+  int sl[N];  // slot of the member at each place, -1 past m
 #pragma unroll
-  for (int i = 0; i < CL_LDS; ++i) sl[i] = i == 0 ? s : -1;
+  for (int i = 0; i < N; ++i) sl[i] = i == 0 ? s : -1;
   // adds the contacts of the member at place h; false when the candidate gives up
   auto expand = [&](int h, const AdjRow &ru, int du, const Dense4 &e4, int &res) {
     for (int a = 0; a < du; ++a) {
@@ -1698,17 +1699,17 @@ __device__ __forceinline__ int gather_cluster(Row q, int cap, int s, int g, Adj 
       const int es = adj_slot(e);
       int p = -1;
 #pragma unroll
-      for (int i = 0; i < CL_LDS; ++i)
+      for (int i = 0; i < N; ++i)
         if (sl[i] == es) p = i;
       if (p < 0) {
-        if (m == cap) {
+        if (m == N) {
           res = -1;
           return false;
         }
         p = m;
         q[m] = (e & ~0xffffffffll) | ((long long)m << 29) | es;
 #pragma unroll
-        for (int i = 1; i < CL_LDS; ++i)
+        for (int i = 1; i < N; ++i)
           if (i == m) sl[i] = es;
         ++m;
       }
@@ -1720,7 +1721,7 @@ __device__ __forceinline__ int gather_cluster(Row q, int cap, int s, int g, Adj 
     const bool two = head + 1 < m;
     int u0 = s, u1 = s;
 #pragma unroll
-    for (int i = 1; i < CL_LDS; ++i) {
+    for (int i = 1; i < N; ++i) {
       if (i == head) u0 = sl[i];
       if (i == head + 1) u1 = sl[i];
     }
@@ -1740,15 +1741,15 @@ __device__ __forceinline__ int gather_cluster(Row q, int cap, int s, int g, Adj 
 // Orders the m gathered entries by index: all are read at once and each is
 // written to its rank among them (the indices are distinct), so no chain of
 // dependent LDS accesses as an insertion sort would make.
-template <class Row> __device__ __forceinline__ void sort_members(Row q, int m) {
-  long long e[CL_LDS];
+template <int N, class Row> __device__ __forceinline__ void sort_members(Row q, int m) {
+  long long e[N];
 #pragma unroll
-  for (int i = 0; i < CL_LDS; ++i) e[i] = i < m ? q[i] : 0x7fffffffffffffffll;
+  for (int i = 0; i < N; ++i) e[i] = i < m ? q[i] : 0x7fffffffffffffffll;
 #pragma unroll
-  for (int i = 0; i < CL_LDS; ++i) {
+  for (int i = 0; i < N; ++i) {
     int r = 0;
 #pragma unroll
-    for (int j = 0; j < CL_LDS; ++j) r += e[j] < e[i];
+    for (int j = 0; j < N; ++j) r += e[j] < e[i];
     if (i < m) q[r] = e[i];
   }
 }
@@ -1761,17 +1762,17 @@ template <class Row> __device__ __forceinline__ void sort_members(Row q, int m) 
 // records of all members are loaded in one round (registers indexed by the
 // members' places in index order), so the pairs run with no memory round
 // trip between them.
-template <int P, class Row>
+template <int P, int N, class Row>
 __device__ __forceinline__ void resolve_cluster(Row q, int m, unsigned long long A,
                                                 const Consts<typename Prec<P>::T> &k,
                                                 Parts<typename Prec<P>::T> &pt, int32_t *done, long long &ncoll,
                                                 long long &nwall) {
   using T = typename Prec<P>::T;
-  sort_members(q, m);
-  int pl[CL_LDS], kk[CL_LDS];
-  T xx[CL_LDS], yy[CL_LDS], vx[CL_LDS], vy[CL_LDS];
+  sort_members<N>(q, m);
+  int pl[N], kk[N];
+  T xx[N], yy[N], vx[N], vy[N];
 #pragma unroll
-  for (int i = 0; i < CL_LDS; ++i) {
+  for (int i = 0; i < N; ++i) {
     pl[i] = 0;
     if (i < m) {
       const long long qi = q[i];
@@ -1785,11 +1786,11 @@ __device__ __forceinline__ void resolve_cluster(Row q, int m, unsigned long long
     }
   }
 #pragma unroll
-  for (int i = 0; i < CL_LDS; ++i) {
+  for (int i = 0; i < N; ++i) {
     if (i < m) {
       const unsigned nbr = (unsigned)(A >> (8 * pl[i])) & 0xffu;  // places of its neighbours
 #pragma unroll
-      for (int j = i + 1; j < CL_LDS; ++j) {
+      for (int j = i + 1; j < N; ++j) {
         if (j < m && ((nbr >> pl[j]) & 1u)) {
           T dx, dy;
           Pos<P>::sep(k, kk[i], xx[i], yy[i], kk[j], xx[j], yy[j], dx, dy);
@@ -2020,15 +2021,16 @@ __device__ int resolve_group(ClusterLds<P, G> &B, int *shi, int s0, int g, const
 // particle is marked, as DONE_WHOLE with its degree; it may be deg itself.
 template <int P, int NT, int BIG> struct ClustersLds {
   static constexpr int G = NT == BLOCK ? BLOCK : WAVE;
-  // In a workgroup of 1 024 threads a lane has too few registers for a cluster of
-  // its own: the wavefronts take all.
-  static constexpr bool LANES = NT == BLOCK;
+  // Members a lane takes: in a workgroup of 1 024 threads it has registers for
+  // four.  With none there, pairs taken by wavefronts too, the collision stage of
+  // 100 000 spheres in the bottom quarter of 400 x 400 cells took 304 us, not 272.
+  static constexpr int LANE = NT == BLOCK ? CL_LDS : 4;
   long long bigc[BIG], hugec[G == BLOCK ? BIG : 1];
   int nbig, nhuge;
   int shi[BLOCK / 64];
   // the per-lane gathering area, reused afterwards for the group paths
   union {
-    long long qs[CL_LDS * NT];
+    long long qs[LANE * NT];
     ClusterLds<P, WAVE> wave[NT / WAVE];
     ClusterLds<P, G> big;
   };
@@ -2037,19 +2039,18 @@ template <int P, int NT, int BIG, class Cand>
 __device__ __forceinline__ void resolve_candidates(ClustersLds<P, NT, BIG> &S, const int tot, Cand cand,
     Parts<typename Prec<P>::T> pt, Adj adj, const int32_t *deg, int32_t *done,
     const Consts<typename Prec<P>::T> &k, int32_t *more, long long &ncoll, long long &nwall) {
+  constexpr int LANE = ClustersLds<P, NT, BIG>::LANE;
   if (threadIdx.x == 0) S.nbig = S.nhuge = 0;
   __syncthreads();
   const LdsColumn<NT> ql{S.qs + threadIdx.x};
   for (int f = threadIdx.x; f < tot; f += NT) {
     const long long r = cand(f);
     const int s = (int)(r & 0xffffffffll), g = (int)(r >> 32);
-    int m = -1;
-    if constexpr (ClustersLds<P, NT, BIG>::LANES) {
-      unsigned long long A;
-      m = gather_cluster(ql, CL_LDS, s, g, adj, deg, A);
-      if (m > 0) resolve_cluster<P>(ql, m, A, k, pt, done, ncoll, nwall);
-    }
-    if (m < 0) {
+    unsigned long long A;
+    const int m = gather_cluster<LANE>(ql, s, g, adj, deg, A);
+    if (m > 0) {
+      resolve_cluster<P, LANE>(ql, m, A, k, pt, done, ncoll, nwall);
+    } else if (m < 0) {
       const int slot = atomicAdd(&S.nbig, 1);  // the workgroup resolves it below
       if (slot < BIG) S.bigc[slot] = r;
       else atomicOr(more, 1);  // queue full

@@ -60,10 +60,12 @@ constexpr int PATCH_NB = 8;          // partners' places kept in registers
 constexpr int PATCH_NONE = 0xffff;   // no partner, or one outside
 // Bands of rows a patch of the first pass is taken in, before the rest of it is
 // left, and the share (one in PATCH_FLOOD) of the bed that may be left so before
-// the second pass only lists: its patches would be as full.  1 M spheres in the
-// bottom 30 % of a periodic 512 x 4096 riser: 36 + 45 us for the passes, 75 + 79
-// without the limits.  Beds laid out about right take two bands at most.
-constexpr int PATCH_BANDS = 3, PATCH_FLOOD = 16;
+// the second pass only lists: its patches would be as full.  Beds laid out about
+// right take two bands at most.  The collision stage of 1 M spheres in the bottom
+// 40 % of a periodic 1000 x 1600 lattice takes 590, 320 and 250 us with 3, 4 and 6
+// bands, and as long with 12; of 100 000 in a quarter of 400 x 400 cells 272 us
+// with 6, 302 with 12.
+constexpr int PATCH_BANDS = 6, PATCH_FLOOD = 16;
 // Particles a patch's workgroup looks at together: of the first pass, where about
 // half of them have contacts, and of the second, where few are left.
 constexpr int PATCH_HELD0 = 2 * BLOCK, PATCH_HELD1 = 8 * BLOCK;
@@ -758,9 +760,9 @@ __device__ __forceinline__ void final_mem(const FinalMem M, Parts<typename Prec<
 // all workgroups have taken its clusters; of a bed resolved by clusters those too
 // large for a workgroup.  The final workgroup is then the one that ends last; if
 // there is nothing to do before it, the others end at once.  At most one
-// workgroup per CU, since each has the LDS of the final one.  1 M spheres in the
-// bottom 30 % of a riser laid out for twice the height, 300 000 of them left: 180
-// us, against 250 with a pass of wider patches and the final workgroup in memory.
+// workgroup per CU, since each has the LDS of the final one.  The collision stage
+// of 100 000 spheres in the bottom quarter of 400 x 400 cells takes 272 us, against
+// 531 with a pass of wider patches and the final workgroup in memory.
 constexpr int REST_BLOCKS = 256, REST_BIG = 512;
 struct RestBuffers {
   int32_t *left, *left2, *place_of;
